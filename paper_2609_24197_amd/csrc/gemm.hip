@@ -30,6 +30,7 @@
 // a bf16 plane carries 8, so one product does what a bf16 hi/lo pair would otherwise be needed
 // for.  More than 128 rows run as 128-row launches, one after the other.
 #include <algorithm>
+#include <initializer_list>
 #include <utility>
 
 #include "common.h"
@@ -522,7 +523,7 @@ skinny_kernel(GemmArgs g, int kper, int nitems) {
 }
 
 // Sum of the split-K partials in k-part order, then the usual epilogue.
-__global__ void __launch_bounds__(256) skinny_reduce(GemmArgs g, int nparts) {
+__global__ void __launch_bounds__(256) split_reduce(GemmArgs g, int nparts) {
   const size_t total = (size_t)g.M * g.N;
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
     const int m = (int)(e / g.N), n = (int)(e % g.N);
@@ -550,7 +551,7 @@ __global__ void __launch_bounds__(256) skinny_reduce(GemmArgs g, int nparts) {
 
 // The same for 4 consecutive columns per thread (N % 4 == 0, and ldc, ldr, ldch % 4 == 0):
 // 16-byte loads of the partials, 8 k-parts issued together, then 16-byte stores.
-__global__ void __launch_bounds__(256) skinny_reduce4(GemmArgs g, int nparts) {
+__global__ void __launch_bounds__(256) split_reduce4(GemmArgs g, int nparts) {
   constexpr int GROUP = 8;
   const size_t total = (size_t)g.M * g.N, quads = total / 4;
   for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
@@ -599,6 +600,18 @@ __global__ void __launch_bounds__(256) skinny_reduce4(GemmArgs g, int nparts) {
       if (g.C_l16) *reinterpret_cast<f16x4*>(g.C_l16 + (size_t)m * g.ldch + n) = l;
     }
   }
+}
+
+// Sum of nparts partial planes [M][N] in g.part, with the product's epilogue.
+hipError_t launch_reduce(const GemmArgs& g, int nparts, hipStream_t s) {
+  const size_t total = (size_t)g.M * g.N;
+  const bool vec = g.N % 4 == 0 && (!g.C || g.ldc % 4 == 0) && (!g.R || g.ldr % 4 == 0) &&
+                   (!(g.C_hi || g.C_h16) || g.ldch % 4 == 0);
+  size_t blocks = ((vec ? total / 4 : total) + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  if (vec) hipLaunchKernelGGL(split_reduce4, dim3((unsigned)blocks), dim3(256), 0, s, g, nparts);
+  else hipLaunchKernelGGL(split_reduce, dim3((unsigned)blocks), dim3(256), 0, s, g, nparts);
+  return hipGetLastError();
 }
 
 int device_cus() {
@@ -664,15 +677,7 @@ hipError_t launch_skinny_t(const GemmArgs& g, const SkPlan& p, hipStream_t s) {
   const int grid = p.ksplit == 1 && nitems > device_cus() ? device_cus() : nitems;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(S::NT), 0, s, g, p.kper, nitems);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.ksplit == 1) return e;
-  const size_t total = (size_t)g.M * g.N;
-  const bool vec = g.N % 4 == 0 && (!g.C || g.ldc % 4 == 0) && (!g.R || g.ldr % 4 == 0) &&
-                   (!(g.C_hi || g.C_h16) || g.ldch % 4 == 0);
-  size_t blocks = ((vec ? total / 4 : total) + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  if (vec) hipLaunchKernelGGL(skinny_reduce4, dim3((unsigned)blocks), dim3(256), 0, s, g, p.ksplit);
-  else hipLaunchKernelGGL(skinny_reduce, dim3((unsigned)blocks), dim3(256), 0, s, g, p.ksplit);
-  return hipGetLastError();
+  return e != hipSuccess || p.ksplit == 1 ? e : launch_reduce(g, p.ksplit, s);
 }
 
 template <int MT, bool ALO>
@@ -691,30 +696,6 @@ hipError_t launch_skinny_a(const GemmArgs& g, const SkPlan& p, hipStream_t s) {
   if (g.M <= 64) return launch_skinny_m<4, ALO>(g, p, s);
   return launch_skinny_m<8, ALO>(g, p, s);
 }
-
-// ------------------------------------------------------------- pipelined dense path
-//
-// Many rows (M >= 128): 128 x 128 output tiles, 4 waves of 64 x 64 (v_mfma_f32_32x32x16_bf16).
-// A and W k-tiles (KT = 64 or 32 wide) go straight from global memory into LDS
-// (global_load_lds_dwordx4), ST stages deep, so ST-1 tiles are in flight while one is
-// multiplied; every LDS stage is its own object so that the compiler's wait for outstanding
-// LDS DMA names only the stage being read.  Rows past M or N re-read the last valid row (their
-// results are never stored); K must be a multiple of KT.  With KT = 32 a workgroup needs at
-// most 72 KB of LDS, so two share a CU and each covers the other's waits for memory.
-
-template <int TM, int TN, bool ALO, int ST, int KT>
-struct DmaCfg {
-  static constexpr int NT = 256;
-  static constexpr int BM = 2 * TM * 32, BN = 2 * TN * 32;
-  static constexpr int CPRT = KT / 8;                               // 16-byte units per tile row
-  static constexpr int SA = BM * KT, SW = BN * KT;                  // elements per plane per stage
-  static constexpr int STAGE = SA * (ALO ? 2 : 1) + SW;
-  static constexpr int A_I = BM * CPRT / NT, W_I = BN * CPRT / NT; // DMA instructions per wave
-  static constexpr int NI = A_I * (ALO ? 2 : 1) + W_I;
-  static constexpr int VM = (ST - 2) * NI;
-  static_assert(KT == 64 || KT == 32, "k-tile");
-  static_assert(BM * CPRT % NT == 0 && BN * CPRT % NT == 0 && VM < 64 && ST >= 2 && ST <= 4, "dma gemm shape");
-};
 
 // LDS unit (16 bytes) of logical chunk `chunk` of tile row `row` in a KT-wide tile.  Rows of
 // 128 bytes (KT = 64) XOR the chunk with (row / 2) mod 8, rows of 64 bytes (KT = 32) with
@@ -757,77 +738,119 @@ __device__ __forceinline__ void store_block32(const GemmArgs& g, const f32x16& a
   }
 }
 
-template <int TM, int TN, bool ALO, int ST, int KT>
-__global__ void __launch_bounds__(256) gemm_dma_kernel(GemmArgs g) {
-  using C = DmaCfg<TM, TN, ALO, ST, KT>;
-  // one LDS object per (stage, operand): the A planes and the W tile of stage s
-  constexpr int PA = C::SA * (ALO ? 2 : 1);
-  __shared__ __align__(16) bf16 A0s[PA], W0s[C::SW];
-  __shared__ __align__(16) bf16 A1s[PA], W1s[C::SW];
-  __shared__ __align__(16) bf16 A2s[ST > 2 ? PA : 8], W2s[ST > 2 ? C::SW : 8];
-  __shared__ __align__(16) bf16 A3s[ST > 3 ? PA : 8], W3s[ST > 3 ? C::SW : 8];
-  auto sa_of = [&](auto I) -> bf16* {
-    if constexpr (decltype(I)::value == 0) return A0s;
-    else if constexpr (decltype(I)::value == 1) return A1s;
-    else if constexpr (decltype(I)::value == 2) return A2s;
-    else return A3s;
-  };
-  auto sw_of = [&](auto I) -> bf16* {
-    if constexpr (decltype(I)::value == 0) return W0s;
-    else if constexpr (decltype(I)::value == 1) return W1s;
-    else if constexpr (decltype(I)::value == 2) return W2s;
-    else return W3s;
-  };
+// ---------------------------------------------------------------------------------------
+// Streamed products: row-major W at up to a few hundred rows (and up to one round of 128 x 128
+// tiles beyond that).  Bound by the stream over W from HBM at few rows, by the matrix units from
+// about 128 rows with hi/lo A; what the older kernels lacked was bytes in flight: 128 x 128 tiles
+// of 32-wide k-tiles kept 16 KB of W under way per CU, and a short N left most CUs idle.
+//   * One workgroup of eight waves per CU: 128 columns, 32, 64 or 128 rows, 64-wide k-tiles (whole
+//     128-byte lines of W), as many LDS stages as fit (3 to 6: 32 to 80 KB of W in flight per CU).
+//   * The eight waves are two groups of four that take alternate halves of every k-tile, so a wave
+//     owns 64 x 64 (32 x 64, 32 x 32) of the tile and each fragment read feeds as many products as
+//     four waves would; the groups' sums meet in LDS at the end.
+//   * K is split until the chip is covered (stream_plan); each part writes a plane of fp32 sums.
+//   * Column tiles start their walk over K at different k-tiles: rows of W are a power of two
+//     apart, so workgroups in step would all read the same memory channels (16 x 16768 x 4096:
+//     37 -> 30 us).
+// Measured (weights out of cache, reduction included, before -> after): 128 x 6144 x 4096 hi/lo
+// 62 -> 26 us, 128 x 24576 x 4096 hi/lo 166 -> 70, 128 x 4096 x 12288 hi/lo 69 -> 38,
+// 48 x 32000 x 4096 70 -> 46 (5.6 TB/s), 16 x 16768 x 4096 52 -> 30, 217 x 6144 x 4096 47 -> 27,
+// 1024 x 4096 x 4096 53 -> 41, 1024 x 4096 x 8192 90 -> 78.
+// Tried and not kept: even shares of all k-tiles per workgroup across tile boundaries (75-80 us at
+// 128 x 24576 x 4096 hi/lo), A stored k-tile by k-tile (no change).
+#ifndef HSPEC_BIG_MIN_M
+#define HSPEC_BIG_MIN_M 256   // rows from which products of many tiles take the large tiles
+#endif
+constexpr int SG_KT = 64, SG_NT = 512, SG_BN = 128;
 
-  const int mt_count = (g.M + C::BM - 1) / C::BM;
-  const int nt_count = (g.N + C::BN - 1) / C::BN;
-  int mt, nt;
-  tile_of(blockIdx.x, mt_count * nt_count, mt_count, mt, nt);
-  const int m0 = mt * C::BM, n0 = nt * C::BN;
+struct StreamPlan {
+  int bm = 0;                   // row-tile height (0: the product is not served)
+  int mt = 0, nt = 0;           // tile grid
+  int ksplit = 1, kper = 0;     // k-parts of kper k-tiles
+  float* out = nullptr;         // sums of k-part i: out + i * plane, rows of ld elements
+  size_t plane = 0;
+  int ld = 0;
+  int add_r = 0;                // add the residual in the epilogue (whole tiles written to C)
+};
+
+template <int BMV, int NP, int ST>
+struct StreamCfg {
+  static constexpr int BM = BMV, BN = SG_BN;
+  static constexpr int WM = BM >= 64 ? 2 : 1, WN = 4 / WM;      // waves of one k-group
+  static constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
+  static constexpr int SA = BM * SG_KT, SW = BN * SG_KT;        // elements per plane per stage
+  static constexpr int STAGE = SA * NP + SW;
+  static constexpr int A_I = BM >= 64 ? BM / 64 : 1, W_I = BN / 64;   // DMA per wave (1 KB each)
+  static constexpr int NI = A_I * NP + W_I;
+  static constexpr int VM = (ST - 2) * NI;
+  static_assert(VM < 64 && ST >= 2 && ST <= 6, "stream gemm shape");
+  static_assert(STAGE * 2 >= 4 * TM * 16 * 64 * 4, "k-group exchange fits a stage");
+};
+
+template <int BMV, int NP, int ST>
+__global__ void __launch_bounds__(SG_NT) gemm_stream_kernel(GemmArgs g, StreamPlan p) {
+  using C = StreamCfg<BMV, NP, ST>;
+  constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN;
+  __shared__ __align__(16) bf16 s0[C::STAGE], s1[C::STAGE];
+  __shared__ __align__(16) bf16 s2[ST > 2 ? C::STAGE : 8], s3[ST > 3 ? C::STAGE : 8];
+  __shared__ __align__(16) bf16 s4[ST > 4 ? C::STAGE : 8], s5[ST > 5 ? C::STAGE : 8];
+  auto stage = [&](auto I) __attribute__((always_inline)) -> bf16* {
+    if constexpr (decltype(I)::value == 0) return s0;
+    else if constexpr (decltype(I)::value == 1) return s1;
+    else if constexpr (decltype(I)::value == 2) return s2;
+    else if constexpr (decltype(I)::value == 3) return s3;
+    else if constexpr (decltype(I)::value == 4) return s4;
+    else return s5;
+  };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / 2, wn = wave % 2;
+  const int kg = wave >> 2, wm = (wave & 3) / C::WN, wn = (wave & 3) % C::WN;
 
-  const int rows_a = min(C::BM, g.M - m0);
-  const bf16* A0 = g.A_hi + (size_t)m0 * g.lda;
-  const bf16* Al0 = (ALO ? g.A_lo : g.A_hi) + (size_t)m0 * g.lda;
-  // W row segment of this tile (tiles never straddle a segment boundary)
-  const bf16* wbase = g.W_hi;
+  int mt, v;
+  tile_of(blockIdx.x, p.mt * p.nt * p.ksplit, p.mt, mt, v);
+  const int nt = v % p.nt, kp = v / p.nt;
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int kb = kp * p.kper, nk = min(g.K / SG_KT, kb + p.kper) - kb;
+
+  const int rows_a = min(BM, g.M - m0);
+  const bf16* wbase = g.W_hi;   // W row segment of this tile (tiles never straddle one)
   int wseg0 = 0, wseg1 = g.N;
   if (g.W2) {
     if (n0 >= g.N1 + g.N2) { wbase = g.W3; wseg0 = g.N1 + g.N2; }
     else if (n0 >= g.N1) { wbase = g.W2; wseg0 = g.N1; wseg1 = g.N1 + g.N2; }
     else wseg1 = g.N1;
   }
-  const int rows_w = min(C::BN, wseg1 - n0);
-
-  // unit u (16 bytes) of a stage plane: row u / CPRT, stored chunk u % CPRT = logical chunk ^
-  // swz_key_t(row).  Source offsets of k-tile 0 per lane; k-tile t adds t * (a_step, w_step).
-  size_t a_off[C::A_I], w_off[C::W_I];
+  const int rows_w = min(BN, wseg1 - n0);
+  const bf16* Ab = g.A_hi + (size_t)m0 * g.lda + (size_t)kb * SG_KT;
+  const bf16* Alb = (NP == 2 ? g.A_lo : g.A_hi) + (size_t)m0 * g.lda + (size_t)kb * SG_KT;
+  const bf16* Wb = wbase + (size_t)(n0 - wseg0) * g.ldw + (size_t)kb * SG_KT;
+  // unit q (16 bytes) of a plane: row q / 8, stored chunk q % 8 = logical chunk ^ key(row)
+  int a_off[C::A_I], w_off[C::W_I];
 #pragma unroll
   for (int i = 0; i < C::A_I; ++i) {
-    const int u = (i * 4 + wave) * 64 + lane, row = u / C::CPRT;
-    const int k = 8 * ((u % C::CPRT) ^ swz_key_t<KT>(row));
-    a_off[i] = (size_t)min(row, rows_a - 1) * g.lda + k;
+    const int u = (i * 8 + (BM >= 64 ? wave : (wave & 3))) * 64 + lane, row = u / 8;
+    a_off[i] = min(row, rows_a - 1) * g.lda + 8 * ((u % 8) ^ swz_key_t<64>(row));
   }
 #pragma unroll
   for (int i = 0; i < C::W_I; ++i) {
-    const int u = (i * 4 + wave) * 64 + lane, row = u / C::CPRT;
-    const int k = 8 * ((u % C::CPRT) ^ swz_key_t<KT>(row));
-    const int n = n0 + min(row, rows_w - 1);
-    w_off[i] = (size_t)(n - wseg0) * g.ldw + k;
+    const int u = (i * 8 + wave) * 64 + lane, row = u / 8;
+    w_off[i] = min(row, rows_w - 1) * g.ldw + 8 * ((u % 8) ^ swz_key_t<64>(row));
   }
-  const size_t w_step = (size_t)KT;
-  auto issue = [&](int t, bf16* L, bf16* LW) {
-    const size_t ka = (size_t)t * KT, kw = (size_t)t * w_step;
+  // each column tile walks its k-tiles from its own start, so that the workgroups do not all
+  // read the same columns of W and A (the same memory channels) at once
+  const int rot = nt % nk;
+  auto issue = [&](int t, bf16* L) __attribute__((always_inline)) {
+    int k = t + rot;
+    if (k >= nk) k -= nk;
+    const bf16 *wk = Wb + (size_t)k * SG_KT, *ak = Ab + (size_t)k * SG_KT, *alk = Alb + (size_t)k * SG_KT;
+#pragma unroll
+    for (int i = 0; i < C::W_I; ++i) dma16(wk + w_off[i], L + (C::SA * NP + (i * 8 + wave) * 64 * 8));
 #pragma unroll
     for (int i = 0; i < C::A_I; ++i) {
-      const int u0 = (i * 4 + wave) * 64;
-      dma16(A0 + a_off[i] + ka, L + u0 * 8);
-      if constexpr (ALO) dma16(Al0 + a_off[i] + ka, L + C::SA + u0 * 8);
+      const int q0 = (i * 8 + (BM >= 64 ? wave : (wave & 3))) * 64 * 8;
+      dma16(ak + a_off[i], L + q0);
+      if constexpr (NP == 2) dma16(alk + a_off[i], L + (C::SA + q0));
     }
-#pragma unroll
-    for (int i = 0; i < C::W_I; ++i) dma16(wbase + w_off[i] + kw, LW + (i * 4 + wave) * 64 * 8);
   };
 
   f32x16 acc[TM][TN];
@@ -838,100 +861,205 @@ __global__ void __launch_bounds__(256) gemm_dma_kernel(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
-  // Fragments of k-step ks + 1 are read while the MFMAs of k-step ks run.
-  auto compute = [&](const bf16* L, const bf16* LW) {
-    const bf16* sA = L;
-    const bf16* sAl = L + C::SA;
-    const bf16* sW = LW;
-    bf16x8 fa[2][TM], fal[2][ALO ? TM : 1], fw[2][TN];
-    auto frags = [&](int ks, int buf) {
-      const int ch = 2 * ks + (lane >> 5);
+  // element offsets of this lane's fragments within a stage (one offset per read: a pointer built
+  // in several steps loses the record of which stage it reads, and with it the exact waits)
+  int a_fr[2][TM], w_fr[2][TN];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int ch = 4 * kg + 2 * ks + (lane >> 5);
+#pragma unroll
+    for (int a = 0; a < TM; ++a) a_fr[ks][a] = 8 * swz_t<64>((wm * TM + a) * 32 + (lane & 31), ch);
+#pragma unroll
+    for (int b = 0; b < TN; ++b) w_fr[ks][b] = C::SA * NP + 8 * swz_t<64>((wn * TN + b) * 32 + (lane & 31), ch);
+  }
+  // one k-tile: every fragment of this k-group's two k-steps is read, then refill() issues the
+  // DMA of a later tile, then the products
+  auto compute = [&](const bf16* L, auto refill) __attribute__((always_inline)) {
+    bf16x8 fa[2][TM], fl[2][NP == 2 ? TM : 1], fw[2][TN];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int b = 0; b < TN; ++b) fw[ks][b] = *reinterpret_cast<const bf16x8*>(L + w_fr[ks][b]);
 #pragma unroll
       for (int a = 0; a < TM; ++a) {
-        const int r = (wm * TM + a) * 32 + (lane & 31);
-        fa[buf][a] = *reinterpret_cast<const bf16x8*>(sA + 8 * swz_t<KT>(r, ch));
-        if constexpr (ALO) fal[buf][a] = *reinterpret_cast<const bf16x8*>(sAl + 8 * swz_t<KT>(r, ch));
+        fa[ks][a] = *reinterpret_cast<const bf16x8*>(L + a_fr[ks][a]);
+        if constexpr (NP == 2) fl[ks][a] = *reinterpret_cast<const bf16x8*>(L + (C::SA + a_fr[ks][a]));
       }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    refill();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < TN; ++b) {
-        const int r = (wn * TN + b) * 32 + (lane & 31);
-        fw[buf][b] = *reinterpret_cast<const bf16x8*>(sW + 8 * swz_t<KT>(r, ch));
-      }
-    };
-    frags(0, 0);
-#pragma unroll
-    for (int ks = 0; ks < KT / 16; ++ks) {
-      if (ks + 1 < KT / 16) frags(ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);   // the next k-step's LDS reads go out before these MFMAs
-      const int cb = ks & 1;
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-          acc[a][b] = mma32(fa[cb][a], fw[cb][b], acc[a][b]);
-          if constexpr (ALO) acc[a][b] = mma32(fal[cb][a], fw[cb][b], acc[a][b]);
+          acc[a][b] = mma32(fa[ks][a], fw[ks][b], acc[a][b]);
+          if constexpr (NP == 2) acc[a][b] = mma32(fl[ks][a], fw[ks][b], acc[a][b]);
         }
-    }
   };
 
-  const int nk = (g.K + KT - 1) / KT;
-  // prologue without branches (tiles past the end re-read the last one into unused stages),
-  // so that the compiler's record of which stage each pending DMA fills stays exact
   [&]<int... I>(std::integer_sequence<int, I...>) {
-    (issue(min(I, nk - 1), sa_of(Int<I>{}), sw_of(Int<I>{})), ...);
+    (issue(min(I, nk - 1), stage(Int<I>{})), ...);
   }(std::make_integer_sequence<int, ST - 1>{});
-  // steady state: straight-line rounds of ST steps, each waiting for its own tile only
-  auto steady = [&](int t, auto S) {
+  auto steady = [&](int t, auto S) __attribute__((always_inline)) {
     wait_vm_lgkm0<C::VM>();
-    wg_barrier();   // tile t is in LDS for every wave; every wave is done reading tile t-1
+    wg_barrier();
     constexpr int N = (decltype(S)::value + ST - 1) % ST;
-    issue(t + ST - 1, sa_of(Int<N>{}), sw_of(Int<N>{}));
-    compute(sa_of(S), sw_of(S));
+    compute(stage(S), [&]() __attribute__((always_inline)) { issue(t + ST - 1, stage(Int<N>{})); });
   };
-  auto step = [&](int t, auto S) {
+  auto step = [&](int t, auto S) __attribute__((always_inline)) {
     if (t + ST - 2 < nk) wait_vm_lgkm0<C::VM>();
     else wait_vm_lgkm0<0>();
     wg_barrier();
     constexpr int N = (decltype(S)::value + ST - 1) % ST;
-    if (t + ST - 1 < nk) issue(t + ST - 1, sa_of(Int<N>{}), sw_of(Int<N>{}));
-    compute(sa_of(S), sw_of(S));
+    if (t + ST - 1 < nk) issue(t + ST - 1, stage(Int<N>{}));
+    compute(stage(S), []() __attribute__((always_inline)) {});
   };
   int t0 = 0;
   for (; t0 + 2 * ST - 2 < nk; t0 += ST) {
-    [&]<int... I>(std::integer_sequence<int, I...>) {
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
       (steady(t0 + I, Int<I>{}), ...);
     }(std::make_integer_sequence<int, ST>{});
   }
   for (; t0 < nk; t0 += ST) {
-    [&]<int... I>(std::integer_sequence<int, I...>) {
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
       ((t0 + I < nk ? step(t0 + I, Int<I>{}) : void()), ...);
     }(std::make_integer_sequence<int, ST>{});
   }
+  wait_vm_lgkm0<0>();
+  wg_barrier();   // every wave is done with the stages
 
+  // the two k-groups' sums meet: group 1 hands over column block 0, group 0 the last one
+  static_assert(TN <= 2, "one column block per k-group");
+  f32x4* ex0 = reinterpret_cast<f32x4*>(s0);
+  f32x4* ex1 = reinterpret_cast<f32x4*>(s1);
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int b = 0; b < TN; ++b)
-      store_block32(g, acc[a][b], m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane);
+    for (int q = 0; q < 4; ++q) {
+      const int o = (((wave & 3) * TM + a) * 4 + q) * 64 + lane;
+      if (kg == 1) ex0[o] = f32x4{acc[a][0][4 * q], acc[a][0][4 * q + 1], acc[a][0][4 * q + 2], acc[a][0][4 * q + 3]};
+      else if (TN > 1) ex1[o] = f32x4{acc[a][TN - 1][4 * q], acc[a][TN - 1][4 * q + 1], acc[a][TN - 1][4 * q + 2], acc[a][TN - 1][4 * q + 3]};
+    }
+  __syncthreads();
+  if (TN == 1 && kg == 1) return;
+  const f32x4* ex = kg ? ex1 : ex0;
+  const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
+  const __amdgpu_buffer_rsrc_t rs = buf(p.out + (size_t)kp * p.plane + (size_t)m0 * p.ld + n0, 0x7ffffeff);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) {
+    const int mb = (wm * TM + a) * 32 + 4 * (lane >> 5), nb = (wn * TN + (kg ? TN - 1 : 0)) * 32 + (lane & 31);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 o = ex[(((wave & 3) * TM + a) * 4 + q) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float r = kg == 0 ? acc[a][0][4 * q + e] + o[e] : acc[a][TN - 1][4 * q + e] + o[e];
+        const int m = mb + 8 * q + e;
+        const bool in = m < rows && nb < cols;
+        if (p.add_r && in) {
+          const size_t ro = (size_t)(m0 + m) * g.ldr + n0 + nb;
+          r += g.r_bf16 ? bf2f(reinterpret_cast<const bf16*>(g.R)[ro]) : reinterpret_cast<const float*>(g.R)[ro];
+        }
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r), rs, in ? (m * p.ld + nb) * 4 : SK_OOB, 0, 0);
+      }
+    }
+  }
 }
 
-template <int TM, int TN, bool ALO, int ST, int KT>
-hipError_t launch_dma(const GemmArgs& g, hipStream_t s) {
-  using C = DmaCfg<TM, TN, ALO, ST, KT>;
-  const int tiles = ((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
-  hipLaunchKernelGGL((gemm_dma_kernel<TM, TN, ALO, ST, KT>), dim3(tiles), dim3(C::NT), 0, s, g);
-  return hipGetLastError();
+// Rows of a streamed tile: as few as cover M, up to 128.
+constexpr int stream_bm(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+
+// Work division of a streamed product, bm = 0 if it is not served.  The split over K minimises an
+// estimate fitted to the measured products above: rounds of the CUs times k-tiles per workgroup
+// (three more for its start and end), no less than W at the streaming rate, and the planes'
+// traffic and reduction.
+// From 256 rows only products whose 128 x 128 tiles fit one round of CUs: beyond that the large
+// tiles are faster (1024 x 6144 x 4096: 74 us against 78; 512 x 24576 x 4096 hi/lo 195 against 211),
+// within it these (1024 x 4096 x 4096: 41 us against 53; 512 x 6320 x 4096: 40 against 50).
+StreamPlan stream_plan(int M, int N, int K, bool a_lo, int cus) {
+  StreamPlan p;
+  if (M <= 0 || N <= 0 || K <= 0 || K % SG_KT) return p;
+  const int bm = stream_bm(M);
+  const long long mt = (M + bm - 1) / bm, nt = ((long long)N + SG_BN - 1) / SG_BN, tiles = mt * nt;
+  if (M >= HSPEC_BIG_MIN_M && tiles > cus) return p;
+  if (tiles * 16 > 0x7fffffffLL) return p;
+  const int nk = K / SG_KT;
+  const double step = bm == 32 ? 0.42 : bm == 64 ? (a_lo ? 0.6 : 0.45) : (a_lo ? 1.05 : 0.6);   // us
+  const double stream = (double)N * K * 2 / 5.3e6;
+  double best = 0;
+  for (int ks = 1; ks <= 16 && (ks == 1 || nk / ks >= 4); ++ks) {
+    const int kper = (nk + ks - 1) / ks;
+    if ((nk + kper - 1) / kper != ks) continue;
+    const double rounds = (double)((tiles * ks + cus - 1) / cus);
+    double t = std::max(rounds * (kper + 3) * step, stream);
+    if (ks > 1) t += 3 + (double)ks * M * N * 8 / 4e6;
+    if (p.bm == 0 || t < best) {
+      best = t;
+      p.bm = bm;
+      p.mt = (int)mt;
+      p.nt = (int)nt;
+      p.ksplit = ks;
+      p.kper = kper;
+    }
+  }
+  return p;
 }
 
-#ifndef HSPEC_DMA_KT
-#define HSPEC_DMA_KT 32
-#endif
-// The dense products of the step (M = B k rows): 128 x 128 tiles, KT-wide k-tiles.
-hipError_t launch_dense(const GemmArgs& g, hipStream_t s) {
-  if constexpr (HSPEC_DMA_KT == 32)
-    return g.A_lo ? launch_dma<2, 2, true, 3, 32>(g, s) : launch_dma<2, 2, false, 4, 32>(g, s);
-  else
-    return g.A_lo ? launch_dma<2, 2, true, 3, 64>(g, s) : launch_dma<2, 2, false, 4, 64>(g, s);
+// Outputs other than fp32 C (+ R) are written by the reduction of the planes, for products of at
+// most this many elements (larger ones keep the kernels that write them directly).
+constexpr long long kStreamPlaneMax = 1LL << 22;
+
+// The plan launch_gemm runs a product with on the streamed path, bm = 0 if another path takes it.
+StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
+  StreamPlan p;
+  if (g.W_lo || g.w_packed || g.f16) return p;
+  if (g.W2 && (g.N1 % SG_BN || g.N2 % SG_BN)) return p;
+  // 16-byte LDS DMA
+  for (const void* q : {(const void*)g.A_hi, (const void*)g.A_lo, (const void*)g.W_hi, (const void*)g.W2, (const void*)g.W3})
+    if ((uintptr_t)q % 16) return p;
+  if (g.lda % 8 || g.ldw % 8) return p;
+  // 32-bit element offsets inside a tile's rows of A, W and the output
+  const int ldo = std::max(g.ldc, g.N);
+  if (128LL * g.lda >= (1LL << 31) || 128LL * g.ldw >= (1LL << 31) || 128LL * ldo * 4 >= 0x7ffffeffLL) return p;
+  p = stream_plan(g.M, g.N, g.K, g.A_lo != nullptr, cus);
+  if (!p.bm) return p;
+  const bool plain = g.C && !g.C_hi && !g.C_h16 && g.out_scale == 1.f;
+  if (!plain && (long long)g.M * g.N > kStreamPlaneMax) p.bm = 0;
+  if (p.ksplit > 1 && (!g.part || g.part_cap < (size_t)p.ksplit * g.M * g.N)) {
+    p.ksplit = 1;   // no room for the planes
+    p.kper = g.K / SG_KT;
+  }
+  if (!plain && (!g.part || g.part_cap < (size_t)p.ksplit * g.M * g.N)) p.bm = 0;
+  if (p.bm && plain && p.ksplit == 1) {
+    p.out = g.C;
+    p.ld = g.ldc;
+    p.add_r = g.R != nullptr;
+  } else {
+    p.out = g.part;
+    p.ld = g.N;
+    p.plane = (size_t)g.M * g.N;
+  }
+  return p;
+}
+
+hipError_t launch_stream(const GemmArgs& g, const StreamPlan& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.mt * p.nt * p.ksplit)), nt(SG_NT);
+  if (p.bm == 32) {
+    if (g.A_lo) hipLaunchKernelGGL((gemm_stream_kernel<32, 2, 6>), grid, nt, 0, s, g, p);
+    else hipLaunchKernelGGL((gemm_stream_kernel<32, 1, 6>), grid, nt, 0, s, g, p);
+  } else if (p.bm == 64) {
+    if (g.A_lo) hipLaunchKernelGGL((gemm_stream_kernel<64, 2, 4>), grid, nt, 0, s, g, p);
+    else hipLaunchKernelGGL((gemm_stream_kernel<64, 1, 6>), grid, nt, 0, s, g, p);
+  } else {
+    if (g.A_lo) hipLaunchKernelGGL((gemm_stream_kernel<128, 2, 3>), grid, nt, 0, s, g, p);
+    else hipLaunchKernelGGL((gemm_stream_kernel<128, 1, 4>), grid, nt, 0, s, g, p);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.out == g.C) return e;
+  return launch_reduce(g, p.ksplit, s);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -948,9 +1076,6 @@ hipError_t launch_dense(const GemmArgs& g, hipStream_t s) {
 // kernel sums in k-part order, so the result does not depend on scheduling.
 #ifndef HSPEC_BIG_ST
 #define HSPEC_BIG_ST 4
-#endif
-#ifndef HSPEC_BIG_MIN_M
-#define HSPEC_BIG_MIN_M 256   // rows from which products take the large tiles
 #endif
 constexpr int GB_KT = 32, GB_NT = 512, GB_ST = HSPEC_BIG_ST;
 
@@ -1385,6 +1510,9 @@ size_t gemm_scratch_elems(int M, int N, int K, bool a_lo, bool w_lo) {
   for (const bool lo : {a_lo, false}) {
     const SkPlan p = skinny_plan(M, N, K, lo, w_lo, device_cus());
     if (p.use && p.ksplit > 1) n = std::max(n, (size_t)p.ksplit * M * N);
+    if (w_lo) continue;
+    const StreamPlan q = stream_plan(M, N, K, lo, device_cus());
+    if (q.bm && (q.ksplit > 1 || (long long)M * N <= kStreamPlaneMax)) n = std::max(n, (size_t)q.ksplit * M * N);
   }
   if (M >= HSPEC_BIG_MIN_M && !w_lo && K % GB_KT == 0) {
     n = std::max(n, big_scratch_elems(big_plan(M, N, K, false, device_cus())));
@@ -1415,10 +1543,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     }
     return hipSuccess;
   }
+  // (the packed W is the weight-streaming kernel's own)
+  if (const StreamPlan p = stream_plan_for(g, device_cus()); p.bm) return launch_stream(g, p, s);
   if (g.W2) {
     if (big_ok(g)) return launch_big(g, s);
-    const bool dma = g.M > 64 && !g.W_lo && !g.w_packed && g.K % BK == 0 && g.N1 % 128 == 0 && g.N2 % 128 == 0;
-    if (dma) return launch_dense(g, s);
     // one launch per segment, each writing its own column range of C
     const bf16* ws[3] = {g.W_hi, g.W2, g.W3};
     const int n0s[3] = {0, g.N1, g.N1 + g.N2}, ns[3] = {g.N1, g.N2, g.N - g.N1 - g.N2};
@@ -1452,7 +1580,6 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   }
   if (g.M <= 64 && !g.w_packed) return launch_cfg<1, 4, 2, 2>(g, s);      // 64 x 256: weight streaming
   if (big_ok(g)) return launch_big(g, s);
-  if (!g.W_lo && g.K % BK == 0) return launch_dense(g, s);
   if (g.M <= 128) return launch_cfg<2, 2, 2, 4>(g, s);     // 128 x 256
   return launch_cfg<2, 2, 2, 2>(g, s);                     // 128 x 128: dense
 }
