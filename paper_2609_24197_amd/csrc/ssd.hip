@@ -26,15 +26,6 @@ namespace {
 constexpr int P = 64;
 constexpr int QMAX = 16;
 
-template <int N>
-struct ScanLds {
-  static constexpr int XT = P * (QMAX + 1);          // x^T tile, fp32, padded rows
-  static constexpr int MM = QMAX * (QMAX + 1);        // mixing matrix, fp32
-  static constexpr int BT = N * (QMAX + 1);           // B^T tile, fp32
-  static constexpr int ST = P * (N + 1);              // state, fp32, padded rows
-  static constexpr int BYTES = 4 * (XT + MM + BT + ST);
-};
-
 __device__ __forceinline__ bf16x8 ld8_or0(const bf16* p, bool ok) { return ok ? ld8(p) : zero8(); }
 
 __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& lo) {
@@ -69,237 +60,294 @@ __device__ __forceinline__ void mix_mfma(const float* Mm, const float* xT, int l
   }
 }
 
-template <int N>
-__global__ void __launch_bounds__(64) ssd_scan_kernel(ScanArgs a) {
-  constexpr int NS = (N + 31) / 32;
-  using LD = ScanLds<N>;
-  extern __shared__ __align__(16) float sm[];
-  float* xT = sm;                       // [P][QMAX+1]
-  float* Mm = xT + LD::XT;              // [QMAX][QMAX+1]
-  float* Bt = Mm + LD::MM;              // [N][QMAX+1]
-  float* S = Bt + LD::BT;               // [P][N+1]
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+#define LDS_AS __attribute__((address_space(3)))
 
+// Orders a wave's LDS writes before its own later reads (a wave's LDS accesses execute in order;
+// this keeps the compiler from exchanging them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Elements (row 4 g4 + i, column of this lane) of a 16 x 16 piece of a row-major bf16 tile in LDS,
+// i = 0..3: the transposing read takes four columns at a time, piece q = lane % 4 of each row.
+__device__ __forceinline__ bf16x4 ld_tr(const bf16* p) {
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)p));
+}
+__device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ void split4(const float* v, bf16x4& hi, bf16x4& lo) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    hi[e] = f2bf(v[e]);
+    lo[e] = f2bf(v[e] - bf2f(hi[e]));
+  }
+}
+
+// Several chunks, or a final state: one wave per (request, head), four to a workgroup, each on its
+// own.  Bound by HBM (the fp32 final state is two thirds of the bytes at one to three chunks), so
+// the state stays in registers from S0 to S_final, as the accumulators of its own update:
+//   * S^T in 16 x 16 blocks, columns p.  The rows of a block pair are ordered so that lane group
+//     g4 holds n = 32 j + 8 g4 .. + 7: S0 and S_final move in 16-byte pieces, and the pair is, as
+//     it stands, the k operand of C S^T (split into bf16 hi/lo planes).
+//   * B C^T comes out with a lane's four rows s = 4 g4 + i of column t, which is the A operand of
+//     M x; x and B are staged in LDS as they are and read transposed (ds_read_b64_tr_b16).
+//   * k = 16 tokens fill half of v_mfma_f32_16x16x32_bf16: the other half takes the lo plane of M
+//     and of W X against the same x and B, so a hi/lo product costs one instruction.
+// Measured at B = 64, H = 128, N = 128, bf16 (was: state in LDS, one wave of 47 KB per workgroup,
+// three per CU): T = 40 with S_final 500 -> 136 us (3.9 TB/s).
+// Buffer resource of `bytes` bytes from base (wave-uniform); accesses past the end read zero and
+// write nothing.  BUF_OOB: an offset past every range.
+constexpr int BUF_OOB = 0x7fffff00;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+template <int N, bool LO>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1 : 2))) ssd_scan_state(ScanArgs a) {
+  constexpr int NJ = (N + 31) / 32;
+  constexpr int XP = P + 16, BP = (N < 32 ? 32 : N) + 16;   // LDS row pitches, elements
+  constexpr int NPL = LO ? 2 : 1;
+  __shared__ __align__(16) bf16 xs_all[4][NPL][QMAX * XP];
+  __shared__ __align__(16) bf16 bs_all[4][NPL][QMAX * BP];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, g4 = lane >> 4, l16 = lane & 15;
   const int H = a.H, T = a.T, G = a.G;
-  const int b = blockIdx.x / H, h = blockIdx.x % H;
-  const int grp = h / (H / G);
-  const int lane = threadIdx.x, g4 = lane >> 4, l16 = lane & 15;
-  const float Ah = a.A_is_log ? -__expf(a.A[h]) : a.A[h], Dh = a.Dskip[h];
-  const size_t s0_off = ((size_t)b * H + h) * P * N;
+  const long long unit = (long long)blockIdx.x * 4 + wave;
+  if (unit >= (long long)a.B * H) return;
+  const int b = (int)(unit / H), h = (int)(unit % H), grp = h / (H / G);
+  bf16* xs = xs_all[wave][0];
+  bf16* bs = bs_all[wave][0];
+  constexpr int XLO = QMAX * XP, BLO = QMAX * BP;   // the lo planes' offsets
+  const size_t s0_off = (size_t)unit * P * N;
 
-  // S0 into LDS in 16-byte pieces (8 elements of a row), every load of a round issued before
-  // its first LDS write (two rounds at N = 128 to bound the registers)
-  {
-    constexpr int PR = N / 8, PER = P * PR / 64, RND = PER > 8 ? PER / 2 : PER;
+  // ---- S0: lane holds n = 32 j + 8 g4 .. + 7 of rows p = 16 pb + l16; every load of a plane is
+  // issued before the first is used
+  f32x4 st[2 * NJ][4];
+  auto s0_plane = [&](const void* base, bool f16, bool add) __attribute__((always_inline)) {
+    u32x4 raw[NJ][4];
 #pragma unroll
-    for (int r0 = 0; r0 < PER; r0 += RND) {
-      bf16x8 hv[RND], lv[RND];
-      f16x8 fv[RND];
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int j = 0; j < RND; ++j) {
-        const int q = (r0 + j) * 64 + lane, p = q / PR, n0 = (q % PR) * 8;
-        const size_t off = s0_off + (size_t)p * N + n0;
-        if (a.S0_h16) {
-          fv[j] = *reinterpret_cast<const f16x8*>(a.S0_h16 + off);
-        } else {
-          hv[j] = ld8_or0(a.S0_hi + off, a.S0_hi != nullptr);
-          lv[j] = ld8_or0(a.S0_lo + off, a.S0_lo != nullptr);
+      for (int pb = 0; pb < 4; ++pb) {
+        const int n = 32 * j + 8 * g4;
+        raw[j][pb] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(base) + s0_off +
+                                                     (size_t)(16 * pb + l16) * N + (n < N ? n : 0));
+      }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) {
+        const bool in = 32 * j + 8 * g4 < N;
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, raw[j][pb]);
+        const f16x8 hv = __builtin_bit_cast(f16x8, raw[j][pb]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = in ? (f16 ? (float)hv[e] : bf2f(bv[e])) : 0.f;
+          f32x4& d = st[2 * j + e / 4][pb];
+          d[e % 4] = add ? d[e % 4] + v : v;
         }
       }
+  };
+  if (a.S0_h16) {
+    s0_plane(a.S0_h16, true, false);
+  } else if (a.S0_hi) {
+    s0_plane(a.S0_hi, false, false);
+    if (LO && a.S0_lo) s0_plane(a.S0_lo, false, true);
+  } else {
 #pragma unroll
-      for (int j = 0; j < RND; ++j) {
-        const int q = (r0 + j) * 64 + lane, p = q / PR, n0 = (q % PR) * 8;
+    for (int nb = 0; nb < 2 * NJ; ++nb)
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          S[p * (N + 1) + n0 + e] = a.S0_h16 ? (float)fv[j][e] : bf2f(hv[j][e]) + bf2f(lv[j][e]);
-      }
-    }
+      for (int pb = 0; pb < 4; ++pb) st[nb][pb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  __syncthreads();
+  const float Ah = a.A_is_log ? -__expf(a.A[h]) : a.A[h], Dh = a.Dskip[h];
 
-  // A chunk's global inputs (dt, the x tile, the C and B fragments) come into registers one
-  // chunk ahead: the next chunk's loads are in flight while this one is computed.
+  // ---- a chunk's inputs, loaded while the chunk before updates the state: buffer loads from the
+  // chunk's first token, whose ranges end with the chunk (later tokens and absent planes read zero)
+  constexpr int NB = N >= 32 ? N / 32 : 1;   // 16-byte pieces of a B row per lane (4 lanes a row; N = 16: 2)
   struct ChunkIn {
     float dtv;
-    bf16x8 xh0, xh1, xl0, xl1;
-    bf16x8 cf[NS], cfl[NS], bfr[NS], bfl[NS];
+    u32x4 x[NPL][2], bt[NPL][NB], c[NPL][NJ];
   };
-  auto load_chunk = [&](int c0, ChunkIn& r) {
-    const int Qc = max(0, min(a.chunk, T - c0));   // 0 past the last chunk: nothing is read
-    r.dtv = l16 < Qc ? a.dt[(size_t)(b * T + c0 + l16) * a.dt_ld + h] : 0.f;
-    // x tile: lane holds x[t = lane / 4][p = 16 (lane % 4) .. + 15], zero past the chunk
-    const int xt = lane >> 2, xp = 16 * (lane & 3);
-    const bool xok = xt < Qc;
-    const size_t xoff = (size_t)(b * T + c0 + xt) * a.x_ld + (size_t)h * P + xp;
-    r.xh0 = ld8_or0(a.x_hi + xoff, xok);
-    r.xh1 = ld8_or0(a.x_hi + xoff + 8, xok);
-    r.xl0 = a.x_lo ? ld8_or0(a.x_lo + xoff, xok) : zero8();
-    r.xl1 = a.x_lo ? ld8_or0(a.x_lo + xoff + 8, xok) : zero8();
-    // C (A operand, rows t) and B (B operand, columns s) fragments over n
-    const size_t tok_t = (size_t)(b * T + c0 + l16) * a.bc_ld + (size_t)grp * N;
+  const int rt = lane >> 2, rq = lane & 3;   // this lane's row and quarter of the x and B tiles
+  const bool bq = N >= 32 || rq < 2;
+  const int x_vo = (rt * a.x_ld + 16 * rq) * 2, b_vo = bq ? (rt * a.bc_ld + 8 * NB * rq) * 2 : BUF_OOB;
+  const int c_vo = 8 * g4 < N ? (l16 * a.bc_ld + 8 * g4) * 2 : BUF_OOB, dt_vo = l16 * a.dt_ld * 4;
+  auto load_chunk = [&](int c0, ChunkIn& r) __attribute__((always_inline)) {
+    const int Qc = min(a.chunk, T - c0);
+    const size_t tok0 = (size_t)b * T + c0;
+    r.dtv = __uint_as_float(
+        __builtin_amdgcn_raw_buffer_load_b32(rsrc(a.dt + tok0 * a.dt_ld + h, (Qc * a.dt_ld - h) * 4), dt_vo, 0, 0));
+    const size_t xo = tok0 * a.x_ld + (size_t)h * P, bo = tok0 * a.bc_ld + (size_t)grp * N;
+    const int xr = (Qc * a.x_ld - h * P) * 2, br = (Qc * a.bc_ld - grp * N) * 2;
 #pragma unroll
-    for (int ns = 0; ns < NS; ++ns) {
-      const int n = 32 * ns + 8 * g4;
-      const bool ok = l16 < Qc && n < N;
-      r.cf[ns] = ld8_or0(a.C_hi + tok_t + n, ok);
-      r.cfl[ns] = a.C_lo ? ld8_or0(a.C_lo + tok_t + n, ok) : zero8();
-      r.bfr[ns] = ld8_or0(a.B_hi + tok_t + n, ok);
-      r.bfl[ns] = a.B_lo ? ld8_or0(a.B_lo + tok_t + n, ok) : zero8();
+    for (int pl = 0; pl < NPL; ++pl) {
+      const bf16 *xp = pl ? a.x_lo : a.x_hi, *bp = pl ? a.B_lo : a.B_hi, *cp = pl ? a.C_lo : a.C_hi;
+      const __amdgpu_buffer_rsrc_t xs_r = rsrc(xp + xo, xp ? xr : 0), bs_r = rsrc(bp + bo, bp ? br : 0),
+                                   cs_r = rsrc(cp + bo, cp ? br : 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) r.x[pl][i] = __builtin_amdgcn_raw_buffer_load_b128(xs_r, x_vo + 16 * i, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) r.bt[pl][i] = __builtin_amdgcn_raw_buffer_load_b128(bs_r, b_vo + 16 * i, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) r.c[pl][j] = __builtin_amdgcn_raw_buffer_load_b128(cs_r, c_vo + 64 * j, 0, 0);
     }
   };
+  const int y_vo = (4 * g4 * H * P + l16) * 4;
+  if (N < 32) {   // columns 16..31 of the B tile are zero throughout
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl)
+      if (rq < 2) *reinterpret_cast<bf16x8*>(bs + pl * BLO + rt * BP + 16 + 8 * rq) = zero8();
+  }
   ChunkIn nx;
   load_chunk(0, nx);
 
   for (int c0 = 0; c0 < T; c0 += a.chunk) {
     const int Qc = min(a.chunk, T - c0);
     const ChunkIn cur = nx;
-    load_chunk(c0 + a.chunk, nx);
+    wave_lds_fence();   // the previous chunk's tiles have been read
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4*>(xs + (pl * XLO + rt * XP + 16 * rq + 8 * i)) = cur.x[pl][i];
+      if (bq) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) *reinterpret_cast<u32x4*>(bs + (pl * BLO + rt * BP + 8 * (rq * NB + i))) = cur.bt[pl][i];
+      }
+    }
+    bf16x8 cf[NPL][NJ];
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) cf[pl][j] = __builtin_bit_cast(bf16x8, cur.c[pl][j]);
+    wave_lds_fence();
+
+    // ---- l_t, the inclusive cumulative sum of dt A (lane l16 of every group holds token l16)
     const float dtv = cur.dtv;
-    // the inclusive cumulative sum of dt*A over the chunk (lanes 0..15)
     float cum = dtv * Ah;
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       const float v = __shfl_up(cum, off, 16);
       if (l16 >= off) cum += v;
     }
-    // x^T tile in LDS
-    {
-      const int xt = lane >> 2, xp = 16 * (lane & 3);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        xT[(xp + e) * (QMAX + 1) + xt] = bf2f(cur.xh0[e]) + bf2f(cur.xl0[e]);
-        xT[(xp + 8 + e) * (QMAX + 1) + xt] = bf2f(cur.xh1[e]) + bf2f(cur.xl1[e]);
-      }
-    }
-    const bf16x8 *cf = cur.cf, *cfl = cur.cfl, *bfr = cur.bfr, *bfl = cur.bfl;
-    // state term C S^T: lane gets rows t = 4 g4 + i, column p = 16 pb + l16
-    f32x4 ys[4];
-#pragma unroll
-    for (int pb = 0; pb < 4; ++pb) {
-      ys[pb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int p = 16 * pb + l16;
-#pragma unroll
-      for (int ns = 0; ns < NS; ++ns) {
-        const int n = 32 * ns + 8 * g4;
-        bf16x8 sh, sl;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = n + e < N ? S[p * (N + 1) + n + e] : 0.f;
-        split8(v, sh, sl);
-        ys[pb] = mma16(cf[ns], sh, ys[pb]);
-        if (a.C_lo) ys[pb] = mma16(cfl[ns], sh, ys[pb]);
-        ys[pb] = mma16(cf[ns], sl, ys[pb]);
-      }
-    }
-    // C B^T: lane gets rows t = 4 g4 + i, column s = l16
-    f32x4 cb = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ns = 0; ns < NS; ++ns) {
-      cb = mma16(cf[ns], bfr[ns], cb);
-      if (a.C_lo) cb = mma16(cfl[ns], bfr[ns], cb);
-      if (a.B_lo) cb = mma16(cf[ns], bfl[ns], cb);
-    }
-    const float ell_s = __shfl(cum, l16);            // l_s for this lane's column s
-    const float dt_s = __shfl(dtv, l16);
-    float ell_t[4];
+    const float ell_end = __shfl(cum, 15);   // (dt is zero past the chunk)
+    float ell[4], dts[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int t = 4 * g4 + i;
-      ell_t[i] = __shfl(cum, t);
-      const bool ok = l16 <= t && t < Qc;
-      Mm[t * (QMAX + 1) + l16] = ok ? cb[i] * __expf(ell_t[i] - ell_s) * dt_s : 0.f;
+      ell[i] = __shfl(cum, 4 * g4 + i);
+      dts[i] = __shfl(dtv, 4 * g4 + i);
     }
-    // B^T tile for the state update, Bt[n][s], from the B fragments already in registers
-    // (token s = lane % 16, zero past the chunk)
+
+    // ---- B C^T: rows s = 4 g4 + i, column t = l16; then M[t][s] as the A operand of M x
+    f32x4 cb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ns = 0; ns < NS; ++ns)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int n = 32 * ns + 8 * g4 + e;
-        if (n < N) Bt[n * (QMAX + 1) + l16] = bf2f(bfr[ns][e]) + bf2f(bfl[ns][e]);
+    for (int j = 0; j < NJ; ++j) {
+      const bf16x8 bf = *reinterpret_cast<const bf16x8*>(bs + l16 * BP + 32 * j + 8 * g4);
+      cb = mma16(bf, cf[0][j], cb);
+      if constexpr (LO) {
+        cb = mma16(bf, cf[NPL - 1][j], cb);
+        cb = mma16(*reinterpret_cast<const bf16x8*>(bs + BLO + l16 * BP + 32 * j + 8 * g4), cf[0][j], cb);
       }
-    __syncthreads();
-    // y = exp(l_t) (C S^T) + M x + D x, M x on MFMA
-    f32x4 mx[4];
-    mix_mfma(Mm, xT, lane, mx);
+    }
+    float mv[4], wv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool ok = 4 * g4 + i <= l16 && l16 < Qc;
+      mv[i] = ok ? cb[i] * __expf(cum - ell[i]) * dts[i] : 0.f;
+      wv[i] = __expf(ell_end - ell[i]) * dts[i];
+    }
+    const bf16x4 z4 = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
+    bf16x4 mh, ml;
+    split4(mv, mh, ml);
+
+    // ---- per 16 columns p: C S^T from the state before this chunk, then with x of tokens
+    // 4 g4 + i the output y = exp(l_t) C S^T + M x + D x (rows t = 4 g4 + i) and W X
+    float dec[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dec[i] = __expf(ell[i]);
+    // (the buffer's range ends with the chunk: rows past it are dropped)
+    const __amdgpu_buffer_rsrc_t yr = rsrc(a.y + ((size_t)b * T + c0) * H * P + (size_t)h * P, (Qc * H - h) * P * 4);
+    bf16x8 wx[4];
 #pragma unroll
     for (int pb = 0; pb < 4; ++pb) {
-      const int p = 16 * pb + l16;
+      f32x4 ys = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = st[2 * j][pb][e];
+          v[4 + e] = st[2 * j + 1][pb][e];
+        }
+        bf16x8 sh, sl;
+        split8(v, sh, sl);
+        ys = mma16(cf[0][j], sh, ys);
+        if constexpr (LO) ys = mma16(cf[NPL - 1][j], sh, ys);
+        ys = mma16(cf[0][j], sl, ys);
+      }
+      const int o = (4 * g4 + (l16 >> 2)) * XP + 16 * pb + 4 * (l16 & 3);
+      const bf16x4 xh = ld_tr(xs + o);
+      f32x4 y = mma16(cat4(mh, ml), cat4(xh, xh), f32x4{0.f, 0.f, 0.f, 0.f});
+      float xv[4], w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xv[i] = bf2f(xh[i]);
+      if constexpr (LO) {
+        const bf16x4 xl = ld_tr(xs + XLO + o);
+        y = mma16(cat4(mh, z4), cat4(xl, z4), y);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xv[i] += bf2f(xl[i]);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int t = 4 * g4 + i;
-        if (t >= Qc) continue;
-        const float acc = __expf(ell_t[i]) * ys[pb][i] + Dh * xT[p * (QMAX + 1) + t] + mx[pb][i];
-        a.y[(size_t)(b * T + c0 + t) * H * P + (size_t)h * P + p] = acc;
+        const float out = dec[i] * ys[i] + Dh * xv[i] + y[i];
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out), yr, y_vo + 64 * pb, i * H * P * 4, 0);
+        w[i] = wv[i] * xv[i];
+      }
+      bf16x4 wh, wl;
+      split4(w, wh, wl);
+      wx[pb] = cat4(wh, wl);
+      __builtin_amdgcn_sched_barrier(0);   // (one column block's planes of S at a time: registers)
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (c0 + a.chunk < T) load_chunk(c0 + a.chunk, nx);   // (here: C's registers are free)
+    // ---- S^T <- exp(l_end) S^T + B^T (W X)
+    const float de = __expf(ell_end);
+#pragma unroll
+    for (int nb = 0; nb < 2 * NJ; ++nb) {
+      // rows of block nb: position 4 q + i is n = 32 (nb / 2) + 8 q + 4 (nb % 2) + i
+      const int o = (4 * g4 + (l16 >> 2)) * BP + 32 * (nb / 2) + 4 * (nb & 1) + 8 * (l16 & 3);
+      const bf16x4 bh = ld_tr(bs + o);
+      const bf16x8 bb = cat4(bh, bh);
+      bf16x8 bl = zero8();
+      if constexpr (LO) bl = cat4(ld_tr(bs + BLO + o), z4);
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) {
+        st[nb][pb] = mma16(bb, wx[pb], st[nb][pb] * de);
+        if constexpr (LO) st[nb][pb] = mma16(bl, wx[pb], st[nb][pb]);
       }
     }
-    {
-      // S <- exp(l_end) S + (W X) B on v_mfma_f32_32x32x16_bf16: A = W X (row p, k = s) with
-      // W X [p][s] = exp(l_end - l_s) dt_s x_s[p], B = the B tile (k = s, column n), the
-      // accumulator the decayed state in the 32 x 32 block layout (lane holds rows
-      // 8 (i / 4) + 4 (lane / 32) + i % 4 of column lane % 32), read from and written back to
-      // LDS by the same lane.  fp32 operands as bf16 hi/lo planes (three products).
-      const float ell_end = __shfl(cum, Qc - 1);
-      const float dec = __expf(ell_end);
-      const int r32 = lane & 31, h2 = lane >> 5;
-      float wv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int sx = 8 * h2 + e;
-        const float w = __shfl(dtv, sx) * __expf(ell_end - __shfl(cum, sx));
-        wv[e] = sx < Qc ? w : 0.f;
-      }
-      bf16x8 wh[2], wl[2];
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = wv[e] * xT[(32 * pb + r32) * (QMAX + 1) + 8 * h2 + e];
-        split8(v, wh[pb], wl[pb]);
-      }
-#pragma unroll
-      for (int nb = 0; nb < (N + 31) / 32; ++nb) {
-        const int n = 32 * nb + r32;
-        const bool nok = n < N;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = nok ? Bt[n * (QMAX + 1) + 8 * h2 + e] : 0.f;
-        bf16x8 bh, bl;
-        split8(v, bh, bl);
-#pragma unroll
-        for (int pb = 0; pb < 2; ++pb) {
-          f32x16 acc;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int p = 32 * pb + 8 * (i / 4) + 4 * h2 + (i % 4);
-            acc[i] = nok ? dec * S[p * (N + 1) + n] : 0.f;
-          }
-          acc = mma32(wh[pb], bh, acc);
-          acc = mma32(wl[pb], bh, acc);
-          acc = mma32(wh[pb], bl, acc);
-          if (nok) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) S[(32 * pb + 8 * (i / 4) + 4 * h2 + (i % 4)) * (N + 1) + n] = acc[i];
-          }
-        }
-      }
-    }
-    __syncthreads();
   }
 
   if (a.S_final) {
     // 16-byte stores where the caller's buffer allows them
     const bool vec = (reinterpret_cast<uintptr_t>(a.S_final) & 15) == 0;
-    for (int q = lane; q < P * N / 4; q += 64) {
-      const int p = q / (N / 4), n0 = (q % (N / 4)) * 4;
-      const float* sr = S + p * (N + 1) + n0;
-      float* dst = a.S_final + s0_off + (size_t)p * N + n0;
-      if (vec) {
-        *reinterpret_cast<f32x4*>(dst) = f32x4{sr[0], sr[1], sr[2], sr[3]};
-      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dst[e] = sr[e];
+    for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+      for (int nb = 0; nb < 2 * NJ; ++nb) {
+        const int n = 32 * (nb / 2) + 8 * g4 + 4 * (nb & 1);
+        if (n >= N) continue;
+        float* dst = a.S_final + s0_off + (size_t)(16 * pb + l16) * N + n;
+        if (vec) {
+          *reinterpret_cast<f32x4*>(dst) = st[nb][pb];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[e] = st[nb][pb][e];
+        }
       }
-    }
   }
 }
 
@@ -579,10 +627,10 @@ __global__ void __launch_bounds__(64 * SCAN_HW) __attribute__((amdgpu_waves_per_
 template <int N>
 hipError_t launch_n(const ScanArgs& a, hipStream_t s) {
   const bool multi = a.S_final != nullptr || a.T > a.chunk;
-  constexpr int lds_multi = ScanLds<N>::BYTES;
   if (multi) {
-    auto kern = ssd_scan_kernel<N>;
-    hipLaunchKernelGGL(kern, dim3(a.B * a.H), dim3(64), lds_multi, s, a);
+    const unsigned grid = (unsigned)(((long long)a.B * a.H + 3) / 4);
+    if (a.x_lo || a.B_lo || a.C_lo || a.S0_lo) hipLaunchKernelGGL((ssd_scan_state<N, true>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((ssd_scan_state<N, false>), dim3(grid), dim3(256), 0, s, a);
   } else {
     // heads in groups of SCAN_HW that share B and C: one workgroup per group of heads
     const bool grouped = a.S0_h16 && a.H % SCAN_HW == 0 && (a.H / a.G) % SCAN_HW == 0;
