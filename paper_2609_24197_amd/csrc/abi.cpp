@@ -333,8 +333,11 @@ void plan_mamba(Arena& ar, const hspec_mamba_cfg& c, bool u_norm, MambaPlan& p) 
 }
 
 // in_proj -> conv/split -> scan from S0 planes -> gated norm -> out_proj (+ residual R).
+// With `sum`, out_proj's product may be left as partial sums for the next kernel, which then adds R
+// (the residual) and writes out: see GemmArgs::defer.  `clear`: status words to clear, or null.
 hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Planes u, const MambaPlan& p,
-                            const void* R, int r_bf16, float* out, float* S_final, hipStream_t st) {
+                            const void* R, int r_bf16, float* out, float* S_final, int* clear, hspec::Parts* sum,
+                            hipStream_t st) {
   const int M = c.B * c.k;
   const int di = c.H * c.P, gn = c.G * c.N;
   const int dproj = 2 * di + 2 * gn + c.H;
@@ -346,11 +349,14 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
   gi.W_hi = win.hi; gi.W_lo = win.lo; gi.ldw = c.d_model;
   gi.M = M; gi.N = dproj; gi.K = c.d_model;
   gi.C = p.zx; gi.ldc = dproj;
+  hspec::Parts zx(p.zx);
+  gi.defer = &zx;
   use_scratch(gi, p.gs);
   HIP_TRY(hspec::launch_gemm(gi, st));
 
   hspec::ConvArgs ca;
-  ca.zxbcdt = p.zx; ca.conv_w = w.conv_w; ca.conv_b = w.conv_b; ca.w_bf16 = !is_f32(c.dtype);
+  ca.clear = clear;
+  ca.zxbcdt = zx; ca.conv_w = w.conv_w; ca.conv_b = w.conv_b; ca.w_bf16 = !is_f32(c.dtype);
   ca.dt_bias = w.dt_bias;
   ca.B = c.B; ca.T = c.k; ca.H = c.H; ca.P = c.P; ca.G = c.G; ca.N = c.N; ca.K = c.conv_w;
   ca.x_hi = p.x_hi; ca.x_lo = p.x_lo; ca.B_hi = p.B_hi; ca.B_lo = p.B_lo; ca.C_hi = p.C_hi; ca.C_lo = p.C_lo;
@@ -365,7 +371,7 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
   sa.x_ld = di; sa.bc_ld = gn; sa.dt_ld = c.H;
   HIP_TRY(hspec::launch_ssd_scan(sa, st));
 
-  HIP_TRY(hspec::launch_gated_rmsnorm(p.y, p.zx, dproj, w.gnorm_w, M, di, c.G, c.eps, p.yn_hi, p.yn_lo, st));
+  HIP_TRY(hspec::launch_gated_rmsnorm(p.y, zx, dproj, w.gnorm_w, M, di, c.G, c.eps, p.yn_hi, p.yn_lo, st));
 
   hspec::GemmArgs go;
   go.A_hi = p.yn_hi; go.A_lo = p.yn_lo; go.lda = di;
@@ -373,7 +379,8 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
   go.M = M; go.N = c.d_model; go.K = di;
   go.C = out; go.ldc = c.d_model;
   go.R = R; go.ldr = c.d_model; go.r_bf16 = r_bf16;
-  use_scratch(go, p.gs);
+  go.defer = sum;
+  use_scratch(go, p.gs);   // (in_proj's partial sums were last read by the gated norm)
   HIP_TRY(hspec::launch_gemm(go, st));
   return HSPEC_OK;
 }
@@ -475,7 +482,7 @@ hspec::AttnArgs sweep_args(const hspec_attn_cfg& c, const AttnPlan& p, const int
 hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Planes xn, const void* k_cache,
                            const void* v_cache, const int32_t* pt, const int32_t* lens, int max_ctx_len,
                            const AttnPlan& p, const void* R, int r_bf16, float* out, int* status, int plan_clear,
-                           hipStream_t st) {
+                           hspec::Parts* sum, hipStream_t st) {
   const int M = c.B * c.k;
   const hspec::AttnArgs plan = sweep_args(c, p, pt, lens, max_ctx_len, status);
   const bool plan_fused = c.B <= hspec::kWorklistFusedMax;
@@ -490,6 +497,7 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
   HIP_TRY(as_planes(v_cache, c.dtype, p.vc, vc, st));
   const Planes* ws[3] = {&wq, &wk, &wv};
   const int nrows[3] = {c.Hq * c.D, c.Hkv * c.D, c.Hkv * c.D};
+  hspec::Parts qkv(p.qkv);
   if (!wq.lo) {
     // one product over the three row segments [W_q; W_k; W_v]
     hspec::GemmArgs g;
@@ -497,6 +505,7 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
     g.W_hi = wq.hi; g.W2 = wk.hi; g.W3 = wv.hi; g.N1 = nrows[0]; g.N2 = nrows[1]; g.ldw = c.d_model;
     g.M = M; g.N = ldq; g.K = c.d_model;
     g.C = p.qkv; g.ldc = ldq;
+    g.defer = &qkv;
     use_scratch(g, p.gs);
     HIP_TRY(hspec::launch_gemm(g, st));
   } else {
@@ -512,7 +521,7 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
       col += nrows[i];
     }
   }
-  HIP_TRY(hspec::launch_qk_norm_rope(p.qkv, w.q_norm_w, w.k_norm_w, lens, c.B, c.k, c.Hq, c.Hkv, c.D, c.eps,
+  HIP_TRY(hspec::launch_qk_norm_rope(qkv, w.q_norm_w, w.k_norm_w, lens, c.B, c.k, c.Hq, c.Hkv, c.D, c.eps,
                                      c.rope_theta, p.q_hi, p.q_lo, p.k_hi, p.k_lo, p.v_hi, p.v_lo, st,
                                      plan_fused ? &plan : nullptr, plan_clear));
   hspec::AttnArgs a = plan;
@@ -527,9 +536,18 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
   g.M = M; g.N = c.d_model; g.K = c.Hq * c.D;
   g.C = out; g.ldc = c.d_model;
   g.R = R; g.ldr = c.d_model; g.r_bf16 = r_bf16;
+  g.defer = sum;
   use_scratch(g, p.gs);
   HIP_TRY(hspec::launch_gemm(g, st));
   return HSPEC_OK;
+}
+
+// RMSNorm of a sublayer's output: out itself, or the sum of the partial products it was left as
+// (GemmArgs::defer) and the residual R, which also writes out.
+hipError_t norm_output(const hspec::Parts& sum, const void* R, int r_bf16, float* out, const float* w, int rows, int n,
+                       float eps, bf16* hi, bf16* lo, hipStream_t st) {
+  if (sum.p == out) return hspec::launch_rmsnorm_planes(out, 0, w, rows, n, eps, hi, lo, st);
+  return hspec::launch_sum_rmsnorm_planes(sum, R, r_bf16, out, w, rows, n, eps, hi, lo, st);
 }
 
 struct DraftPlan {
@@ -595,11 +613,10 @@ HSPEC_API hspec_status hspec_mamba_block_scan(const hspec_mamba_cfg* cfg, const 
   int* status = status_word(ar);
   MambaPlan p;
   plan_mamba(ar, *cfg, false, p);
-  HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
   if (hspec_status s = run_state(*cfg, *w, h_last, p.st, nullptr, st)) return s;
   Planes u;
   HIP_TRY(as_planes(block_hidden, cfg->dtype, p.u_in, u, st));
-  return run_mamba_core(*cfg, *w, u, p, nullptr, 0, out, S_final, st);
+  return run_mamba_core(*cfg, *w, u, p, nullptr, 0, out, S_final, status, nullptr, st);   // (no kernel sets a bit)
 }
 
 HSPEC_API size_t hspec_target_kv_block_attn_workspace(const hspec_attn_cfg* cfg, int max_ctx_len) {
@@ -632,7 +649,7 @@ HSPEC_API hspec_status hspec_target_kv_block_attn(const hspec_attn_cfg* cfg, con
   Planes xn;
   HIP_TRY(as_planes(x, cfg->dtype, p.x_in, xn, st));
   return run_attn_core(*cfg, *w, xn, k_cache, v_cache, page_table, ctx_lens, max_ctx_len, p, nullptr, 0, out, status,
-                       hspec::kStatusClear, st);
+                       hspec::kStatusClear, nullptr, st);
 }
 
 HSPEC_API size_t hspec_draft_step_workspace(const hspec_mamba_cfg* mcfg, const hspec_attn_cfg* acfg,
@@ -671,11 +688,12 @@ HSPEC_API hspec_status hspec_draft_step(const hspec_mamba_cfg* mcfg, const hspec
   if (hspec_status s = run_state(*mcfg, *mw, h_last, p.m.st, nullptr, st)) return s;
   HIP_TRY(hspec::launch_rmsnorm_planes(block_emb, !f32, norm1_w, M, mcfg->d_model, mcfg->eps, p.m.u_hi, p.m.u_lo, st));
   Planes u{p.m.u_hi, p.m.u_lo};
-  if (hspec_status s = run_mamba_core(*mcfg, *mw, u, p.m, block_emb, !f32, p.x1, nullptr, st)) return s;
-  HIP_TRY(hspec::launch_rmsnorm_planes(p.x1, 0, norm2_w, M, acfg->d_model, acfg->eps, p.at.xn_hi, p.at.xn_lo, st));
+  hspec::Parts x1(p.x1);
+  if (hspec_status s = run_mamba_core(*mcfg, *mw, u, p.m, block_emb, !f32, p.x1, nullptr, nullptr, &x1, st)) return s;
+  HIP_TRY(norm_output(x1, block_emb, !f32, p.x1, norm2_w, M, acfg->d_model, acfg->eps, p.at.xn_hi, p.at.xn_lo, st));
   Planes xn{p.at.xn_hi, p.at.xn_lo};
   return run_attn_core(*acfg, *aw, xn, k_cache, v_cache, page_table, ctx_lens, max_ctx_len, p.at, p.x1, 0, out, status,
-                       hspec::kStatusClear, st);
+                       hspec::kStatusClear, nullptr, st);
 }
 
 HSPEC_API size_t hspec_ssd_scan_workspace(int B, int T, int H, int P, int N, int G, hspec_dtype dtype) {
@@ -714,7 +732,6 @@ HSPEC_API hspec_status hspec_ssd_scan(int B, int T, int H, int P, int N, int G, 
     sc = reserve_split(ar, dtype, (size_t)B * T * G * N);
     ss = reserve_split(ar, dtype, (size_t)B * H * P * N);
   }
-  HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
   Planes px, pb, pc, ps;
   HIP_TRY(as_planes(x, dtype, sx, px, st));
   HIP_TRY(as_planes(Bm, dtype, sb, pb, st));
@@ -727,6 +744,7 @@ HSPEC_API hspec_status hspec_ssd_scan(int B, int T, int H, int P, int N, int G, 
   a.y = y; a.S_final = S_final;
   a.B = B; a.T = T; a.H = H; a.P = P; a.N = N; a.G = G; a.chunk = chunk;
   a.x_ld = H * P; a.bc_ld = G * N; a.dt_ld = H;
+  a.clear = status;
   HIP_TRY(hspec::launch_ssd_scan(a, st));
   return HSPEC_OK;
 }
@@ -885,8 +903,9 @@ void plan_forward(Arena& ar, const hspec_mamba_cfg& mc, const hspec_attn_cfg& ac
 
 // x_out = x + W_down (SiLU(W_gate u) * (W_up u)), u already normalised (planes).
 hspec_status run_mlp(const hspec_mamba_cfg& c, const hspec_layer_w& L, int ff, Planes u, const ForwardPlan& p,
-                     const void* x, int x_bf16, float* x_out, hipStream_t st) {
+                     const void* x, int x_bf16, float* x_out, hspec::Parts* sum, hipStream_t st) {
   const int M = c.B * c.k;
+  hspec::Parts gu(p.gu);
   Planes wg, wu, wd;
   HIP_TRY(as_planes(L.W_gate, c.dtype, p.wg, wg, st));
   HIP_TRY(as_planes(L.W_up, c.dtype, p.wu, wu, st));
@@ -898,6 +917,7 @@ hspec_status run_mlp(const hspec_mamba_cfg& c, const hspec_layer_w& L, int ff, P
     g.W_hi = wg.hi; g.W2 = wu.hi; g.N1 = ff; g.N2 = ff; g.ldw = c.d_model;
     g.M = M; g.N = 2 * ff; g.K = c.d_model;
     g.C = p.gu; g.ldc = 2 * ff;
+    g.defer = &gu;
     use_scratch(g, p.gs);
     HIP_TRY(hspec::launch_gemm(g, st));
   } else {
@@ -912,13 +932,14 @@ hspec_status run_mlp(const hspec_mamba_cfg& c, const hspec_layer_w& L, int ff, P
       HIP_TRY(hspec::launch_gemm(g, st));
     }
   }
-  HIP_TRY(hspec::launch_silu_mul(p.gu, M, ff, p.h_hi, p.h_lo, st));
+  HIP_TRY(hspec::launch_silu_mul(gu, M, ff, p.h_hi, p.h_lo, st));
   hspec::GemmArgs g;
   g.A_hi = p.h_hi; g.A_lo = p.h_lo; g.lda = ff;
   g.W_hi = wd.hi; g.W_lo = wd.lo; g.ldw = ff;
   g.M = M; g.N = c.d_model; g.K = ff;
   g.C = x_out; g.ldc = c.d_model;
   g.R = x; g.ldr = c.d_model; g.r_bf16 = x_bf16;
+  g.defer = sum;
   use_scratch(g, p.gs);
   HIP_TRY(hspec::launch_gemm(g, st));
   return HSPEC_OK;
@@ -990,7 +1011,10 @@ HSPEC_API hspec_status hspec_drafter_forward(const hspec_mamba_cfg* mcfg, const 
   plan_forward(ar, mc, ac, ff, max_ctx_len, p);
   const int M = mc.B * mc.k;
   const bool f32 = is_f32(mc.dtype);
-  HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
+  // the status words: cleared by the first attention's work list (no kernel before it sets a bit),
+  // or here when there is no attention
+  int plan_clear = hspec::kStatusClear;
+  if (!any_attn) HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
   if (any_mamba) {
     hspec_mamba_w sw{};
     sw.W_r = W_r;
@@ -999,39 +1023,55 @@ HSPEC_API hspec_status hspec_drafter_forward(const hspec_mamba_cfg* mcfg, const 
   }
 
   // the residual stream: block_emb (storage dtype), then fp32 buffers; the last sublayer
-  // writes straight into out
+  // writes straight into out.  Between sublayers it may be (x_sum, x_res): a product's partial
+  // sums and the residual to add, which the next norm adds up into x.
   int total = 0;
   for (int l = 0; l < n_layers; ++l) total += 1 + (layers[l].mamba ? 1 : 0) + (layers[l].attn ? 1 : 0);
   int done = 0;
   const void* x = block_emb;
   int x_bf16 = !f32;
-  auto dst = [&]() -> float* { return ++done == total ? out : (x == p.xa ? p.xb : p.xa); };
+  hspec::Parts x_sum;
+  const void* x_res = nullptr;
+  int res_bf16 = 0;
+  float* x_f32 = nullptr;   // x as the fp32 buffer it is (or will be) in, null for block_emb
+  // norm of the residual stream, then x becomes the residual of the sublayer that writes y
+  auto norm = [&](const float* w, int n, float eps, bf16* hi, bf16* lo) -> hipError_t {
+    if (!x_f32) return hspec::launch_rmsnorm_planes(x, x_bf16, w, M, n, eps, hi, lo, st);
+    return norm_output(x_sum, x_res, res_bf16, x_f32, w, M, n, eps, hi, lo, st);
+  };
+  auto next = [&]() -> float* { return ++done == total ? out : (x_f32 == p.xa ? p.xb : p.xa); };
+  auto advance = [&](float* y) {
+    x_res = x;
+    res_bf16 = x_bf16;
+    x = x_f32 = y;
+    x_bf16 = 0;
+  };
   Planes u{p.m.u_hi, p.m.u_lo};
   for (int l = 0; l < n_layers; ++l) {
     const hspec_layer_w& L = layers[l];
-    float* y = nullptr;
     if (L.mamba) {
-      HIP_TRY(hspec::launch_rmsnorm_planes(x, x_bf16, L.norm1_w, M, mc.d_model, mc.eps, p.m.u_hi, p.m.u_lo, st));
-      y = dst();
-      if (hspec_status s = run_mamba_core(mc, *L.mamba, u, p.m, x, x_bf16, y, nullptr, st)) return s;
-      x = y;
-      x_bf16 = 0;
+      HIP_TRY(norm(L.norm1_w, mc.d_model, mc.eps, p.m.u_hi, p.m.u_lo));
+      float* y = next();
+      x_sum = hspec::Parts(y);
+      if (hspec_status s = run_mamba_core(mc, *L.mamba, u, p.m, x, x_bf16, y, nullptr, nullptr, &x_sum, st)) return s;
+      advance(y);
     }
     if (L.attn) {
-      HIP_TRY(hspec::launch_rmsnorm_planes(x, x_bf16, L.norm2_w, M, ac.d_model, ac.eps, p.at.xn_hi, p.at.xn_lo, st));
+      HIP_TRY(norm(L.norm2_w, ac.d_model, ac.eps, p.at.xn_hi, p.at.xn_lo));
       Planes xn{p.at.xn_hi, p.at.xn_lo};
-      y = dst();
+      float* y = next();
+      x_sum = hspec::Parts(y);
       if (hspec_status s = run_attn_core(ac, *L.attn, xn, L.k_cache, L.v_cache, page_table, ctx_lens, max_ctx_len,
-                                         p.at, x, x_bf16, y, status, 0, st))   // work list, fresh queue
+                                         p.at, x, x_bf16, y, status, plan_clear, &x_sum, st))   // work list, fresh queue
         return s;
-      x = y;
-      x_bf16 = 0;
+      plan_clear = 0;
+      advance(y);
     }
-    HIP_TRY(hspec::launch_rmsnorm_planes(x, x_bf16, L.norm3_w, M, mc.d_model, mc.eps, p.m.u_hi, p.m.u_lo, st));
-    y = dst();
-    if (hspec_status s = run_mlp(mc, L, ff, u, p, x, x_bf16, y, st)) return s;
-    x = y;
-    x_bf16 = 0;
+    HIP_TRY(norm(L.norm3_w, mc.d_model, mc.eps, p.m.u_hi, p.m.u_lo));
+    float* y = next();
+    x_sum = hspec::Parts(y);
+    if (hspec_status s = run_mlp(mc, L, ff, u, p, x, x_bf16, y, done == total ? nullptr : &x_sum, st)) return s;
+    advance(y);
   }
   return HSPEC_OK;
 }

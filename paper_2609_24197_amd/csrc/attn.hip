@@ -462,7 +462,12 @@ __global__ void __launch_bounds__(PLAN_THREADS) attn_plan(AttnArgs a, int clear_
 // sum_s l_s 2^(m_s - m*) over the splits in split order; o = (O_blk + sum) / (l_blk + sum).
 constexpr int RED_COLS = 16;
 constexpr int RED_THREADS = 256;
-constexpr int RED_NS = 4;   // splits whose loads are all issued together; more take further rounds
+// Splits whose loads are all issued together; more take further rounds, after one pass over the running
+// maxima, RED_NM of them at a time.  (8 in every round costs the merge its occupancy, 142 registers against
+// 85: 128 requests of the large shape 345 -> 349 us.  With the maxima read one after the other a request of
+// 8 windowed splits took 7.9 us to merge, now 6.7.)  The reduction that also takes the block keys has
+// few workgroups per CU anyway and takes 8.
+constexpr int RED_NS = 4, RED_NM = 8, RED_NS_MANY = 8;
 
 __device__ __forceinline__ f32x4 ld4_planes(const bf16* hi, const bf16* lo, size_t off) {
   const bf16x4 hv = *reinterpret_cast<const bf16x4*>(hi + off);
@@ -500,6 +505,14 @@ __global__ void __launch_bounds__(RED_THREADS) attn_merge(AttnArgs a) {
     cc[p] = ok[p] ? c0 + it / nq : c0;   // c0 < R: a valid column for the masked lanes
     d4[p] = (it % nq) * 4;
   }
+  float mstar[PER], lsum[PER];
+  f32x4 acc[PER];
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    mstar[p] = -INFINITY;
+    lsum[p] = 0.f;
+    acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   float m[PER][RED_NS], l[PER][RED_NS];
   f32x4 o[PER][RED_NS];
   auto fetch = [&](int s0) {
@@ -518,9 +531,6 @@ __global__ void __launch_bounds__(RED_THREADS) attn_merge(AttnArgs a) {
         o[p][i] = in ? ov : f32x4{0.f, 0.f, 0.f, 0.f};
       }
   };
-  float mstar[PER];
-#pragma unroll
-  for (int p = 0; p < PER; ++p) mstar[p] = -INFINITY;
   if (nsplit <= RED_NS) {
     fetch(0);
 #pragma unroll
@@ -528,16 +538,17 @@ __global__ void __launch_bounds__(RED_THREADS) attn_merge(AttnArgs a) {
 #pragma unroll
       for (int i = 0; i < RED_NS; ++i) mstar[p] = fmaxf(mstar[p], m[p][i]);
   } else {
-    for (int sp = 0; sp < nsplit; ++sp)
+    for (int s0 = 0; s0 < nsplit; s0 += RED_NM) {   // (the last split repeated past the end)
+      float mm[PER][RED_NM];
 #pragma unroll
-      for (int p = 0; p < PER; ++p) mstar[p] = fmaxf(mstar[p], a.part_ml[((unit0 + sp) * R + cc[p]) * 2]);
-  }
-  float lsum[PER];
-  f32x4 acc[PER];
+      for (int p = 0; p < PER; ++p)
 #pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    lsum[p] = 0.f;
-    acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < RED_NM; ++i) mm[p][i] = a.part_ml[((unit0 + min(s0 + i, nsplit - 1)) * R + cc[p]) * 2];
+#pragma unroll
+      for (int p = 0; p < PER; ++p)
+#pragma unroll
+        for (int i = 0; i < RED_NM; ++i) mstar[p] = fmaxf(mstar[p], mm[p][i]);
+    }
   }
   for (int s0 = 0; s0 < nsplit; s0 += RED_NS) {
     if (nsplit > RED_NS) fetch(s0);
@@ -578,6 +589,7 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   constexpr int DPL = D / 16;    // dims per lane in P V and the merge
   constexpr int KC = 16;         // block keys per chunk
   constexpr int P4 = D / 4;      // float4 pieces per row
+  constexpr int NS = RED_NS_MANY;
   static_assert(RED_COLS == 16 && RED_THREADS == 256, "16 columns x 16 lanes");
   __shared__ __align__(16) float sQ[RED_COLS * DP];
   __shared__ __align__(16) float sK[KC * DP];
@@ -597,12 +609,12 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   const int d0 = ln * DPL;
 
   // the splits' running maxima, sums and partial outputs for this lane's dims (all loads in
-  // flight together when there are at most RED_NS splits), issued before the block keys
-  float m[RED_NS], l[RED_NS];
-  f32x4 o[RED_NS][DPL / 4];
+  // flight together when there are at most NS splits), issued before the block keys
+  float m[NS], l[NS];
+  f32x4 o[NS][DPL / 4];
   auto fetch = [&](int s0) {
 #pragma unroll
-    for (int i = 0; i < RED_NS; ++i) {
+    for (int i = 0; i < NS; ++i) {
       const bool in = s0 + i < nsplit;
       const size_t u = (unit0 + s0 + (in ? i : 0)) * R + c;
       m[i] = in ? a.part_ml[u * 2] : -INFINITY;
@@ -612,7 +624,7 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
         o[i][e] = in ? *reinterpret_cast<const f32x4*>(a.part_o + u * D + d0 + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
-  if (nsplit <= RED_NS) fetch(0);
+  if (nsplit <= NS) fetch(0);
 
   // q of the workgroup's columns (the last column repeated past R)
   for (int p = tid; p < RED_COLS * P4; p += RED_THREADS) {
@@ -665,21 +677,27 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   }
 
   float mstar = mb;
-  if (nsplit <= RED_NS) {
+  if (nsplit <= NS) {
 #pragma unroll
-    for (int i = 0; i < RED_NS; ++i) mstar = fmaxf(mstar, m[i]);
+    for (int i = 0; i < NS; ++i) mstar = fmaxf(mstar, m[i]);
   } else {
-    for (int sp = 0; sp < nsplit; ++sp) mstar = fmaxf(mstar, a.part_ml[((unit0 + sp) * R + c) * 2]);
+    for (int s0 = 0; s0 < nsplit; s0 += NS) {   // (the last split repeated past the end)
+      float mm[NS];
+#pragma unroll
+      for (int i = 0; i < NS; ++i) mm[i] = a.part_ml[((unit0 + min(s0 + i, nsplit - 1)) * R + c) * 2];
+#pragma unroll
+      for (int i = 0; i < NS; ++i) mstar = fmaxf(mstar, mm[i]);
+    }
   }
   const float eb = exp2f(mb - mstar);
   float lsum = lb * eb;
   f32x4 acc[DPL / 4];
 #pragma unroll
   for (int e = 0; e < DPL / 4; ++e) acc[e] = ob[e] * eb;
-  for (int s0 = 0; s0 < nsplit; s0 += RED_NS) {
-    if (nsplit > RED_NS) fetch(s0);
+  for (int s0 = 0; s0 < nsplit; s0 += NS) {
+    if (nsplit > NS) fetch(s0);
 #pragma unroll
-    for (int i = 0; i < RED_NS; ++i) {
+    for (int i = 0; i < NS; ++i) {
       const float w = exp2f(m[i] - mstar);
       lsum += l[i] * w;
 #pragma unroll

@@ -1,6 +1,8 @@
 // Normalisation, convolution and rotary kernels of the drafting step, plus small helpers.
 // Each writes its result as bf16 planes ready to be MFMA operands (hi, and lo = rounding
 // residual where the next contraction needs fp32-level accuracy).
+#include <cmath>
+
 #include "common.h"
 #include "kernels.h"
 #include "worklist.h"
@@ -20,7 +22,7 @@ __device__ __forceinline__ float softplus(float v) {
   return fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v)));
 }
 
-// Block-wide sum for 256 threads.
+// Block-wide sum (red: one entry per wave).
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);
   const int w = threadIdx.x >> 6;
@@ -113,8 +115,77 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* x, const float* w
   }
 }
 
+// x = (planes of a product) + residual, written as fp32, and RMSNorm(x) w as bf16 planes: one
+// workgroup of 1024 threads per row, 4 consecutive elements per thread and step, every plane's
+// load in flight together (a row is a chain of latencies: 256 threads took 8 us at 128 rows of 4096 in
+// 8 planes, 1024 take 6.4).  NR > 0: the row fits in NR steps and stays in registers; NR == 0:
+// any n, the second pass re-reads the x it wrote.
+template <int NR>
+__global__ void __launch_bounds__(1024) sum_rmsnorm_kernel(Parts sum, const void* r, int r_bf16, float* x,
+                                                           const float* w, int n, float eps, bf16* hi, bf16* lo) {
+  __shared__ float red[16];
+  const size_t row = (size_t)blockIdx.x * n;
+  auto load_x = [&](int i) {
+    const size_t at[1] = {row + i};
+    f32x4 v[1], q;
+    if (r_bf16) {
+      const bf16x4 b = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const bf16*>(r) + row + i);
+      q = f32x4{bf2f(b[0]), bf2f(b[1]), bf2f(b[2]), bf2f(b[3])};
+    } else {
+      q = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(r) + row + i);
+    }
+    ld4_parts<1, 8>(sum.p, sum.np, sum.plane, at, v);
+    return v[0] + q;
+  };
+  auto scale = [&](int i, f32x4 v, float rs) {
+    const f32x4 g = *reinterpret_cast<const f32x4*>(w + i);
+    bf16x4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float u = v[e] * rs * g[e];
+      h[e] = f2bf(u);
+      l[e] = f2bf(u - bf2f(h[e]));
+    }
+    *reinterpret_cast<bf16x4*>(hi + row + i) = h;
+    if (lo) *reinterpret_cast<bf16x4*>(lo + row + i) = l;
+  };
+  f32x4 v[NR > 0 ? NR : 1];
+  float ss = 0.f;
+  if constexpr (NR > 0) {
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+      const int i = (threadIdx.x + c * 1024) * 4;
+      v[c] = load_x(i < n ? i : 0);
+      if (i >= n) continue;
+      *reinterpret_cast<f32x4*>(x + row + i) = v[c];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss += v[c][e] * v[c][e];
+    }
+  } else {
+    for (int i = threadIdx.x * 4; i < n; i += 4096) {
+      v[0] = load_x(i);
+      *reinterpret_cast<f32x4*>(x + row + i) = v[0];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss += v[0][e] * v[0][e];
+    }
+  }
+  ss = block_sum(ss, red);
+  const float rs = rsqrtf(ss / n + eps);
+  if constexpr (NR > 0) {
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+      const int i = (threadIdx.x + c * 1024) * 4;
+      if (i < n) scale(i, v[c], rs);
+    }
+  } else {
+    for (int i = threadIdx.x * 4; i < n; i += 4096)   // (each thread its own elements)
+      scale(i, *reinterpret_cast<const f32x4*>(x + row + i), rs);
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) conv_split_kernel(ConvArgs a) {
+  if (a.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   const int di = a.H * a.P, gn = a.G * a.N, cdim = di + 2 * gn;
   const int dproj = 2 * di + 2 * gn + a.H;
   const int tok = blockIdx.y;                        // b*T + t
@@ -126,7 +197,7 @@ __global__ void __launch_bounds__(256) conv_split_kernel(ConvArgs a) {
       float v = to_f32(cb[c]);
       for (int j = 0; j < a.K; ++j) {
         const int tau = t - (a.K - 1) + j;
-        if (tau >= 0) v += to_f32(cw[(size_t)c * a.K + j]) * a.zxbcdt[(size_t)(tok - t + tau) * dproj + di + c];
+        if (tau >= 0) v += to_f32(cw[(size_t)c * a.K + j]) * ld1_parts(a.zxbcdt.p, a.zxbcdt.np, a.zxbcdt.plane, (size_t)(tok - t + tau) * dproj + di + c);
       }
       v = silu(v);
       if (c < di) put_planes(a.x_hi, a.x_lo, (size_t)tok * di + c, v);
@@ -134,7 +205,8 @@ __global__ void __launch_bounds__(256) conv_split_kernel(ConvArgs a) {
       else put_planes(a.C_hi, a.C_lo, (size_t)tok * gn + (c - di - gn), v);
     } else {
       const int hh = c - cdim;
-      a.dt[(size_t)tok * a.H + hh] = softplus(a.zxbcdt[(size_t)tok * dproj + 2 * di + 2 * gn + hh] + a.dt_bias[hh]);
+      a.dt[(size_t)tok * a.H + hh] =
+          softplus(ld1_parts(a.zxbcdt.p, a.zxbcdt.np, a.zxbcdt.plane, (size_t)tok * dproj + 2 * di + 2 * gn + hh) + a.dt_bias[hh]);
     }
   }
 }
@@ -144,24 +216,28 @@ __global__ void __launch_bounds__(256) conv_split_kernel(ConvArgs a) {
 // before the block's first are zero) straight from zx, all loads in flight together.  Weights of
 // the 4 channels are 16 consecutive values, read as vectors.  Same alignment needs as the serial
 // kernel below.
-constexpr int CONV_TT = 4;
-
-template <typename T>
+//
+// CONV_TT = 4 reads each input 1.75 times, CONV_TT = 1 four times: with few tokens the launch is
+// a chain of latencies on a handful of workgroups, and one token per thread shortens the chain and
+// makes four times the workgroups (128 tokens of 3200 channels in 5 partial planes: 13.8 -> 6.5 us;
+// 161 tokens in one plane 9.7 -> 5.0).
+template <typename T, int CONV_TT>
 __global__ void __launch_bounds__(256) conv4_tok_kernel(ConvArgs a) {
+  if (a.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   const int di = a.H * a.P, gn = a.G * a.N, cdim = di + 2 * gn;
   const int dproj = 2 * di + 2 * gn + a.H;
   const int nq = (a.T + CONV_TT - 1) / CONV_TT;
   const int b = blockIdx.y / nq, t0 = (blockIdx.y % nq) * CONV_TT;
   const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (c >= cdim + a.H) return;
-  const float* zb = a.zxbcdt + (size_t)b * a.T * dproj;
+  const size_t zb = (size_t)b * a.T * dproj;
   if (c >= cdim) {                                   // dt = softplus(dt_raw + dt_bias), 4 heads
     const int hh = c - cdim;
     f32x4 v[CONV_TT];
+    size_t at[CONV_TT];
 #pragma unroll
-    for (int u = 0; u < CONV_TT; ++u)
-      v[u] = t0 + u < a.T ? *reinterpret_cast<const f32x4*>(zb + (size_t)(t0 + u) * dproj + 2 * di + 2 * gn + hh)
-                          : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < CONV_TT; ++u) at[u] = zb + (size_t)min(t0 + u, a.T - 1) * dproj + 2 * di + 2 * gn + hh;
+    ld4_parts(a.zxbcdt.p, a.zxbcdt.np, a.zxbcdt.plane, at, v);
 #pragma unroll
     for (int u = 0; u < CONV_TT; ++u) {
       if (t0 + u >= a.T) break;
@@ -174,12 +250,13 @@ __global__ void __launch_bounds__(256) conv4_tok_kernel(ConvArgs a) {
   }
   // in[j] is token t0 - 3 + j
   f32x4 in[CONV_TT + 3];
+  size_t at[CONV_TT + 3];
 #pragma unroll
-  for (int j = 0; j < CONV_TT + 3; ++j) {
-    const int tau = t0 - 3 + j;
-    in[j] = tau >= 0 && tau < a.T ? *reinterpret_cast<const f32x4*>(zb + (size_t)tau * dproj + di + c)
-                                  : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int j = 0; j < CONV_TT + 3; ++j) at[j] = zb + (size_t)max(0, min(t0 - 3 + j, a.T - 1)) * dproj + di + c;
+  ld4_parts<CONV_TT + 3, CONV_TT == 1 ? 4 : 2>(a.zxbcdt.p, a.zxbcdt.np, a.zxbcdt.plane, at, in);
+#pragma unroll
+  for (int j = 0; j < 3; ++j)   // (tokens past the last feed no output that is stored)
+    if (t0 - 3 + j < 0) in[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float w[16], bias[4];
   if constexpr (sizeof(T) == 2) {
     const bf16x8 w0 = ld8(reinterpret_cast<const bf16*>(a.conv_w) + (size_t)c * 4);
@@ -230,16 +307,23 @@ __global__ void __launch_bounds__(256) conv4_tok_kernel(ConvArgs a) {
 // dt parts of a zx row 16-byte aligned (checked by the launcher).
 template <typename T>
 __global__ void __launch_bounds__(256) conv_split4_kernel(ConvArgs a) {
+  if (a.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   const int di = a.H * a.P, gn = a.G * a.N, cdim = di + 2 * gn;
   const int dproj = 2 * di + 2 * gn + a.H;
   const int b = blockIdx.y;
   const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (c >= cdim + a.H) return;
-  const float* zrow = a.zxbcdt + (size_t)b * a.T * dproj;
+  const size_t zrow = (size_t)b * a.T * dproj;
+  auto in4 = [&](size_t i) {
+    const size_t at[1] = {i};
+    f32x4 v[1];
+    ld4_parts<1, 4>(a.zxbcdt.p, a.zxbcdt.np, a.zxbcdt.plane, at, v);
+    return v[0];
+  };
   if (c >= cdim) {                                   // dt = softplus(dt_raw + dt_bias), 4 heads
     const int hh = c - cdim;
     for (int t = 0; t < a.T; ++t) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(zrow + (size_t)t * dproj + 2 * di + 2 * gn + hh);
+      const f32x4 v = in4(zrow + (size_t)t * dproj + 2 * di + 2 * gn + hh);
       f32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = softplus(v[e] + a.dt_bias[hh + e]);
@@ -269,7 +353,7 @@ __global__ void __launch_bounds__(256) conv_split4_kernel(ConvArgs a) {
   for (int t = 0; t < a.T; ++t) {
 #pragma unroll
     for (int j = 0; j < 7; ++j) hist[j] = hist[j + 1];
-    hist[7] = *reinterpret_cast<const f32x4*>(zrow + (size_t)t * dproj + di + c);
+    hist[7] = in4(zrow + (size_t)t * dproj + di + c);
     bf16x4 h, l;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -291,24 +375,31 @@ __global__ void __launch_bounds__(256) conv_split4_kernel(ConvArgs a) {
 // gated once, kept in registers between the sum of squares and the scaling pass (chunks past the
 // group's end load its first chunk and count as zero); NR == 0: the second pass re-reads y and z.
 template <bool VEC, int NR>
-__global__ void __launch_bounds__(256) gated_rmsnorm_kernel(const float* y, const float* z, int z_ld,
+__global__ void __launch_bounds__(256) gated_rmsnorm_kernel(const float* y, Parts z, int z_ld,
                                                             const float* w, int n, int G, float eps,
                                                             bf16* hi, bf16* lo) {
   __shared__ float red[4];
   const size_t row = blockIdx.x / G;
   const int gi = blockIdx.x % G, gs = n / G;
   const float* yr = y + row * n + (size_t)gi * gs;
-  const float* zr = z + row * z_ld + (size_t)gi * gs;
+  const size_t zr = row * z_ld + (size_t)gi * gs;
+  auto load8z = [&](int i, float (&v)[8]) {
+    const size_t at[2] = {zr + i, zr + i + 4};
+    f32x4 q[2];
+    ld4_parts(z.p, z.np, z.plane, at, q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = q[e / 4][e % 4];
+  };
   auto gated8 = [&](int i, float (&v)[8]) {
     float zz[8];
     if constexpr (VEC) {
       load8(yr + i, v);
-      load8(zr + i, zz);
+      load8z(i, zz);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         v[e] = yr[i + e];
-        zz[e] = zr[i + e];
+        zz[e] = ld1_parts(z.p, z.np, z.plane, zr + i + e);
       }
     }
 #pragma unroll
@@ -316,12 +407,20 @@ __global__ void __launch_bounds__(256) gated_rmsnorm_kernel(const float* y, cons
   };
   if constexpr (NR > 0) {
     float v[NR][8], zz[NR][8];
+    size_t at[2 * NR];
+    f32x4 zq[2 * NR];
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
       const int i = (threadIdx.x + c * 256) * 8, ic = i < gs ? i : 0;
       load8(yr + ic, v[c]);
-      load8(zr + ic, zz[c]);
+      at[2 * c] = zr + ic;
+      at[2 * c + 1] = zr + ic + 4;
     }
+    ld4_parts(z.p, z.np, z.plane, at, zq);
+#pragma unroll
+    for (int c = 0; c < NR; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) zz[c][e] = zq[2 * c + e / 4][e % 4];
     float ss = 0.f;
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
@@ -374,9 +473,9 @@ __global__ void __launch_bounds__(256) gated_rmsnorm_kernel(const float* y, cons
 constexpr int QKR4_U = 4;
 
 template <bool PLAN>
-__global__ void __launch_bounds__(256) qk_norm_rope4_kernel(const float* qkv, const float* qw, const float* kw,
+__global__ void __launch_bounds__(256) qk_norm_rope4_kernel(Parts qkv, const float* qw, const float* kw,
                                                             const int32_t* ctx_lens, int T, int Hq, int Hkv,
-                                                            int D, float eps, double theta, bf16* q_hi,
+                                                            int D, float eps, double log2_theta, bf16* q_hi,
                                                             bf16* q_lo, bf16* k_hi, bf16* k_lo, bf16* v_hi,
                                                             bf16* v_lo, AttnArgs plan, int plan_clear) {
   if constexpr (PLAN) {   // the first workgroup (dispatched first) builds the KV sweep's work list
@@ -394,20 +493,27 @@ __global__ void __launch_bounds__(256) qk_norm_rope4_kernel(const float* qkv, co
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i0 = 4 * (lane % lph), hsub = lane / lph;
   const int hstep = 4 * hpw;                 // heads per workgroup pass
-  const float* src_tok = qkv + (size_t)tok * nh * D;
+  const size_t src_tok = (size_t)tok * nh * D;
   f32x4 x1[QKR4_U], x2[QKR4_U];
   auto load_heads = [&](int h0) {
+    size_t at[2 * QKR4_U];
+    f32x4 v[2 * QKR4_U];
 #pragma unroll
     for (int u = 0; u < QKR4_U; ++u) {
       const int head = h0 + u * hstep + wave * hpw + hsub;
-      const float* src = src_tok + (size_t)(head < nh ? head : 0) * D + i0;
-      x1[u] = *reinterpret_cast<const f32x4*>(src);
-      x2[u] = *reinterpret_cast<const f32x4*>(src + half);
+      at[2 * u] = src_tok + (size_t)(head < nh ? head : 0) * D + i0;
+      at[2 * u + 1] = at[2 * u] + half;
+    }
+    ld4_parts<2 * QKR4_U, 4>(qkv.p, qkv.np, qkv.plane, at, v);
+#pragma unroll
+    for (int u = 0; u < QKR4_U; ++u) {
+      x1[u] = v[2 * u];
+      x2[u] = v[2 * u + 1];
     }
   };
   load_heads(0);
   for (int p = threadIdx.x; p < half; p += blockDim.x) {
-    double phi = ((double)ctx_lens[b] + j) * pow(theta, -2.0 * (double)p / (double)D);
+    double phi = ((double)ctx_lens[b] + j) * exp2(-2.0 * (double)p / (double)D * log2_theta);
     const double two_pi = 6.283185307179586476925286766559;
     phi -= two_pi * rint(phi / two_pi);
     float sn, cs;
@@ -487,16 +593,24 @@ __global__ void split_kernel(const float* x, size_t n, bf16* hi, bf16* lo) {
     put_planes(hi, lo, i, x[i]);
 }
 
-// h = SiLU(gate) * up for rows [gate | up] of width 2 ff, as bf16 hi/lo planes [rows, ff].
-__global__ void __launch_bounds__(256) silu_mul_kernel(const float* gu, int ff, bf16* hi, bf16* lo) {
+// h = SiLU(gate) * up for rows [gate | up] of width 2 ff, as bf16 hi/lo planes [rows, ff]; four
+// columns per thread (ff % 8 == 0).
+__global__ void __launch_bounds__(256) silu_mul_kernel(Parts gu, int ff, bf16* hi, bf16* lo) {
   const size_t row = blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= ff) return;
-  const float g = gu[row * 2 * ff + i], u = gu[row * 2 * ff + ff + i];
-  const float v = silu(g) * u;
-  const bf16 h = f2bf(v);
-  hi[row * ff + i] = h;
-  if (lo) lo[row * ff + i] = f2bf(v - bf2f(h));
+  const size_t at[2] = {row * 2 * ff + i, row * 2 * ff + ff + i};
+  f32x4 x[2];
+  ld4_parts<2, 4>(gu.p, gu.np, gu.plane, at, x);
+  bf16x4 h, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float v = silu(x[0][e]) * x[1][e];
+    h[e] = f2bf(v);
+    l[e] = f2bf(v - bf2f(h[e]));
+  }
+  *reinterpret_cast<bf16x4*>(hi + row * ff + i) = h;
+  if (lo) *reinterpret_cast<bf16x4*>(lo + row * ff + i) = l;
 }
 
 // Appends the new rows [B*n, Hkv*D] (bf16 planes) of K and V at slot(ctx_len + i) of a paged
@@ -564,14 +678,35 @@ hipError_t launch_rmsnorm_planes(const void* x, int x_bf16, const float* w, int 
   return hipGetLastError();
 }
 
+hipError_t launch_sum_rmsnorm_planes(Parts sum, const void* r, int r_bf16, float* x_out, const float* w, int rows,
+                                     int n, float eps, bf16* out_hi, bf16* out_lo, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  if (n % 8 || !r) return hipErrorInvalidValue;
+  auto launch = [&](auto nrc) {
+    hipLaunchKernelGGL((sum_rmsnorm_kernel<decltype(nrc)::value>), dim3(rows), dim3(1024), 0, s, sum, r, r_bf16, x_out, w,
+                       n, eps, out_hi, out_lo);
+  };
+  if (n <= 4096) launch(Int<1>{});
+  else if (n <= 8192) launch(Int<2>{});
+  else launch(Int<0>{});
+  return hipGetLastError();
+}
+
 hipError_t launch_conv_split(const ConvArgs& a, hipStream_t s) {
   const int di = a.H * a.P, gn = a.G * a.N;
   const int dproj = 2 * di + 2 * gn + a.H;
   const int total = di + 2 * gn + a.H;
   if (dproj % 4 == 0 && di % 4 == 0 && gn % 4 == 0 && a.H % 4 == 0 && a.K == 4) {
-    dim3 grid((total / 4 + 255) / 256, a.B * ((a.T + CONV_TT - 1) / CONV_TT));
-    if (a.w_bf16) hipLaunchKernelGGL(conv4_tok_kernel<bf16>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(conv4_tok_kernel<float>, grid, dim3(256), 0, s, a);
+    const int gx = (total / 4 + 255) / 256;
+    const bool few = (long long)gx * a.B * ((a.T + 3) / 4) < 512;   // fewer than two workgroups per CU
+    const dim3 grid(gx, few ? a.B * a.T : a.B * ((a.T + 3) / 4));
+    if (few) {
+      if (a.w_bf16) hipLaunchKernelGGL((conv4_tok_kernel<bf16, 1>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((conv4_tok_kernel<float, 1>), grid, dim3(256), 0, s, a);
+    } else {
+      if (a.w_bf16) hipLaunchKernelGGL((conv4_tok_kernel<bf16, 4>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((conv4_tok_kernel<float, 4>), grid, dim3(256), 0, s, a);
+    }
     return hipGetLastError();
   }
   if (dproj % 4 == 0 && di % 4 == 0 && gn % 4 == 0 && a.H % 4 == 0 && a.K <= 8) {
@@ -586,7 +721,7 @@ hipError_t launch_conv_split(const ConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gated_rmsnorm(const float* y, const float* z, int z_ld, const float* w, int rows, int n, int G,
+hipError_t launch_gated_rmsnorm(const float* y, Parts z, int z_ld, const float* w, int rows, int n, int G,
                                 float eps, bf16* out_hi, bf16* out_lo, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int gs = n / G;
@@ -601,7 +736,7 @@ hipError_t launch_gated_rmsnorm(const float* y, const float* z, int z_ld, const 
   return hipGetLastError();
 }
 
-hipError_t launch_qk_norm_rope(const float* qkv, const float* qw, const float* kw, const int32_t* ctx_lens, int B,
+hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, const int32_t* ctx_lens, int B,
                                int T, int Hq, int Hkv, int D, float eps, double theta, bf16* q_hi, bf16* q_lo,
                                bf16* k_hi, bf16* k_lo, bf16* v_hi, bf16* v_lo, hipStream_t s, const AttnArgs* plan,
                                int plan_clear) {
@@ -610,10 +745,10 @@ hipError_t launch_qk_norm_rope(const float* qkv, const float* qw, const float* k
   if (plan) {
     if (plan->B > kWorklistFusedMax) return hipErrorInvalidValue;
     hipLaunchKernelGGL(qk_norm_rope4_kernel<true>, dim3(B * T + 1), dim3(256), 0, s, qkv, qw, kw, ctx_lens, T,
-                       Hq, Hkv, D, eps, theta, q_hi, q_lo, k_hi, k_lo, v_hi, v_lo, *plan, plan_clear);
+                       Hq, Hkv, D, eps, log2(theta), q_hi, q_lo, k_hi, k_lo, v_hi, v_lo, *plan, plan_clear);
   } else {
     hipLaunchKernelGGL(qk_norm_rope4_kernel<false>, dim3(B * T), dim3(256), 0, s, qkv, qw, kw, ctx_lens, T,
-                       Hq, Hkv, D, eps, theta, q_hi, q_lo, k_hi, k_lo, v_hi, v_lo, AttnArgs{}, 0);
+                       Hq, Hkv, D, eps, log2(theta), q_hi, q_lo, k_hi, k_lo, v_hi, v_lo, AttnArgs{}, 0);
   }
   return hipGetLastError();
 }
@@ -626,9 +761,10 @@ hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hip
   return hipGetLastError();
 }
 
-hipError_t launch_silu_mul(const float* gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s) {
+hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s) {
   if (rows <= 0 || ff <= 0) return hipSuccess;
-  hipLaunchKernelGGL(silu_mul_kernel, dim3((ff + 255) / 256, rows), dim3(256), 0, s, gu, ff, hi, lo);
+  if (ff % 4) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(silu_mul_kernel, dim3((ff / 4 + 255) / 256, rows), dim3(256), 0, s, gu, ff, hi, lo);
   return hipGetLastError();
 }
 

@@ -602,6 +602,15 @@ __global__ void __launch_bounds__(256) split_reduce4(GemmArgs g, int nparts) {
   }
 }
 
+// Leaves the partial planes to the caller if it takes them.
+bool deferred(const GemmArgs& g, int nparts) {
+  if (!g.defer || g.C_hi || g.C_h16 || g.out_scale != 1.f) return false;
+  g.defer->p = g.part;
+  g.defer->np = nparts;
+  g.defer->plane = (size_t)g.M * g.N;
+  return true;
+}
+
 // Sum of nparts partial planes [M][N] in g.part, with the product's epilogue.
 hipError_t launch_reduce(const GemmArgs& g, int nparts, hipStream_t s) {
   const size_t total = (size_t)g.M * g.N;
@@ -673,11 +682,12 @@ hipError_t launch_skinny_t(const GemmArgs& g, const SkPlan& p, hipStream_t s) {
   auto kern = (g.R && p.ksplit == 1 && !PK) ? skinny_kernel<MT, NTW, NW, ALO, PK, !PK>
                                             : skinny_kernel<MT, NTW, NW, ALO, PK, false>;
   const int nitems = ((g.N + S::BN - 1) / S::BN) * p.ksplit;
-  // one workgroup per CU walks several items when there are more items than CUs
-  const int grid = p.ksplit == 1 && nitems > device_cus() ? device_cus() : nitems;
+  // one workgroup per CU walks several items when there are two rounds of them or more; fewer
+  // run side by side (49152 x 4096 packed, 384 items: 80 -> 69 us)
+  const int grid = p.ksplit == 1 && nitems >= 2 * device_cus() ? device_cus() : nitems;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(S::NT), 0, s, g, p.kper, nitems);
   hipError_t e = hipGetLastError();
-  return e != hipSuccess || p.ksplit == 1 ? e : launch_reduce(g, p.ksplit, s);
+  return e != hipSuccess || p.ksplit == 1 || deferred(g, p.ksplit) ? e : launch_reduce(g, p.ksplit, s);
 }
 
 template <int MT, bool ALO>
@@ -757,9 +767,11 @@ __device__ __forceinline__ void store_block32(const GemmArgs& g, const f32x16& a
 // 48 x 32000 x 4096 70 -> 46 (5.6 TB/s), 16 x 16768 x 4096 52 -> 30, 217 x 6144 x 4096 47 -> 27,
 // 1024 x 4096 x 4096 53 -> 41, 1024 x 4096 x 8192 90 -> 78.
 // Tried and not kept: even shares of all k-tiles per workgroup across tile boundaries (75-80 us at
-// 128 x 24576 x 4096 hi/lo), A stored k-tile by k-tile (no change).
+// 128 x 24576 x 4096 hi/lo), the two k-groups reading and multiplying in alternate slots (73), A stored
+// k-tile by k-tile (no change), and the staggered start in the large tiles below (0-2 % slower at 512 rows
+// and more, where workgroups share W through L2).
 #ifndef HSPEC_BIG_MIN_M
-#define HSPEC_BIG_MIN_M 256   // rows from which products of many tiles take the large tiles
+#define HSPEC_BIG_MIN_M 129   // rows from which products of many tiles take the large tiles
 #endif
 constexpr int SG_KT = 64, SG_NT = 512, SG_BN = 128;
 
@@ -976,9 +988,11 @@ constexpr int stream_bm(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
 // estimate fitted to the measured products above: rounds of the CUs times k-tiles per workgroup
 // (three more for its start and end), no less than W at the streaming rate, and the planes'
 // traffic and reduction.
-// From 256 rows only products whose 128 x 128 tiles fit one round of CUs: beyond that the large
-// tiles are faster (1024 x 6144 x 4096: 74 us against 78; 512 x 24576 x 4096 hi/lo 195 against 211),
-// within it these (1024 x 4096 x 4096: 41 us against 53; 512 x 6320 x 4096: 40 against 50).
+// Past 128 rows only products whose 128 x 128 tiles fit one round of CUs: beyond that the large
+// tiles are faster (1024 x 6144 x 4096: 74 us against 78; 192 x 24576 x 4096 hi/lo 105 against 122, since a
+// 128-wide column tile re-reads A from L2 twice as often: at 128 x 24576 x 4096 hi/lo the DMA of A alone
+// takes 37 us, of W 41, both 59, the whole product 65), within it these (1024 x 4096 x 4096: 41 us
+// against 53; 512 x 6320 x 4096: 40 against 50).
 StreamPlan stream_plan(int M, int N, int K, bool a_lo, int cus) {
   StreamPlan p;
   if (M <= 0 || N <= 0 || K <= 0 || K % SG_KT) return p;
@@ -996,7 +1010,7 @@ StreamPlan stream_plan(int M, int N, int K, bool a_lo, int cus) {
     const double rounds = (double)((tiles * ks + cus - 1) / cus);
     double t = std::max(rounds * (kper + 3) * step, stream);
     if (ks > 1) t += 3 + (double)ks * M * N * 8 / 4e6;
-    if (p.bm == 0 || t < best) {
+    if (p.bm == 0 || t < best || (t == best && tiles * ks <= cus)) {   // (more workgroups at equal estimates)
       best = t;
       p.bm = bm;
       p.mt = (int)mt;
@@ -1058,12 +1072,12 @@ hipError_t launch_stream(const GemmArgs& g, const StreamPlan& p, hipStream_t s) 
     else hipLaunchKernelGGL((gemm_stream_kernel<128, 1, 4>), grid, nt, 0, s, g, p);
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.out == g.C) return e;
+  if (e != hipSuccess || p.out == g.C || deferred(g, p.ksplit)) return e;
   return launch_reduce(g, p.ksplit, s);
 }
 
 // ---------------------------------------------------------------------------------------
-// Large products (M >= 256, the block positions of many requests).  Eight waves in a 2 x 4
+// Large products (the block positions of many requests).  Eight waves in a 2 x 4
 // grid; a wave owns TM x TN blocks of 32 x 32 (v_mfma_f32_32x32x16_bf16) and reads 0.75 KB of
 // LDS fragments per MFMA: 128 x 64 per wave (256 x 256 tiles) for a bf16 A, 64 x 64 per wave
 // with the A lo plane (128 x 256 tiles, two products per block).  With 64 x 64 per wave and one
@@ -1176,6 +1190,7 @@ __global__ void __launch_bounds__(GB_NT) gemm_big_kernel(GemmArgs g, BigPlan p) 
     const int q = (i * 8 + wave) * 64 + lane, row = q / C::CPRT;
     w_off[i] = min(row, rows_w - 1) * g.ldw + 8 * ((q % C::CPRT) ^ swz_key_t<GB_KT>(row));
   }
+  const int nk = ke - kb;
   auto issue = [&](int t, bf16* L, bf16* LW) {
     const int k = t * GB_KT;
 #pragma unroll
@@ -1223,7 +1238,6 @@ __global__ void __launch_bounds__(GB_NT) gemm_big_kernel(GemmArgs g, BigPlan p) 
       }
   };
 
-  const int nk = ke - kb;
   // prologue without branches (tiles past the end re-read the last one into unused stages)
   [&]<int... I>(std::integer_sequence<int, I...>) {
     (issue(min(I, nk - 1), sa_of(Int<I>{}), sw_of(Int<I>{})), ...);
@@ -1522,6 +1536,7 @@ size_t gemm_scratch_elems(int M, int N, int K, bool a_lo, bool w_lo) {
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
+  if (g.defer) *g.defer = Parts(g.C);
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.f16 && !g.w_packed) return hipErrorInvalidValue;   // fp16 operands: the packed W only
   // products with the packed (fp16) W and fp16 outputs run on the weight-streaming path, in
@@ -1529,6 +1544,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if ((g.w_packed || g.C_h16) && g.M > 128 && !g.W2) {
     for (int m0 = 0; m0 < g.M; m0 += 128) {
       GemmArgs h = g;
+      h.defer = nullptr;
       h.M = std::min(128, g.M - m0);
       h.A_hi += (size_t)m0 * g.lda;
       if (h.A_lo) h.A_lo += (size_t)m0 * g.lda;
@@ -1552,6 +1568,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     const int n0s[3] = {0, g.N1, g.N1 + g.N2}, ns[3] = {g.N1, g.N2, g.N - g.N1 - g.N2};
     for (int i = 0; i < 3; ++i) {
       GemmArgs h = g;
+      h.defer = nullptr;
       h.W2 = h.W3 = nullptr;
       h.W_hi = ws[i];
       h.N = ns[i];

@@ -10,6 +10,16 @@ namespace hspec {
 
 typedef __bf16 bf16;
 
+// An fp32 matrix that may still be the partial sums of a product split over K: its value is
+// p[i] + p[plane + i] + ... over np planes, added in plane order.
+struct Parts {
+  const float* p = nullptr;
+  int np = 1;
+  size_t plane = 0;
+  Parts() = default;
+  Parts(const float* q) : p(q) {}
+};
+
 // C[M,N] = A[M,K] * W[N,K]^T (+ R), fp32 accumulate.  *_lo planes are optional.
 struct GemmArgs {
   const bf16* A_hi = nullptr; const bf16* A_lo = nullptr; int lda = 0;
@@ -28,6 +38,10 @@ struct GemmArgs {
   // Optional row segments of W (bf16, not packed): rows [0, N1) come from W_hi, [N1, N1 + N2)
   // from W2 and [N1 + N2, N) from W3, each with leading dimension ldw.
   const bf16* W2 = nullptr; const bf16* W3 = nullptr; int N1 = 0, N2 = 0;
+  // When set (fp32 C and at most R as other output), a product split over K may be left as its
+  // partial sums for the next kernel to add up: *defer receives either C (np = 1, the finished
+  // result, R included) or planes of N columns in `part` (without R).
+  Parts* defer = nullptr;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Whether launch_gemm takes an M x N x K product (bf16 W) on the weight-streaming path, the only
@@ -136,6 +150,7 @@ struct ScanArgs {
   int x_ld = 0;      // elements between consecutive tokens of x (>= H*P)
   int bc_ld = 0;     // elements between consecutive tokens of B and C (>= G*N)
   int dt_ld = 0;     // elements between consecutive tokens of dt (>= H)
+  int* clear = nullptr;   // status words this launch clears (kStatusClear), or null
 };
 hipError_t launch_ssd_scan(const ScanArgs& a, hipStream_t s);
 
@@ -143,10 +158,14 @@ hipError_t launch_ssd_scan(const ScanArgs& a, hipStream_t s);
 // out = x / sqrt(mean(x^2) + eps) * w, rows of n; x is fp32 or bf16; outputs bf16 hi/lo planes.
 hipError_t launch_rmsnorm_planes(const void* x, int x_bf16, const float* w, int rows, int n, float eps,
                                  bf16* out_hi, bf16* out_lo, hipStream_t s);
+// The same of x = sum (the planes of a product) + r (r_bf16: bf16, else fp32), which is also
+// written to x_out (fp32): the residual sum and the next layer's norm in one pass.
+hipError_t launch_sum_rmsnorm_planes(Parts sum, const void* r, int r_bf16, float* x_out, const float* w, int rows,
+                                     int n, float eps, bf16* out_hi, bf16* out_lo, hipStream_t s);
 // Depthwise causal conv (zero left state) + SiLU over the xBC slice of zxbcdt, split into
 // x (bf16 planes) and B, C (bf16 planes); dt = softplus(dt_raw + dt_bias).
 struct ConvArgs {
-  const float* zxbcdt = nullptr;    // [B*T, d_in_proj]
+  Parts zxbcdt;                     // [B*T, d_in_proj]
   const void* conv_w = nullptr;     // [conv_dim, K] storage dtype
   const void* conv_b = nullptr;     // [conv_dim]
   int w_bf16 = 1;
@@ -156,23 +175,24 @@ struct ConvArgs {
   bf16 *B_hi = nullptr, *B_lo = nullptr;   // [B*T, G*N]
   bf16 *C_hi = nullptr, *C_lo = nullptr;
   float* dt = nullptr;                     // [B*T, H]
+  int* clear = nullptr;                    // status words this launch clears (kStatusClear), or null
 };
 hipError_t launch_conv_split(const ConvArgs& a, hipStream_t s);
 // yn = RMSNorm_group(y * SiLU(z)) * w -> bf16 planes.  z rows have stride z_ld.
-hipError_t launch_gated_rmsnorm(const float* y, const float* z, int z_ld, const float* w, int rows,
+hipError_t launch_gated_rmsnorm(const float* y, Parts z, int z_ld, const float* w, int rows,
                                 int n, int G, float eps, bf16* out_hi, bf16* out_lo, hipStream_t s);
 // q/k per-head RMSNorm + RoPE at position ctx_len + j; v copied.  qkv rows [Hq*D | Hkv*D | Hkv*D].
 // With `plan` (at most kWorklistFusedMax requests) one extra workgroup also builds the sweep's
 // work list for those attention arguments, clearing the first plan_clear status words, as
 // launch_attention_plan does.
-hipError_t launch_qk_norm_rope(const float* qkv, const float* qw, const float* kw, const int32_t* ctx_lens,
+hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, const int32_t* ctx_lens,
                                int B, int T, int Hq, int Hkv, int D, float eps, double theta,
                                bf16* q_hi, bf16* q_lo, bf16* k_hi, bf16* k_lo, bf16* v_hi, bf16* v_lo,
                                hipStream_t s, const AttnArgs* plan = nullptr, int plan_clear = 0);
 // fp32 -> bf16 hi/lo planes (lo optional).
 hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hipStream_t s);
 // SwiGLU: h = SiLU(gate) * up from rows [gate | up] (fp32, width 2 ff) -> bf16 planes [rows, ff].
-hipError_t launch_silu_mul(const float* gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s);
+hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s);
 // Appends K/V rows [B*n, Hkv*D] (bf16 planes, lo optional) at slot(ctx_len + i) of a paged cache
 // (bf16 or fp32 storage); unmapped positions set status bit 2, bad page ids bit 1.
 hipError_t launch_kv_append(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi, const bf16* v_lo, int B, int n,

@@ -108,6 +108,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int byt
 
 template <int N, bool LO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1 : 2))) ssd_scan_state(ScanArgs a) {
+  if (a.clear && blockIdx.x == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   constexpr int NJ = (N + 31) / 32;
   constexpr int XP = P + 16, BP = (N < 32 ? 32 : N) + 16;   // LDS row pitches, elements
   constexpr int NPL = LO ? 2 : 1;
@@ -357,6 +358,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1
 // waits for memory once instead of once per state fragment.
 template <int N, bool H16>
 __global__ void __launch_bounds__(64) ssd_scan_one(ScanArgs a) {
+  if (a.clear && blockIdx.x == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   constexpr int NS = (N + 31) / 32;
   __shared__ float xT[P * (QMAX + 1)];   // x^T tile, fp32, padded rows
   __shared__ float Mm[QMAX * (QMAX + 1)];
@@ -493,6 +495,7 @@ __global__ void __launch_bounds__(64) ssd_scan_one(ScanArgs a) {
 constexpr int SCAN_HW = 4;
 template <int N>
 __global__ void __launch_bounds__(64 * SCAN_HW) __attribute__((amdgpu_waves_per_eu(4))) ssd_scan_grp(ScanArgs a) {
+  if (a.clear && blockIdx.x == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
   constexpr int NS = (N + 31) / 32;
   constexpr int CP = N + 8;   // fp16 C row pitch (16 bytes of padding)
   __shared__ float xT_all[SCAN_HW][P * (QMAX + 1)];

@@ -179,6 +179,14 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t) {
   }
   const size_t need = gemm_scratch_elems(g.M, g.N, g.K, g.A_lo != nullptr, g.W_lo != nullptr);
   if (need && g.part_cap >= need) wr("part", g.part, need * F);
+  if (g.defer) {   // partial sums left for the next kernel wherever the scratch allows it
+    *g.defer = Parts(g.C);
+    if (need && g.part_cap >= need && !g.C_hi && !g.C_h16) {
+      g.defer->p = g.part;
+      g.defer->np = 4;
+      g.defer->plane = (size_t)g.M * g.N;
+    }
+  }
   return hipSuccess;
 }
 
@@ -275,7 +283,28 @@ hipError_t launch_ssd_scan(const ScanArgs& a, hipStream_t) {
   rd_opt("S0_lo", a.S0_lo, st * BF);
   rd_opt("S0_h16", a.S0_h16, st * sizeof(_Float16));
   wr("y", a.y, (size_t)rows * a.H * a.P * F);
+  wr_opt("clear", a.clear, kStatusClear * I);
   wr_opt("S_final", a.S_final, st * F);
+  return hipSuccess;
+}
+
+namespace {
+// Every plane of a matrix of n elements.
+void rd_parts(const char* what, const Parts& m, size_t n) {
+  if (m.np < 1) die("planes", m.p, 0);
+  for (int i = 0; i < m.np; ++i) rd(what, m.p + i * m.plane, n * F);
+}
+}  // namespace
+
+hipError_t launch_sum_rmsnorm_planes(Parts sum, const void* r, int r_bf16, float* x_out, const float* w, int rows,
+                                     int n, float, bf16* out_hi, bf16* out_lo, hipStream_t) {
+  Scope s("launch_sum_rmsnorm_planes");
+  rd_parts("sum", sum, (size_t)rows * n);
+  rd("r", r, (size_t)rows * n * (r_bf16 ? BF : F));
+  rd("w", w, (size_t)n * F);
+  wr("x_out", x_out, (size_t)rows * n * F);
+  wr("out_hi", out_hi, (size_t)rows * n * BF);
+  wr_opt("out_lo", out_lo, (size_t)rows * n * BF);
   return hipSuccess;
 }
 
@@ -293,7 +322,8 @@ hipError_t launch_conv_split(const ConvArgs& a, hipStream_t) {
   Scope s("launch_conv_split");
   const size_t rows = (size_t)a.B * a.T, di = (size_t)a.H * a.P, gn = (size_t)a.G * a.N;
   const size_t conv_dim = di + 2 * gn, dproj = 2 * di + 2 * gn + a.H;
-  rd("zxbcdt", a.zxbcdt, rows * dproj * F);
+  rd_parts("zxbcdt", a.zxbcdt, rows * dproj);
+  wr_opt("clear", a.clear, kStatusClear * I);
   rd("conv_w", a.conv_w, conv_dim * a.K * (a.w_bf16 ? BF : F));
   rd("conv_b", a.conv_b, conv_dim * (a.w_bf16 ? BF : F));
   rd("dt_bias", a.dt_bias, (size_t)a.H * F);
@@ -307,25 +337,25 @@ hipError_t launch_conv_split(const ConvArgs& a, hipStream_t) {
   return hipSuccess;
 }
 
-hipError_t launch_gated_rmsnorm(const float* y, const float* z, int z_ld, const float* w, int rows, int n, int,
+hipError_t launch_gated_rmsnorm(const float* y, Parts z, int z_ld, const float* w, int rows, int n, int,
                                 float, bf16* out_hi, bf16* out_lo, hipStream_t) {
   Scope s("launch_gated_rmsnorm");
-  if (z_ld < n) die("z_ld below n", z, 0);
+  if (z_ld < n) die("z_ld below n", z.p, 0);
   rd("y", y, (size_t)rows * n * F);
-  rd("z", z, strided(rows, n, z_ld) * F);
+  rd_parts("z", z, strided(rows, n, z_ld));
   rd("w", w, (size_t)n * F);
   wr("out_hi", out_hi, (size_t)rows * n * BF);
   wr_opt("out_lo", out_lo, (size_t)rows * n * BF);
   return hipSuccess;
 }
 
-hipError_t launch_qk_norm_rope(const float* qkv, const float* qw, const float* kw, const int32_t* ctx_lens, int B,
+hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, const int32_t* ctx_lens, int B,
                                int T, int Hq, int Hkv, int D, float, double, bf16* q_hi, bf16* q_lo, bf16* k_hi,
                                bf16* k_lo, bf16* v_hi, bf16* v_lo, hipStream_t, const AttnArgs* plan,
                                int plan_clear) {
   Scope s("launch_qk_norm_rope");
   const size_t rows = (size_t)B * T;
-  rd("qkv", qkv, rows * (Hq + 2 * Hkv) * D * F);
+  rd_parts("qkv", qkv, rows * (Hq + 2 * Hkv) * D);
   if (Hq > 0) {
     rd("qw", qw, (size_t)D * F);
     wr("q_hi", q_hi, rows * Hq * D * BF);
@@ -352,9 +382,9 @@ hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hip
   return hipSuccess;
 }
 
-hipError_t launch_silu_mul(const float* gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t) {
+hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t) {
   Scope s("launch_silu_mul");
-  rd("gu", gu, (size_t)rows * 2 * ff * F);
+  rd_parts("gu", gu, (size_t)rows * 2 * ff);
   wr("hi", hi, (size_t)rows * ff * BF);
   wr_opt("lo", lo, (size_t)rows * ff * BF);
   return hipSuccess;
