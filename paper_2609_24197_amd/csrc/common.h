@@ -131,6 +131,13 @@ __device__ __forceinline__ float ld1_parts(const float* p, int np, size_t plane,
   return v;
 }
 
+// Buffer resource of `bytes` bytes from base (wave-uniform); accesses past the end read zero and
+// write nothing.  BUF_OOB: an offset past every range.
+constexpr int BUF_OOB = 0x7fffff00;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
 template <int V>
 using Int = std::integral_constant<int, V>;
 

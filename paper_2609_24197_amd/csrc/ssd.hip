@@ -99,13 +99,6 @@ __device__ __forceinline__ void split4(const float* v, bf16x4& hi, bf16x4& lo) {
 //     and of W X against the same x and B, so a hi/lo product costs one instruction.
 // Measured at B = 64, H = 128, N = 128, bf16 (was: state in LDS, one wave of 47 KB per workgroup,
 // three per CU): T = 40 with S_final 500 -> 136 us (3.9 TB/s).
-// Buffer resource of `bytes` bytes from base (wave-uniform); accesses past the end read zero and
-// write nothing.  BUF_OOB: an offset past every range.
-constexpr int BUF_OOB = 0x7fffff00;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
-
 template <int N, bool LO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1 : 2))) ssd_scan_state(ScanArgs a) {
   if (a.clear && blockIdx.x == 0 && threadIdx.x < kStatusClear) a.clear[threadIdx.x] = 0;
@@ -304,7 +297,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float out = dec[i] * ys[i] + Dh * xv[i] + y[i];
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out), yr, y_vo + 64 * pb, i * H * P * 4, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out), yr, y_vo + i * H * P * 4 + 64 * pb, 0, 0);
         w[i] = wv[i] * xv[i];
       }
       bf16x4 wh, wl;

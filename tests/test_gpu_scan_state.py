@@ -32,7 +32,9 @@ def test_scan_state(case, shift):
     d = dev({k: v for k, v in s.items() if v is not None})
     code = hspec.F32 if dtype == "f32" else hspec.BF16
     ws = hspec.workspace(hspec.ssd_scan_workspace(B, T, H, 64, N, G, code))
-    y = torch.full((B, T, H, 64), float("nan"), device="cuda")
+    ny = B * T * H * 64
+    ybuf = torch.full((ny + 16 * H * 64,), float("nan"), device="cuda")   # (room for a whole chunk past the end)
+    y = ybuf[:ny].view(B, T, H, 64)
     n = B * H * 64 * N
     buf = torch.full((n + 8,), float("nan"), device="cuda")
     S = buf[shift:shift + n].view(B, H, 64, N)
@@ -41,5 +43,6 @@ def test_scan_state(case, shift):
     yr, Sr = O.ssd_sequential(s["x"], s["dt"], s["A"], s["Bm"], s["Cm"], s["Dskip"], s["S0"])
     for got, ref in ((host(y), yr), (host(S), Sr)):
         assert np.abs(got - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+    assert torch.isnan(ybuf[ny:]).all()
     rest = host(buf)
     assert np.isnan(rest[:shift]).all() and np.isnan(rest[shift + n:]).all()   # nothing written outside
