@@ -1210,7 +1210,7 @@ void plan_head(Arena& ar, const hspec_head_cfg& c, HeadPlan& p) {
   const size_t M = (size_t)c.B * c.k;
   p.hn = ar.take<bf16>(M * c.d_model);
   p.base = ar.take<float>(M * c.vocab);
-  p.keys = ar.take<unsigned long long>(M);
+  p.keys = ar.take<unsigned long long>(M * hspec::kHeadSlots);
   p.gs = reserve_gemm(ar, HSPEC_BF16, {{(int)M, c.vocab, c.d_model}});
 }
 
@@ -1240,9 +1240,8 @@ HSPEC_API hspec_status hspec_draft_head(const hspec_head_cfg* cfg, const hspec_h
   hspec::HeadArgs h;
   h.B = c.B; h.k = c.k; h.V = c.vocab; h.R = c.rank;
   h.keys = p.keys; h.status = p.status;
-  HIP_TRY(hspec::launch_head_clear(h, hspec::kStatusClear, st));
   const int M = c.B * c.k;
-  HIP_TRY(hspec::launch_rmsnorm_planes(hidden, 0, w->norm_f_w, M, c.d_model, c.eps, p.hn, nullptr, st));
+  HIP_TRY(hspec::launch_head_norm(h, hspec::kStatusClear, hidden, w->norm_f_w, c.d_model, c.eps, p.hn, st));
   // LM head over the pruned vocabulary; written straight into the caller's logits when given
   float* base = logits ? logits : p.base;
   hspec::GemmArgs g;

@@ -63,9 +63,19 @@ __device__ __forceinline__ void put8(bf16* hi, bf16* lo, size_t i, const float (
 // NR chunks of 8 per thread (n <= 2048 NR); every chunk is loaded before the sum of squares and
 // kept in registers for the scaling pass (chunks past the row end load the row's first chunk and
 // count as zero).  NR == 0: any n, the second pass re-reads the row from cache.
-template <typename T, int NR>
+// HEAD: the draft head's first kernel, which also clears the call's status words and keys.
+struct HeadClear {
+  int* status = nullptr;
+  int words = 0;
+  unsigned long long* keys = nullptr;   // kHeadSlots per row
+};
+template <typename T, int NR, bool HEAD = false>
 __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* x, const float* w, int n, float eps,
-                                                      bf16* hi, bf16* lo) {
+                                                      bf16* hi, bf16* lo, HeadClear clr) {
+  if constexpr (HEAD) {
+    if (threadIdx.x < kHeadSlots) clr.keys[(size_t)blockIdx.x * kHeadSlots + threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < clr.words) clr.status[threadIdx.x] = 0;
+  }
   __shared__ float red[4];
   const size_t row = blockIdx.x;
   const T* xr = x + row * n;
@@ -655,26 +665,44 @@ __global__ void zero_kernel(int* p, int n) {
 
 }  // namespace
 
+namespace {
+// f(chunks of 8 per thread when a row of n is held in registers; 0: two passes over the row).
+template <class F>
+void with_row_chunks(int n, F f) {
+  if (n <= 2048) f(Int<1>{});
+  else if (n <= 4096) f(Int<2>{});
+  else if (n <= 8192) f(Int<4>{});
+  else f(Int<0>{});
+}
+}  // namespace
+
 hipError_t launch_rmsnorm_planes(const void* x, int x_bf16, const float* w, int rows, int n, float eps,
                                  bf16* out_hi, bf16* out_lo, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  // chunks of 8 per thread when the row is held in registers (0: two passes over the row)
-  const int nr = n <= 2048 ? 1 : n <= 4096 ? 2 : n <= 8192 ? 4 : 0;
-  auto launch = [&](auto xt, auto nrc) {
-    using T = decltype(xt);
-    hipLaunchKernelGGL((rmsnorm_kernel<T, decltype(nrc)::value>), dim3(rows), dim3(256), 0, s,
-                       (const T*)x, w, n, eps, out_hi, out_lo);
-  };
-  auto by_type = [&](auto nrc) {
-    if (x_bf16) launch(bf16{}, nrc);
-    else launch(0.f, nrc);
-  };
-  switch (nr) {
-    case 1: by_type(Int<1>{}); break;
-    case 2: by_type(Int<2>{}); break;
-    case 4: by_type(Int<4>{}); break;
-    default: by_type(Int<0>{}); break;
-  }
+  with_row_chunks(n, [&](auto nr) {
+    constexpr int NR = decltype(nr)::value;
+    if (x_bf16)
+      hipLaunchKernelGGL((rmsnorm_kernel<bf16, NR>), dim3(rows), dim3(256), 0, s, (const bf16*)x, w, n, eps, out_hi,
+                         out_lo, HeadClear{});
+    else
+      hipLaunchKernelGGL((rmsnorm_kernel<float, NR>), dim3(rows), dim3(256), 0, s, (const float*)x, w, n, eps, out_hi,
+                         out_lo, HeadClear{});
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_head_norm(const HeadArgs& a, int status_words, const float* x, const float* w, int n, float eps,
+                            bf16* out, hipStream_t s) {
+  const int rows = a.B * a.k;
+  if (rows <= 0) return hipSuccess;
+  HeadClear clr;
+  clr.status = a.status;
+  clr.words = status_words;
+  clr.keys = a.keys;
+  with_row_chunks(n, [&](auto nr) {
+    hipLaunchKernelGGL((rmsnorm_kernel<float, decltype(nr)::value, true>), dim3(rows), dim3(256), 0, s, x, w, n, eps, out,
+                       (bf16*)nullptr, clr);
+  });
   return hipGetLastError();
 }
 

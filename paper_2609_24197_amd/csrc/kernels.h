@@ -202,7 +202,9 @@ hipError_t launch_kv_append(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi
 // Zero n int32 words (device status, counters) with a kernel, graph-capture safe.
 hipError_t launch_zero_words(int* p, int n, hipStream_t s);
 
-// Markov correction and token choice of the draft head (one launch per block position).
+// Markov correction and token choice of the draft head (one launch per block position; one for
+// all of them when the tokens are forced).
+constexpr int kHeadSlots = 8;   // keys per (request, position): workgroups spread over them
 struct HeadArgs {
   int B = 0, k = 0, V = 0, R = 0;
   const bf16* E = nullptr;            // [V, R] rank-R code of the preceding token
@@ -213,14 +215,15 @@ struct HeadArgs {
   float inv_temp = 1.f;               // 1 / temperature, with gumbel
   const int32_t* prev = nullptr;      // [B] last committed token
   const int32_t* forced = nullptr;    // [B, k] tokens used as t_{j-1} instead of the chosen ones, or null
-  unsigned long long* keys = nullptr; // [B*k] argmax keys (workspace)
+  unsigned long long* keys = nullptr; // [B*k][kHeadSlots] argmax keys (workspace)
   int32_t* tokens = nullptr;          // [B*k] out
   int* status = nullptr;
 };
-// Clears the status words and the keys of position 0: the first kernel of a head call.
-hipError_t launch_head_clear(const HeadArgs& a, int status_words, hipStream_t s);
-// One Markov-correction launch per block position (each clears the next position's keys),
-// then the tokens.
+// The call's first kernel: RMSNorm(x) w of the rows of x [rows, n] fp32 as one bf16 plane, clearing the
+// status words and every row's argmax keys.
+hipError_t launch_head_norm(const HeadArgs& a, int status_words, const float* x, const float* w, int n, float eps,
+                            bf16* out, hipStream_t s);
+// The Markov-correction launches, then the tokens.
 hipError_t launch_markov_head(const HeadArgs& a, hipStream_t s);
 
 // Host side of the ABI: records msg as this thread's last error (hspec_last_error) and returns s.

@@ -414,10 +414,15 @@ hipError_t launch_zero_words(int* p, int n, hipStream_t) {
   return hipSuccess;
 }
 
-hipError_t launch_head_clear(const HeadArgs& a, int status_words, hipStream_t) {
-  Scope s("launch_head_clear");
+hipError_t launch_head_norm(const HeadArgs& a, int status_words, const float* x, const float* w, int n, float,
+                            bf16* out, hipStream_t) {
+  Scope s("launch_head_norm");
+  const size_t rows = (size_t)a.B * a.k;
+  rd("x", x, rows * n * F);
+  rd("w", w, (size_t)n * F);
+  wr("out", out, rows * n * BF);
   wr("status", a.status, (size_t)status_words * I);
-  wr("keys", a.keys, (size_t)a.B * a.k * sizeof(unsigned long long));
+  wr("keys", a.keys, rows * kHeadSlots * sizeof(unsigned long long));
   return hipSuccess;
 }
 
@@ -431,7 +436,7 @@ hipError_t launch_markov_head(const HeadArgs& a, hipStream_t) {
   rd("prev", a.prev, (size_t)a.B * I);
   rd_opt("forced", a.forced, M * I);
   wr_opt("logits", a.logits, M * a.V * F);
-  wr("keys", a.keys, M * sizeof(unsigned long long));
+  wr("keys", a.keys, M * kHeadSlots * sizeof(unsigned long long));
   wr("tokens", a.tokens, M * I);
   wr("status", a.status, I);
   return hipSuccess;
