@@ -1078,13 +1078,14 @@ HSPEC_API hspec_status hspec_drafter_forward(const hspec_mamba_cfg* mcfg, const 
 
 // ------------------------------------------------ drafter-side KV injection (comparison)
 
+// Layers are taken in groups: one product over the K and V weights of a group, one append launch.
+constexpr int kInjectGroup = hspec::AppendArgs::kMaxLayers;
+
 struct InjectPlan {
   int* status = nullptr;
   SplitSlot h, wfc, wk, wv;
-  float* f = nullptr;                        // fused [M, d_model]
-  bf16 *f_hi = nullptr, *f_lo = nullptr;
-  float* kv = nullptr;                       // [M, 2 Hkv D]: k | v of one layer
-  bf16 *k_hi = nullptr, *k_lo = nullptr, *v_hi = nullptr, *v_lo = nullptr;
+  bf16 *f_hi = nullptr, *f_lo = nullptr;     // fused [M, d_model]
+  float* kv = nullptr;                       // [M, layers of a group, 2 Hkv D]: k | v of each layer
   GemmScratch gs;
 };
 
@@ -1095,15 +1096,14 @@ void plan_inject(Arena& ar, const hspec_attn_cfg& c, int d_h, InjectPlan& p) {
   p.wfc = reserve_split(ar, c.dtype, (size_t)c.d_model * d_h);
   p.wk = reserve_split(ar, c.dtype, kvw * c.d_model);
   p.wv = reserve_split(ar, c.dtype, kvw * c.d_model);
-  p.f = ar.take<float>(M * c.d_model);
   p.f_hi = ar.take<bf16>(M * c.d_model);
   p.f_lo = ar.take<bf16>(M * c.d_model);
-  p.kv = ar.take<float>(M * 2 * kvw);
-  p.k_hi = ar.take<bf16>(M * kvw);
-  p.k_lo = ar.take<bf16>(M * kvw);
-  p.v_hi = ar.take<bf16>(M * kvw);
-  p.v_lo = ar.take<bf16>(M * kvw);
-  p.gs = reserve_gemm(ar, c.dtype, {{(int)M, c.d_model, d_h}, {(int)M, 2 * (int)kvw, c.d_model}, {(int)M, (int)kvw, c.d_model}});
+  p.kv = ar.take<float>(M * 2 * kvw * kInjectGroup);
+  // the fusion, and a group of any size (the last may be short)
+  p.gs.cap = hspec::gemm_scratch_elems((int)M, c.d_model, d_h, true, is_f32(c.dtype));
+  for (int n = 1; n <= 2 * kInjectGroup; ++n)
+    p.gs.cap = std::max(p.gs.cap, hspec::gemm_scratch_elems((int)M, n * (int)kvw, c.d_model, true, is_f32(c.dtype)));
+  if (p.gs.cap) p.gs.p = ar.take<float>(p.gs.cap);
 }
 
 HSPEC_API size_t hspec_kv_inject_workspace(const hspec_attn_cfg* cfg, int d_h) {
@@ -1146,40 +1146,50 @@ HSPEC_API hspec_status hspec_kv_inject(const hspec_attn_cfg* cfg, int d_h, int n
   g.A_hi = h.hi; g.A_lo = h.lo; g.lda = d_h;
   g.W_hi = wfc.hi; g.W_lo = wfc.lo; g.ldw = d_h;
   g.M = M; g.N = c.d_model; g.K = d_h;
-  g.C = p.f; g.ldc = c.d_model;
+  g.C_hi = p.f_hi; g.C_lo = p.f_lo; g.ldch = c.d_model;
   use_scratch(g, p.gs);
   HIP_TRY(hspec::launch_gemm(g, st));
-  HIP_TRY(hspec::launch_split_planes(p.f, (size_t)M * c.d_model, p.f_hi, p.f_lo, st));
-  for (int l = 0; l < n_layers; ++l) {
-    Planes wk, wv;
-    HIP_TRY(as_planes(W_k[l], c.dtype, p.wk, wk, st));
-    HIP_TRY(as_planes(W_v[l], c.dtype, p.wv, wv, st));
-    if (!wk.lo) {   // one product over the two row segments [W_k; W_v]
+  for (int l0 = 0; l0 < n_layers; l0 += kInjectGroup) {
+    const int nl = std::min(kInjectGroup, n_layers - l0), ld = nl * 2 * kvw;
+    hspec::AppendArgs a;
+    a.kv = hspec::Parts(p.kv);
+    if (!is_f32(c.dtype)) {   // one product over the row segments [W_k; W_v] of the group's layers
       hspec::GemmArgs gk;
       gk.A_hi = p.f_hi; gk.A_lo = p.f_lo; gk.lda = c.d_model;
-      gk.W_hi = wk.hi; gk.W2 = wv.hi; gk.N1 = kvw; gk.N2 = kvw; gk.ldw = c.d_model;
-      gk.M = M; gk.N = 2 * kvw; gk.K = c.d_model;
-      gk.C = p.kv; gk.ldc = 2 * kvw;
+      gk.nseg = 2 * nl; gk.seg_rows = kvw; gk.ldw = c.d_model;
+      for (int i = 0; i < nl; ++i) {
+        gk.seg[2 * i] = static_cast<const bf16*>(W_k[l0 + i]);
+        gk.seg[2 * i + 1] = static_cast<const bf16*>(W_v[l0 + i]);
+      }
+      gk.M = M; gk.N = ld; gk.K = c.d_model;
+      gk.C = p.kv; gk.ldc = ld;
+      gk.defer = &a.kv;
       use_scratch(gk, p.gs);
       HIP_TRY(hspec::launch_gemm(gk, st));
     } else {
-      const Planes* w2[2] = {&wk, &wv};
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < 2 * nl; ++i) {
+        Planes w;
+        HIP_TRY(as_planes(i % 2 ? W_v[l0 + i / 2] : W_k[l0 + i / 2], c.dtype, i % 2 ? p.wv : p.wk, w, st));
         hspec::GemmArgs gk;
         gk.A_hi = p.f_hi; gk.A_lo = p.f_lo; gk.lda = c.d_model;
-        gk.W_hi = w2[i]->hi; gk.W_lo = w2[i]->lo; gk.ldw = c.d_model;
+        gk.W_hi = w.hi; gk.W_lo = w.lo; gk.ldw = c.d_model;
         gk.M = M; gk.N = kvw; gk.K = c.d_model;
-        gk.C = p.kv + (size_t)i * kvw; gk.ldc = 2 * kvw;
+        gk.C = p.kv + (size_t)i * kvw; gk.ldc = ld;
         use_scratch(gk, p.gs);
         HIP_TRY(hspec::launch_gemm(gk, st));
       }
     }
-    // k: per-head RMSNorm + RoPE at ctx_len + i (no query heads); v: copied
-    HIP_TRY(hspec::launch_qk_norm_rope(p.kv, nullptr, k_norm_w[l], ctx_lens, c.B, c.k, 0, c.Hkv, c.D, c.eps,
-                                       c.rope_theta, nullptr, nullptr, p.k_hi, p.k_lo, p.v_hi, p.v_lo, st));
-    HIP_TRY(hspec::launch_kv_append(p.k_hi, p.k_lo, p.v_hi, p.v_lo, c.B, c.k, c.Hkv, c.D, page_table, c.max_pages,
-                                    c.num_pages, c.page_size, ctx_lens, k_cache[l], v_cache[l], !is_f32(c.dtype),
-                                    p.status, st));
+    a.n_layers = nl;
+    for (int i = 0; i < nl; ++i) {
+      a.kw[i] = k_norm_w[l0 + i];
+      a.k_cache[i] = k_cache[l0 + i];
+      a.v_cache[i] = v_cache[l0 + i];
+    }
+    a.cache_bf16 = !is_f32(c.dtype);
+    a.B = c.B; a.n = c.k; a.Hkv = c.Hkv; a.D = c.D; a.eps = c.eps; a.rope_theta = c.rope_theta;
+    a.page_table = page_table; a.max_pages = c.max_pages; a.num_pages = c.num_pages; a.ps = c.page_size;
+    a.ctx_lens = ctx_lens; a.status = p.status;
+    HIP_TRY(hspec::launch_kv_append(a, st));
   }
   return HSPEC_OK;
 }

@@ -623,38 +623,91 @@ __global__ void __launch_bounds__(256) silu_mul_kernel(Parts gu, int ff, bf16* h
   if (lo) *reinterpret_cast<bf16x4*>(lo + row * ff + i) = l;
 }
 
-// Appends the new rows [B*n, Hkv*D] (bf16 planes) of K and V at slot(ctx_len + i) of a paged
-// cache.  Positions the table does not map, or page ids outside the pool, set a status bit and
-// are skipped.
+// The new rows of every layer's K and V into its paged cache: one workgroup per token, which computes the
+// token's slot and rotation angles once and then walks the heads of all layers as qk_norm_rope4_kernel
+// does (k: RMSNorm, RoPE; v: copied), D/8 lanes per head.  Positions the table does not map, or page ids
+// outside the pool, set a status bit and are skipped.
 template <typename T>
-__global__ void __launch_bounds__(256) kv_append_kernel(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi,
-                                                        const bf16* v_lo, int n, int row, const int32_t* pt,
-                                                        int max_pages, int num_pages, int ps, const int32_t* lens,
-                                                        T* kc, T* vc, int* status) {
-  const int tok = blockIdx.x, b = tok / n, i = tok % n;
-  const int L = lens[b];
-  const int pos = L + i;
-  const int pg = pos / ps;
-  if (L < 0 || pg >= max_pages) {
-    if (threadIdx.x == 0 && status) atomicOr(status, 2);
+__global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log2_theta) {
+  __shared__ float s_cs[256], s_sn[256];
+  const int tok = blockIdx.x, b = tok / a.n, i = tok % a.n;
+  const int L = a.ctx_lens[b], pos = L + i, pg = pos / a.ps;
+  if (L < 0 || pg >= a.max_pages) {
+    if (threadIdx.x == 0 && a.status) atomicOr(a.status, 2);
     return;
   }
-  const int pid = pt[(size_t)b * max_pages + pg];
-  if (pid < 0 || pid >= num_pages) {
-    if (threadIdx.x == 0 && status) atomicOr(status, 1);
+  const int pid = a.page_table[(size_t)b * a.max_pages + pg];
+  if (pid < 0 || pid >= a.num_pages) {
+    if (threadIdx.x == 0 && a.status) atomicOr(a.status, 1);
     return;
   }
-  const size_t dst = ((size_t)pid * ps + pos % ps) * row, src = (size_t)tok * row;
-  for (int e = threadIdx.x; e < row; e += blockDim.x) {
-    float kv = bf2f(k_hi[src + e]), vv = bf2f(v_hi[src + e]);
-    if (k_lo) kv += bf2f(k_lo[src + e]);
-    if (v_lo) vv += bf2f(v_lo[src + e]);
-    if constexpr (sizeof(T) == 2) {
-      kc[dst + e] = f2bf(kv);
-      vc[dst + e] = f2bf(vv);
-    } else {
-      kc[dst + e] = kv;
-      vc[dst + e] = vv;
+  const int D = a.D, half = D / 2, lph = D / 8, hpp = 256 / lph;   // heads per pass
+  const size_t dst0 = ((size_t)pid * a.ps + pos % a.ps) * a.Hkv * D;
+  for (int p = threadIdx.x; p < half; p += 256) {
+    double phi = (double)pos * exp2(-2.0 * (double)p / (double)D * log2_theta);
+    const double two_pi = 6.283185307179586476925286766559;
+    phi -= two_pi * rint(phi / two_pi);
+    float sn, cs;
+    sincosf((float)phi, &sn, &cs);
+    s_cs[p] = cs;
+    s_sn[p] = sn;
+  }
+  __syncthreads();
+  const int i0 = 4 * (threadIdx.x % lph), nh = a.n_layers * 2 * a.Hkv;
+  f32x4 cs, sn;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    cs[e] = s_cs[i0 + e];
+    sn[e] = s_sn[i0 + e];
+  }
+  constexpr int U = 4;
+  for (int h0 = 0; h0 < nh; h0 += U * hpp) {
+    size_t at[2 * U];
+    f32x4 x[2 * U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int head = h0 + u * hpp + threadIdx.x / lph;
+      at[2 * u] = ((size_t)tok * nh + (head < nh ? head : 0)) * D + i0;
+      at[2 * u + 1] = at[2 * u] + half;
+    }
+    ld4_parts<2 * U, 2>(a.kv.p, a.kv.np, a.kv.plane, at, x);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int head = h0 + u * hpp + threadIdx.x / lph;
+      f32x4 x1 = x[2 * u], x2 = x[2 * u + 1];
+      // sum of squares over the head's D/8 lanes (every lane takes part in the exchange)
+      float ss = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss += x1[e] * x1[e] + x2[e] * x2[e];
+      for (int off = lph / 2; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+      if (head >= nh) continue;
+      const int l = head / (2 * a.Hkv), hh = head % (2 * a.Hkv);
+      const float* kw = a.kw[0];
+      void* dst = hh < a.Hkv ? a.k_cache[0] : a.v_cache[0];
+#pragma unroll
+      for (int k = 1; k < AppendArgs::kMaxLayers; ++k)   // (no indexed copy of the arguments)
+        if (l == k) {
+          kw = a.kw[k];
+          dst = hh < a.Hkv ? a.k_cache[k] : a.v_cache[k];
+        }
+      if (hh < a.Hkv) {
+        const float r = rsqrtf(ss / D + a.eps);
+        const f32x4 g1 = *reinterpret_cast<const f32x4*>(kw + i0), g2 = *reinterpret_cast<const f32x4*>(kw + half + i0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a1 = x1[e] * r * g1[e], a2 = x2[e] * r * g2[e];
+          x1[e] = a1 * cs[e] - a2 * sn[e];
+          x2[e] = a2 * cs[e] + a1 * sn[e];
+        }
+      }
+      T* o = reinterpret_cast<T*>(dst) + dst0 + (size_t)(hh % a.Hkv) * D + i0;
+      if constexpr (sizeof(T) == 2) {
+        *reinterpret_cast<bf16x4*>(o) = bf16x4{f2bf(x1[0]), f2bf(x1[1]), f2bf(x1[2]), f2bf(x1[3])};
+        *reinterpret_cast<bf16x4*>(o + half) = bf16x4{f2bf(x2[0]), f2bf(x2[1]), f2bf(x2[2]), f2bf(x2[3])};
+      } else {
+        *reinterpret_cast<f32x4*>(o) = x1;
+        *reinterpret_cast<f32x4*>(o + half) = x2;
+      }
     }
   }
 }
@@ -796,17 +849,11 @@ hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_kv_append(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi, const bf16* v_lo, int B, int n,
-                            int Hkv, int D, const int32_t* page_table, int max_pages, int num_pages, int ps,
-                            const int32_t* ctx_lens, void* k_cache, void* v_cache, int cache_bf16, int* status,
-                            hipStream_t s) {
-  if (B * n <= 0) return hipSuccess;
-  if (cache_bf16)
-    hipLaunchKernelGGL(kv_append_kernel<bf16>, dim3(B * n), dim3(256), 0, s, k_hi, k_lo, v_hi, v_lo, n, Hkv * D,
-                       page_table, max_pages, num_pages, ps, ctx_lens, (bf16*)k_cache, (bf16*)v_cache, status);
-  else
-    hipLaunchKernelGGL(kv_append_kernel<float>, dim3(B * n), dim3(256), 0, s, k_hi, k_lo, v_hi, v_lo, n, Hkv * D,
-                       page_table, max_pages, num_pages, ps, ctx_lens, (float*)k_cache, (float*)v_cache, status);
+hipError_t launch_kv_append(const AppendArgs& a, hipStream_t s) {
+  if (a.B * a.n <= 0 || a.n_layers <= 0) return hipSuccess;
+  if (a.D < 8 || a.D % 8 || a.D > 512 || 64 % (a.D / 8) || a.n_layers > AppendArgs::kMaxLayers) return hipErrorInvalidValue;
+  if (a.cache_bf16) hipLaunchKernelGGL(kv_append_kernel<bf16>, dim3(a.B * a.n), dim3(256), 0, s, a, log2(a.rope_theta));
+  else hipLaunchKernelGGL(kv_append_kernel<float>, dim3(a.B * a.n), dim3(256), 0, s, a, log2(a.rope_theta));
   return hipGetLastError();
 }
 

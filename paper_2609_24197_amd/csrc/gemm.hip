@@ -721,6 +721,27 @@ __device__ __forceinline__ int swz_t(int row, int chunk) {
   return row * (KT / 8) + (chunk ^ swz_key_t<KT>(row));
 }
 
+// The W row segment that holds column n0: its first row, and the columns [seg0, seg1) it serves (tiles
+// never straddle one).
+__device__ __forceinline__ const bf16* w_segment(const GemmArgs& g, int n0, int& seg0, int& seg1) {
+  const bf16* w = g.W_hi;
+  seg0 = 0;
+  seg1 = g.N;
+  if (g.nseg) {
+    const int i = n0 / g.seg_rows;
+    w = g.seg[0];
+#pragma unroll
+    for (int k = 1; k < GemmArgs::kMaxSeg; ++k) w = i == k ? g.seg[k] : w;   // (no indexed copy of the arguments)
+    seg0 = i * g.seg_rows;
+    seg1 = seg0 + g.seg_rows;
+  } else if (g.W2) {
+    if (n0 >= g.N1 + g.N2) { w = g.W3; seg0 = g.N1 + g.N2; }
+    else if (n0 >= g.N1) { w = g.W2; seg0 = g.N1; seg1 = g.N1 + g.N2; }
+    else seg1 = g.N1;
+  }
+  return w;
+}
+
 __device__ __forceinline__ void dma16(const bf16* src, bf16* lds) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
@@ -825,13 +846,8 @@ __global__ void __launch_bounds__(SG_NT) gemm_stream_kernel(GemmArgs g, StreamPl
   const int kb = kp * p.kper, nk = min(g.K / SG_KT, kb + p.kper) - kb;
 
   const int rows_a = min(BM, g.M - m0);
-  const bf16* wbase = g.W_hi;   // W row segment of this tile (tiles never straddle one)
-  int wseg0 = 0, wseg1 = g.N;
-  if (g.W2) {
-    if (n0 >= g.N1 + g.N2) { wbase = g.W3; wseg0 = g.N1 + g.N2; }
-    else if (n0 >= g.N1) { wbase = g.W2; wseg0 = g.N1; wseg1 = g.N1 + g.N2; }
-    else wseg1 = g.N1;
-  }
+  int wseg0, wseg1;
+  const bf16* wbase = w_segment(g, n0, wseg0, wseg1);
   const int rows_w = min(BN, wseg1 - n0);
   const bf16* Ab = g.A_hi + (size_t)m0 * g.lda + (size_t)kb * SG_KT;
   const bf16* Alb = (NP == 2 ? g.A_lo : g.A_hi) + (size_t)m0 * g.lda + (size_t)kb * SG_KT;
@@ -1031,9 +1047,12 @@ StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   StreamPlan p;
   if (g.W_lo || g.w_packed || g.f16) return p;
   if (g.W2 && (g.N1 % SG_BN || g.N2 % SG_BN)) return p;
+  if (g.nseg && g.seg_rows % SG_BN) return p;
   // 16-byte LDS DMA
   for (const void* q : {(const void*)g.A_hi, (const void*)g.A_lo, (const void*)g.W_hi, (const void*)g.W2, (const void*)g.W3})
     if ((uintptr_t)q % 16) return p;
+  for (int i = 0; i < g.nseg; ++i)
+    if ((uintptr_t)g.seg[i] % 16) return p;
   if (g.lda % 8 || g.ldw % 8) return p;
   // 32-bit element offsets inside a tile's rows of A, W and the output
   const int ldo = std::max(g.ldc, g.N);
@@ -1165,13 +1184,8 @@ __global__ void __launch_bounds__(GB_NT) gemm_big_kernel(GemmArgs g, BigPlan p) 
   const int rows_a = min(BM, g.M - m0);
   const bf16* A0 = g.A_hi + (size_t)m0 * g.lda;
   const bf16* Al0 = (ALO ? g.A_lo : g.A_hi) + (size_t)m0 * g.lda;
-  const bf16* wbase = g.W_hi;   // W row segment of this tile (tiles never straddle one)
-  int wseg0 = 0, wseg1 = g.N;
-  if (g.W2) {
-    if (n0 >= g.N1 + g.N2) { wbase = g.W3; wseg0 = g.N1 + g.N2; }
-    else if (n0 >= g.N1) { wbase = g.W2; wseg0 = g.N1; wseg1 = g.N1 + g.N2; }
-    else wseg1 = g.N1;
-  }
+  int wseg0, wseg1;
+  const bf16* wbase = w_segment(g, n0, wseg0, wseg1);
   const int rows_w = min(BN, wseg1 - n0);
 
   // unit q (16 bytes) of a stage plane: row q / 4, stored chunk q % 4 = logical chunk ^ key(row).
@@ -1393,6 +1407,7 @@ bool big_ok(const GemmArgs& g) {
   // 32-bit element offsets inside a tile's rows of A and W
   if ((long long)bm * g.lda >= (1ll << 31) || (long long)bn * g.ldw >= (1ll << 31)) return false;
   if (g.W2 && (g.N1 % bn || g.N2 % bn)) return false;
+  if (g.nseg && g.seg_rows % bn) return false;
   return true;
 }
 // Row-tile height: 128 for hi/lo A; for one A plane 256, or 128 when 256-row tiles would not
@@ -1541,7 +1556,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.f16 && !g.w_packed) return hipErrorInvalidValue;   // fp16 operands: the packed W only
   // products with the packed (fp16) W and fp16 outputs run on the weight-streaming path, in
   // launches of at most 128 rows
-  if ((g.w_packed || g.C_h16) && g.M > 128 && !g.W2) {
+  if ((g.w_packed || g.C_h16) && g.M > 128 && !g.W2 && !g.nseg) {
     for (int m0 = 0; m0 < g.M; m0 += 128) {
       GemmArgs h = g;
       h.defer = nullptr;
@@ -1561,21 +1576,23 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   }
   // (the packed W is the weight-streaming kernel's own)
   if (const StreamPlan p = stream_plan_for(g, device_cus()); p.bm) return launch_stream(g, p, s);
-  if (g.W2) {
+  if (g.W2 || g.nseg) {
     if (big_ok(g)) return launch_big(g, s);
     // one launch per segment, each writing its own column range of C
     const bf16* ws[3] = {g.W_hi, g.W2, g.W3};
     const int n0s[3] = {0, g.N1, g.N1 + g.N2}, ns[3] = {g.N1, g.N2, g.N - g.N1 - g.N2};
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < (g.nseg ? g.nseg : 3); ++i) {
+      const int n0 = g.nseg ? i * g.seg_rows : n0s[i];
       GemmArgs h = g;
       h.defer = nullptr;
       h.W2 = h.W3 = nullptr;
-      h.W_hi = ws[i];
-      h.N = ns[i];
-      if (h.C) h.C += n0s[i];
-      if (h.C_hi) h.C_hi += n0s[i];
-      if (h.C_lo) h.C_lo += n0s[i];
-      if (h.R) h.R = h.r_bf16 ? (const void*)((const bf16*)h.R + n0s[i]) : (const void*)((const float*)h.R + n0s[i]);
+      h.nseg = 0;
+      h.W_hi = g.nseg ? g.seg[i] : ws[i];
+      h.N = g.nseg ? g.seg_rows : ns[i];
+      if (h.C) h.C += n0;
+      if (h.C_hi) h.C_hi += n0;
+      if (h.C_lo) h.C_lo += n0;
+      if (h.R) h.R = h.r_bf16 ? (const void*)((const bf16*)h.R + n0) : (const void*)((const float*)h.R + n0);
       if (hipError_t e = launch_gemm(h, s)) return e;
     }
     return hipSuccess;

@@ -38,6 +38,10 @@ struct GemmArgs {
   // Optional row segments of W (bf16, not packed): rows [0, N1) come from W_hi, [N1, N1 + N2)
   // from W2 and [N1 + N2, N) from W3, each with leading dimension ldw.
   const bf16* W2 = nullptr; const bf16* W3 = nullptr; int N1 = 0, N2 = 0;
+  // Or nseg row segments of seg_rows rows each, segment i from seg[i] (N = nseg * seg_rows).
+  static constexpr int kMaxSeg = 16;
+  int nseg = 0, seg_rows = 0;
+  const bf16* seg[kMaxSeg] = {};
   // When set (fp32 C and at most R as other output), a product split over K may be left as its
   // partial sums for the next kernel to add up: *defer receives either C (np = 1, the finished
   // result, R included) or planes of N columns in `part` (without R).
@@ -193,12 +197,27 @@ hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, cons
 hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hipStream_t s);
 // SwiGLU: h = SiLU(gate) * up from rows [gate | up] (fp32, width 2 ff) -> bf16 planes [rows, ff].
 hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s);
-// Appends K/V rows [B*n, Hkv*D] (bf16 planes, lo optional) at slot(ctx_len + i) of a paged cache
-// (bf16 or fp32 storage); unmapped positions set status bit 2, bad page ids bit 1.
-hipError_t launch_kv_append(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi, const bf16* v_lo, int B, int n,
-                            int Hkv, int D, const int32_t* page_table, int max_pages, int num_pages, int ps,
-                            const int32_t* ctx_lens, void* k_cache, void* v_cache, int cache_bf16, int* status,
-                            hipStream_t s);
+// New K/V rows of n_layers drafter-side caches: rows of kv [B*n, n_layers * 2 * Hkv * D] hold k | v of each
+// layer; k gets its per-head RMSNorm (kw[l], [D]) and RoPE at position ctx_len + i, and both are written at
+// slot(ctx_len + i) of that layer's paged cache (bf16 or fp32 storage); unmapped positions set status bit
+// 2, bad page ids bit 1.
+struct AppendArgs {
+  static constexpr int kMaxLayers = GemmArgs::kMaxSeg / 2;
+  Parts kv;
+  int n_layers = 0;
+  const float* kw[kMaxLayers] = {};
+  void* k_cache[kMaxLayers] = {};
+  void* v_cache[kMaxLayers] = {};
+  int cache_bf16 = 1;
+  int B = 0, n = 0, Hkv = 0, D = 0;
+  float eps = 0.f;
+  double rope_theta = 0.;
+  const int32_t* page_table = nullptr;
+  int max_pages = 0, num_pages = 0, ps = 0;
+  const int32_t* ctx_lens = nullptr;
+  int* status = nullptr;
+};
+hipError_t launch_kv_append(const AppendArgs& a, hipStream_t s);
 // Zero n int32 words (device status, counters) with a kernel, graph-capture safe.
 hipError_t launch_zero_words(int* p, int n, hipStream_t s);
 

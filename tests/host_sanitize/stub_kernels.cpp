@@ -148,6 +148,9 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t) {
   rd_opt("A_lo", g.A_lo, strided(g.M, g.K, g.lda) * BF);
   if (g.w_packed) {
     rd("W_hi (packed)", g.W_hi, (size_t)g.N * g.K * BF);
+  } else if (g.nseg) {
+    if (g.nseg < 0 || g.nseg > GemmArgs::kMaxSeg || (long long)g.nseg * g.seg_rows != g.N) die("W segments", nullptr, 0);
+    for (int i = 0; i < g.nseg; ++i) rd("W segment", g.seg[i], strided(g.seg_rows, g.K, g.ldw) * BF);
   } else if (g.W2) {
     const int n3 = g.N - g.N1 - g.N2;
     if (g.N1 <= 0 || g.N2 <= 0 || n3 < 0 || (n3 > 0) != (g.W3 != nullptr)) die("W segments", nullptr, 0);
@@ -390,21 +393,19 @@ hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipSt
   return hipSuccess;
 }
 
-hipError_t launch_kv_append(const bf16* k_hi, const bf16* k_lo, const bf16* v_hi, const bf16* v_lo, int B, int n,
-                            int Hkv, int D, const int32_t* page_table, int max_pages, int num_pages, int ps,
-                            const int32_t* ctx_lens, void* k_cache, void* v_cache, int cache_bf16, int* status,
-                            hipStream_t) {
+hipError_t launch_kv_append(const AppendArgs& a, hipStream_t) {
   Scope s("launch_kv_append");
-  const size_t rows = (size_t)B * n * Hkv * D, cache = (size_t)num_pages * ps * Hkv * D * (cache_bf16 ? BF : F);
-  rd("k_hi", k_hi, rows * BF);
-  rd_opt("k_lo", k_lo, rows * BF);
-  rd("v_hi", v_hi, rows * BF);
-  rd_opt("v_lo", v_lo, rows * BF);
-  rd("page_table", page_table, (size_t)B * max_pages * I);
-  rd("ctx_lens", ctx_lens, (size_t)B * I);
-  wr("k_cache", k_cache, cache);
-  wr("v_cache", v_cache, cache);
-  wr("status", status, I);
+  if (a.n_layers < 1 || a.n_layers > AppendArgs::kMaxLayers) die("layers", nullptr, 0);
+  const size_t row = (size_t)a.Hkv * a.D, cache = (size_t)a.num_pages * a.ps * row * (a.cache_bf16 ? BF : F);
+  rd_parts("kv", a.kv, (size_t)a.B * a.n * a.n_layers * 2 * row);
+  rd("page_table", a.page_table, (size_t)a.B * a.max_pages * I);
+  rd("ctx_lens", a.ctx_lens, (size_t)a.B * I);
+  for (int l = 0; l < a.n_layers; ++l) {
+    rd("kw", a.kw[l], (size_t)a.D * F);
+    wr("k_cache", a.k_cache[l], cache);
+    wr("v_cache", a.v_cache[l], cache);
+  }
+  wr("status", a.status, I);
   return hipSuccess;
 }
 

@@ -1,0 +1,65 @@
+"""KV injection over layer groups: one layer, more than one group of eight, row segments that do and do not
+fill column tiles, few and many rows, both storages; unmapped positions and bad pages are flagged and
+skipped, every other slot keeps its value."""
+import numpy as np
+import pytest
+
+import oracle.hspec_oracle as O
+from gpu_util import dev, host
+from paper_2609_24197_amd import hspec, inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,k,layers,Hkv,D,dm,dtype", [
+    (1, 1, 1, 1, 64, 64, "bf16"), (3, 5, 9, 2, 64, 128, "bf16"), (2, 16, 3, 1, 128, 192, "bf16"),
+    (20, 16, 8, 2, 128, 256, "bf16"), (4, 4, 10, 3, 64, 72, "bf16"), (2, 3, 9, 1, 64, 64, "f32"),
+])
+def test_inject_groups(B, k, layers, Hkv, D, dm, dtype):
+    cfg = I.StepConfig(name="i", B=B, k=k, d_model=dm, H=2, P=64, N=16, G=1, chunk=16, Hq=Hkv, Hkv=Hkv, D=D, dtype=dtype,
+                       lengths="uniform:0:40", n_fuse=2)
+    L = I.make_lengths(cfg, 1)
+    pt, pages = I.make_page_table(cfg, L + k, 1, extra_pages=2)
+    W = I.make_inject_weights(cfg, 1, layers)
+    h = I.normal("h", (B, k, cfg.d_h), 1.0, 1, dtype)
+    shape = (pages, cfg.page_size, Hkv, D)
+    caches = [dict(k_cache=I.normal(f"k{i}", shape, 1.0, 1, dtype), v_cache=I.normal(f"v{i}", shape, 1.0, 1, dtype))
+              for i in range(layers)]
+    d = dict(W_fc=hspec.to_device(W["W_fc"]), layers=[dev(w) for w in W["layers"]])
+    dc = [dev(c) for c in caches]
+    ws = hspec.workspace(hspec.kv_inject_workspace(cfg, pt.shape[1], pages))
+    hspec.kv_inject(cfg, d, hspec.to_device(h), dc, hspec.to_device(pt), hspec.to_device(L), ws)
+    assert hspec.read_status(ws) == 0
+    ref = O.kv_inject(h, W["W_fc"], W["layers"], caches, pt, L, cfg)
+    written = {int(pt[b, (L[b] + i) // 16]) * 16 + (int(L[b]) + i) % 16 for b in range(B) for i in range(k)}
+    rest = np.array([s for s in range(pages * 16) if s not in written])
+    f = (lambda a: np.asarray(a, np.float64)) if dtype == "f32" else (lambda a: I.bf16_bits_to_f32(a).astype(np.float64))
+    for l in range(layers):
+        for name in ("k_cache", "v_cache"):
+            got, old = f(host(dc[l][name])), f(caches[l][name])
+            want = np.asarray(ref[l][name], np.float64)
+            # bf16: the result's own rounding (2^-9 of it) and the operands' hi/lo planes; fp32: the planes
+            tol = (2.0 ** -8 if dtype == "bf16" else 2e-4) * np.maximum(1.0, np.abs(want))
+            assert (np.abs(got - want) <= tol).all(), (l, name)
+            assert np.array_equal(got.reshape(pages * 16, -1)[rest], old.reshape(pages * 16, -1)[rest])
+
+
+def test_inject_flags_and_skips():
+    cfg = I.StepConfig(name="i", B=3, k=4, d_model=64, H=2, P=64, N=16, G=1, chunk=16, Hq=1, Hkv=1, D=64,
+                       lengths="list:3,14,30")
+    L = np.array([3, 14, 30], np.int32)
+    pt = np.array([[0, 1], [2, 9], [3, 4]], np.int32)      # request 1 runs into a page outside the pool,
+    pages = 5                                              # request 2 past the table
+    W = I.make_inject_weights(cfg, 2, 2)
+    caches = [dict(k_cache=I.normal(f"k{i}", (pages, 16, 1, 64), 1.0, 2, "bf16"),
+                   v_cache=I.normal(f"v{i}", (pages, 16, 1, 64), 1.0, 2, "bf16")) for i in range(2)]
+    d = dict(W_fc=hspec.to_device(W["W_fc"]), layers=[dev(w) for w in W["layers"]])
+    dc = [dev(c) for c in caches]
+    ws = hspec.workspace(hspec.kv_inject_workspace(cfg, 2, pages))
+    h = I.normal("h", (3, 4, cfg.d_h), 1.0, 2, "bf16")
+    hspec.kv_inject(cfg, d, hspec.to_device(h), dc, hspec.to_device(pt), hspec.to_device(L), ws)
+    assert hspec.read_status(ws) == hspec.DEV_BAD_PAGE | hspec.DEV_BAD_CTX_LEN
+    written = {3, 4, 5, 6, 2 * 16 + 14, 2 * 16 + 15, 4 * 16 + 14, 4 * 16 + 15}
+    for l in range(2):
+        changed = (host(dc[l]["k_cache"]).reshape(80, -1) != caches[l]["k_cache"].reshape(80, -1)).any(1)
+        assert set(np.nonzero(changed)[0]) == written
