@@ -68,12 +68,30 @@ bool is_f32(hspec_dtype d) { return d == HSPEC_F32; }
 long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
 bool dtype_ok(hspec_dtype d) { return d == HSPEC_BF16 || d == HSPEC_F32; }
 
-// A storage-dtype matrix as MFMA planes: bf16 storage is its own hi plane; fp32 storage is
-// split into (hi, lo) inside the workspace.
+// A storage-dtype matrix as MFMA planes: bf16 storage is its own hi plane.  fp32 storage is split
+// into (hi, lo) in the workspace for the kernels that read planes; products read it in place (f32)
+// and split it on chip.
 struct Planes {
   const bf16* hi = nullptr;
   const bf16* lo = nullptr;
+  const float* f32 = nullptr;
 };
+Planes in_place(const void* src, hspec_dtype d) {
+  if (is_f32(d)) return Planes{nullptr, nullptr, static_cast<const float*>(src)};
+  return Planes{static_cast<const bf16*>(src), nullptr, nullptr};
+}
+const bf16* rows_of(const void* w) { return static_cast<const bf16*>(w); }   // (fp32 rows under GemmArgs::w_f32)
+void set_a(hspec::GemmArgs& g, const Planes& a, int ld) {
+  g.A_hi = a.f32 ? rows_of(a.f32) : a.hi;
+  g.A_lo = a.lo;
+  g.a_f32 = a.f32 != nullptr;
+  g.lda = ld;
+}
+void set_w(hspec::GemmArgs& g, const void* w, hspec_dtype d, int ld) {
+  g.W = rows_of(w);
+  g.w_f32 = is_f32(d);
+  g.ldw = ld;
+}
 struct SplitSlot {
   bf16* hi = nullptr;
   bf16* lo = nullptr;
@@ -88,22 +106,24 @@ SplitSlot reserve_split(Arena& ar, hspec_dtype d, size_t n) {
   }
   return s;
 }
-hipError_t as_planes(const void* src, hspec_dtype d, const SplitSlot& slot, Planes& out, hipStream_t st) {
-  if (!is_f32(d)) {
-    out.hi = static_cast<const bf16*>(src);
-    out.lo = nullptr;
-    return hipSuccess;
+// The tensors of a call that have to be split, in one launch.
+struct Splits {
+  hspec::SplitArgs a;
+  Planes add(const void* src, hspec_dtype d, const SplitSlot& slot) {
+    if (!is_f32(d)) return in_place(src, d);
+    a.x[a.n] = static_cast<const float*>(src);
+    a.hi[a.n] = slot.hi;
+    a.lo[a.n] = slot.lo;
+    a.len[a.n++] = slot.n;
+    return Planes{slot.hi, slot.lo, nullptr};
   }
-  out.hi = slot.hi;
-  out.lo = slot.lo;
-  return hspec::launch_split_planes(static_cast<const float*>(src), slot.n, slot.hi, slot.lo, st);
-}
+  hipError_t launch(hipStream_t st) const { return a.n ? hspec::launch_split_planes(a, st) : hipSuccess; }
+};
 
-// The planes as_planes gave for src on an earlier call with the same workspace, without
+// The planes Splits gave for src on an earlier call with the same workspace, without
 // splitting again: src itself for bf16 storage, the workspace slot for fp32.
 Planes planes_in_place(const void* src, hspec_dtype d, const SplitSlot& slot) {
-  if (!is_f32(d)) return Planes{static_cast<const bf16*>(src), nullptr};
-  return Planes{slot.hi, slot.lo};
+  return is_f32(d) ? Planes{slot.hi, slot.lo, nullptr} : in_place(src, d);
 }
 
 // Split-K scratch shared by a sequence of GEMMs on one stream, sized for the largest.
@@ -219,7 +239,6 @@ hspec_status check_ws(void* ws, size_t have, size_t need) {
 constexpr int kFScaleLog2 = 6;
 
 struct StatePlan {
-  SplitSlot h, wr, wds;
   GemmScratch gs;
   bf16 *F_hi = nullptr, *F_lo = nullptr;        // bf16 planes of F (unpacked W_dS)
   _Float16 *F_h16 = nullptr, *F_l16 = nullptr;  // fp16 planes of F (packed W_dS; l16 only precise)
@@ -229,9 +248,6 @@ struct StatePlan {
 
 void plan_state(Arena& ar, const hspec_mamba_cfg& c, bool s0_planes, StatePlan& p) {
   const size_t dS = (size_t)c.H * c.P * c.N;
-  p.h = reserve_split(ar, c.dtype, (size_t)c.B * c.d_h);
-  p.wr = reserve_split(ar, c.dtype, (size_t)c.r * c.d_h);
-  p.wds = reserve_split(ar, c.dtype, dS * c.r);
   if (c.flags & HSPEC_W_DS_PACKED) {
     // one fp16 plane (11 significant bits), or hi/lo fp16 planes with HSPEC_MAMBA_PRECISE_IO
     p.F_h16 = ar.take<_Float16>((size_t)c.B * c.r);
@@ -257,13 +273,9 @@ void plan_state(Arena& ar, const hspec_mamba_cfg& c, bool s0_planes, StatePlan& 
 // bf16 planes and/or one fp16 plane).
 hspec_status run_state(const hspec_mamba_cfg& c, const hspec_mamba_w& w, const void* h_last, const StatePlan& p,
                        float* S0_f32, hipStream_t st) {
-  Planes h, wr, wds;
-  HIP_TRY(as_planes(h_last, c.dtype, p.h, h, st));
-  HIP_TRY(as_planes(w.W_r, c.dtype, p.wr, wr, st));
-  HIP_TRY(as_planes(w.W_dS, c.dtype, p.wds, wds, st));
   hspec::GemmArgs g1;
-  g1.A_hi = h.hi; g1.A_lo = h.lo; g1.lda = c.d_h;
-  g1.W_hi = wr.hi; g1.W_lo = wr.lo; g1.ldw = c.d_h;
+  set_a(g1, in_place(h_last, c.dtype), c.d_h);
+  set_w(g1, w.W_r, c.dtype, c.d_h);
   g1.M = c.B; g1.N = c.r; g1.K = c.d_h;
   g1.C_hi = p.F_hi; g1.C_lo = p.F_lo; g1.ldch = c.r;
   g1.C_h16 = p.F_h16; g1.C_l16 = p.F_l16; g1.h16_scale = 1.f / (1 << kFScaleLog2);
@@ -278,7 +290,7 @@ hspec_status run_state(const hspec_mamba_cfg& c, const hspec_mamba_w& w, const v
     g2.f16 = 1;
     g2.out_scale = (float)(1 << kFScaleLog2) / (float)(1 << hspec::kPackScaleLog2);
   }
-  g2.W_hi = wds.hi; g2.W_lo = wds.lo; g2.ldw = c.r;
+  set_w(g2, w.W_dS, c.dtype, c.r);
   g2.M = c.B; g2.N = dS; g2.K = c.r;
   g2.C = S0_f32; g2.ldc = dS;
   g2.C_hi = p.S0_hi; g2.C_lo = p.S0_lo; g2.C_h16 = p.S0_h16; g2.ldch = dS;
@@ -290,7 +302,6 @@ hspec_status run_state(const hspec_mamba_cfg& c, const hspec_mamba_w& w, const v
 
 struct MambaPlan {
   StatePlan st;
-  SplitSlot u_in, win, wout;
   bf16 *u_hi = nullptr, *u_lo = nullptr;      // normalised block input (draft step)
   float* zx = nullptr;
   bf16 *x_hi = nullptr, *x_lo = nullptr, *B_hi = nullptr, *B_lo = nullptr, *C_hi = nullptr, *C_lo = nullptr;
@@ -313,11 +324,7 @@ void plan_mamba(Arena& ar, const hspec_mamba_cfg& c, bool u_norm, MambaPlan& p) 
   if (u_norm) {
     p.u_hi = ar.take<bf16>(M * c.d_model);
     if (io_lo) p.u_lo = ar.take<bf16>(M * c.d_model);
-  } else {
-    p.u_in = reserve_split(ar, c.dtype, M * c.d_model);
   }
-  p.win = reserve_split(ar, c.dtype, dproj * c.d_model);
-  p.wout = reserve_split(ar, c.dtype, (size_t)c.d_model * di);
   p.zx = ar.take<float>(M * dproj);
   p.x_hi = ar.take<bf16>(M * di);
   p.x_lo = ar.take<bf16>(M * di);   // x feeds the state update: kept as hi/lo planes
@@ -341,12 +348,9 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
   const int M = c.B * c.k;
   const int di = c.H * c.P, gn = c.G * c.N;
   const int dproj = 2 * di + 2 * gn + c.H;
-  Planes win, wout;
-  HIP_TRY(as_planes(w.W_in, c.dtype, p.win, win, st));
-  HIP_TRY(as_planes(w.W_out, c.dtype, p.wout, wout, st));
   hspec::GemmArgs gi;
-  gi.A_hi = u.hi; gi.A_lo = u.lo; gi.lda = c.d_model;
-  gi.W_hi = win.hi; gi.W_lo = win.lo; gi.ldw = c.d_model;
+  set_a(gi, u, c.d_model);
+  set_w(gi, w.W_in, c.dtype, c.d_model);
   gi.M = M; gi.N = dproj; gi.K = c.d_model;
   gi.C = p.zx; gi.ldc = dproj;
   hspec::Parts zx(p.zx);
@@ -375,7 +379,7 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
 
   hspec::GemmArgs go;
   go.A_hi = p.yn_hi; go.A_lo = p.yn_lo; go.lda = di;
-  go.W_hi = wout.hi; go.W_lo = wout.lo; go.ldw = di;
+  set_w(go, w.W_out, c.dtype, di);
   go.M = M; go.N = c.d_model; go.K = di;
   go.C = out; go.ldc = c.d_model;
   go.R = R; go.ldr = c.d_model; go.r_bf16 = r_bf16;
@@ -386,7 +390,7 @@ hspec_status run_mamba_core(const hspec_mamba_cfg& c, const hspec_mamba_w& w, Pl
 }
 
 struct AttnPlan {
-  SplitSlot x_in, wq, wk, wv, wo, kc, vc, qin, kbin, vbin;
+  SplitSlot kc, vc, qin, kbin, vbin;
   bf16 *xn_hi = nullptr, *xn_lo = nullptr;   // normalised input (draft step)
   float* qkv = nullptr;
   bf16 *q_hi = nullptr, *q_lo = nullptr, *k_hi = nullptr, *k_lo = nullptr, *v_hi = nullptr, *v_lo = nullptr;
@@ -429,13 +433,7 @@ void plan_attn(Arena& ar, const hspec_attn_cfg& c, int max_ctx_len, bool x_norm,
   if (x_norm) {
     p.xn_hi = ar.take<bf16>(M * c.d_model);
     if (io_lo) p.xn_lo = ar.take<bf16>(M * c.d_model);
-  } else {
-    p.x_in = reserve_split(ar, c.dtype, M * c.d_model);
   }
-  p.wq = reserve_split(ar, c.dtype, (size_t)c.Hq * c.D * c.d_model);
-  p.wk = reserve_split(ar, c.dtype, (size_t)c.Hkv * c.D * c.d_model);
-  p.wv = reserve_split(ar, c.dtype, (size_t)c.Hkv * c.D * c.d_model);
-  p.wo = reserve_split(ar, c.dtype, (size_t)c.d_model * c.Hq * c.D);
   p.qkv = ar.take<float>(M * (c.Hq + 2 * c.Hkv) * c.D);
   // q, k and v: hi/lo planes for fp32 storage (the sweep's hi/lo products) and for precise
   // attention I/O (the reduction rebuilds the block keys in fp32 from both planes)
@@ -488,39 +486,19 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
   const bool plan_fused = c.B <= hspec::kWorklistFusedMax;
   if (!plan_fused) HIP_TRY(hspec::launch_attention_plan(plan, plan_clear, st));
   const int ldq = (c.Hq + 2 * c.Hkv) * c.D;
-  Planes wq, wk, wv, wo, kc, vc;
-  HIP_TRY(as_planes(w.W_q, c.dtype, p.wq, wq, st));
-  HIP_TRY(as_planes(w.W_k, c.dtype, p.wk, wk, st));
-  HIP_TRY(as_planes(w.W_v, c.dtype, p.wv, wv, st));
-  HIP_TRY(as_planes(w.W_o, c.dtype, p.wo, wo, st));
-  HIP_TRY(as_planes(k_cache, c.dtype, p.kc, kc, st));
-  HIP_TRY(as_planes(v_cache, c.dtype, p.vc, vc, st));
-  const Planes* ws[3] = {&wq, &wk, &wv};
-  const int nrows[3] = {c.Hq * c.D, c.Hkv * c.D, c.Hkv * c.D};
+  Splits split;
+  const Planes kc = split.add(k_cache, c.dtype, p.kc), vc = split.add(v_cache, c.dtype, p.vc);
+  HIP_TRY(split.launch(st));
   hspec::Parts qkv(p.qkv);
-  if (!wq.lo) {
-    // one product over the three row segments [W_q; W_k; W_v]
-    hspec::GemmArgs g;
-    g.A_hi = xn.hi; g.A_lo = xn.lo; g.lda = c.d_model;
-    g.W_hi = wq.hi; g.W2 = wk.hi; g.W3 = wv.hi; g.N1 = nrows[0]; g.N2 = nrows[1]; g.ldw = c.d_model;
-    g.M = M; g.N = ldq; g.K = c.d_model;
-    g.C = p.qkv; g.ldc = ldq;
-    g.defer = &qkv;
-    use_scratch(g, p.gs);
-    HIP_TRY(hspec::launch_gemm(g, st));
-  } else {
-    int col = 0;
-    for (int i = 0; i < 3; ++i) {
-      hspec::GemmArgs g;
-      g.A_hi = xn.hi; g.A_lo = xn.lo; g.lda = c.d_model;
-      g.W_hi = ws[i]->hi; g.W_lo = ws[i]->lo; g.ldw = c.d_model;
-      g.M = M; g.N = nrows[i]; g.K = c.d_model;
-      g.C = p.qkv + col; g.ldc = ldq;
-      use_scratch(g, p.gs);
-      HIP_TRY(hspec::launch_gemm(g, st));
-      col += nrows[i];
-    }
-  }
+  hspec::GemmArgs gq;   // one product over the three row segments [W_q; W_k; W_v]
+  set_a(gq, xn, c.d_model);
+  set_w(gq, w.W_q, c.dtype, c.d_model);
+  gq.W2 = rows_of(w.W_k); gq.W3 = rows_of(w.W_v); gq.N1 = c.Hq * c.D; gq.N2 = c.Hkv * c.D;
+  gq.M = M; gq.N = ldq; gq.K = c.d_model;
+  gq.C = p.qkv; gq.ldc = ldq;
+  gq.defer = &qkv;
+  use_scratch(gq, p.gs);
+  HIP_TRY(hspec::launch_gemm(gq, st));
   HIP_TRY(hspec::launch_qk_norm_rope(qkv, w.q_norm_w, w.k_norm_w, lens, c.B, c.k, c.Hq, c.Hkv, c.D, c.eps,
                                      c.rope_theta, p.q_hi, p.q_lo, p.k_hi, p.k_lo, p.v_hi, p.v_lo, st,
                                      plan_fused ? &plan : nullptr, plan_clear));
@@ -532,7 +510,7 @@ hspec_status run_attn_core(const hspec_attn_cfg& c, const hspec_attn_w& w, Plane
   HIP_TRY(hspec::launch_attention(a, st));
   hspec::GemmArgs g;
   g.A_hi = p.o_hi; g.A_lo = p.o_lo; g.lda = c.Hq * c.D;
-  g.W_hi = wo.hi; g.W_lo = wo.lo; g.ldw = c.Hq * c.D;
+  set_w(g, w.W_o, c.dtype, c.Hq * c.D);
   g.M = M; g.N = c.d_model; g.K = c.Hq * c.D;
   g.C = out; g.ldc = c.d_model;
   g.R = R; g.ldr = c.d_model; g.r_bf16 = r_bf16;
@@ -614,9 +592,7 @@ HSPEC_API hspec_status hspec_mamba_block_scan(const hspec_mamba_cfg* cfg, const 
   MambaPlan p;
   plan_mamba(ar, *cfg, false, p);
   if (hspec_status s = run_state(*cfg, *w, h_last, p.st, nullptr, st)) return s;
-  Planes u;
-  HIP_TRY(as_planes(block_hidden, cfg->dtype, p.u_in, u, st));
-  return run_mamba_core(*cfg, *w, u, p, nullptr, 0, out, S_final, status, nullptr, st);   // (no kernel sets a bit)
+  return run_mamba_core(*cfg, *w, in_place(block_hidden, cfg->dtype), p, nullptr, 0, out, S_final, status, nullptr, st);   // (no kernel sets a bit)
 }
 
 HSPEC_API size_t hspec_target_kv_block_attn_workspace(const hspec_attn_cfg* cfg, int max_ctx_len) {
@@ -646,9 +622,7 @@ HSPEC_API hspec_status hspec_target_kv_block_attn(const hspec_attn_cfg* cfg, con
   AttnPlan p;
   plan_attn(ar, *cfg, max_ctx_len, false, p);
   // no kernel before the work list sets a status bit: the work list clears the status words
-  Planes xn;
-  HIP_TRY(as_planes(x, cfg->dtype, p.x_in, xn, st));
-  return run_attn_core(*cfg, *w, xn, k_cache, v_cache, page_table, ctx_lens, max_ctx_len, p, nullptr, 0, out, status,
+  return run_attn_core(*cfg, *w, in_place(x, cfg->dtype), k_cache, v_cache, page_table, ctx_lens, max_ctx_len, p, nullptr, 0, out, status,
                        hspec::kStatusClear, nullptr, st);
 }
 
@@ -732,15 +706,14 @@ HSPEC_API hspec_status hspec_ssd_scan(int B, int T, int H, int P, int N, int G, 
     sc = reserve_split(ar, dtype, (size_t)B * T * G * N);
     ss = reserve_split(ar, dtype, (size_t)B * H * P * N);
   }
-  Planes px, pb, pc, ps;
-  HIP_TRY(as_planes(x, dtype, sx, px, st));
-  HIP_TRY(as_planes(Bm, dtype, sb, pb, st));
-  HIP_TRY(as_planes(Cm, dtype, sc, pc, st));
-  if (S0) HIP_TRY(as_planes(S0, dtype, ss, ps, st));
+  Splits split;
+  const Planes px = split.add(x, dtype, sx), pb = split.add(Bm, dtype, sb), pc = split.add(Cm, dtype, sc);
+  const Planes ps = S0 ? split.add(S0, dtype, ss) : Planes{};
+  HIP_TRY(split.launch(st));
   hspec::ScanArgs a;
   a.x_hi = px.hi; a.x_lo = px.lo; a.dt = dt; a.A = A; a.A_is_log = 0;
   a.B_hi = pb.hi; a.B_lo = pb.lo; a.C_hi = pc.hi; a.C_lo = pc.lo; a.Dskip = Dskip;
-  a.S0_hi = S0 ? ps.hi : nullptr; a.S0_lo = S0 ? ps.lo : nullptr;
+  a.S0_hi = ps.hi; a.S0_lo = ps.lo;
   a.y = y; a.S_final = S_final;
   a.B = B; a.T = T; a.H = H; a.P = P; a.N = N; a.G = G; a.chunk = chunk;
   a.x_ld = H * P; a.bc_ld = G * N; a.dt_ld = H;
@@ -790,11 +763,13 @@ HSPEC_API hspec_status hspec_paged_attn_phase(const hspec_attn_cfg* cfg, const v
   if (!(phases & (HSPEC_PHASE_SWEEP | HSPEC_PHASE_REDUCE))) return HSPEC_OK;
   Planes pq, pk, pv, kc, vc;
   if (phases & HSPEC_PHASE_SWEEP) {
-    HIP_TRY(as_planes(q, cfg->dtype, p.qin, pq, st));
-    HIP_TRY(as_planes(k_blk, cfg->dtype, p.kbin, pk, st));
-    HIP_TRY(as_planes(v_blk, cfg->dtype, p.vbin, pv, st));
-    HIP_TRY(as_planes(k_cache, cfg->dtype, p.kc, kc, st));
-    HIP_TRY(as_planes(v_cache, cfg->dtype, p.vc, vc, st));
+    Splits split;
+    pq = split.add(q, cfg->dtype, p.qin);
+    pk = split.add(k_blk, cfg->dtype, p.kbin);
+    pv = split.add(v_blk, cfg->dtype, p.vbin);
+    kc = split.add(k_cache, cfg->dtype, p.kc);
+    vc = split.add(v_cache, cfg->dtype, p.vc);
+    HIP_TRY(split.launch(st));
   } else {
     // the reduction alone still reads the block q, k and v: the caller's bf16 tensors, or the
     // planes the sweep phase of this attention wrote into the workspace (fp32 storage)
@@ -839,8 +814,6 @@ HSPEC_API size_t hspec_linear_workspace(hspec_dtype dtype, int M, int N, int K) 
   Arena ar;
   status_word(ar);
   if (M > 0 && N > 0 && K > 0) {
-    reserve_split(ar, dtype, (size_t)M * K);
-    reserve_split(ar, dtype, (size_t)N * K);
     reserve_gemm(ar, dtype, {{M, N, K}});
   }
   return ar.size();
@@ -857,15 +830,11 @@ HSPEC_API hspec_status hspec_linear(hspec_dtype dtype, int M, int N, int K, cons
   hipStream_t st = (hipStream_t)stream;
   Arena ar{(char*)workspace};
   int* status = status_word(ar);
-  SplitSlot sa = reserve_split(ar, dtype, (size_t)M * K), sw = reserve_split(ar, dtype, (size_t)N * K);
   const GemmScratch gs = reserve_gemm(ar, dtype, {{M, N, K}});
   HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
-  Planes pa, pw;
-  HIP_TRY(as_planes(A, dtype, sa, pa, st));
-  HIP_TRY(as_planes(W, dtype, sw, pw, st));
   hspec::GemmArgs g;
-  g.A_hi = pa.hi; g.A_lo = pa.lo; g.lda = K;
-  g.W_hi = pw.hi; g.W_lo = pw.lo; g.ldw = K;
+  set_a(g, in_place(A, dtype), K);
+  set_w(g, W, dtype, K);
   g.M = M; g.N = N; g.K = K;
   g.C = C; g.ldc = N; g.R = R; g.ldr = N; g.r_bf16 = 0;
   use_scratch(g, gs);
@@ -879,7 +848,6 @@ struct ForwardPlan {
   MambaPlan m;                              // with the state plan; its u planes also feed the MLP
   AttnPlan at;
   float *xa = nullptr, *xb = nullptr;       // residual stream, alternating
-  SplitSlot wg, wu, wd;
   float* gu = nullptr;                      // [M, 2 ff]: gate | up
   bf16 *h_hi = nullptr, *h_lo = nullptr;    // [M, ff]
   GemmScratch gs;
@@ -892,9 +860,6 @@ void plan_forward(Arena& ar, const hspec_mamba_cfg& mc, const hspec_attn_cfg& ac
   const size_t M = (size_t)mc.B * mc.k;
   p.xa = ar.take<float>(M * mc.d_model);
   p.xb = ar.take<float>(M * mc.d_model);
-  p.wg = reserve_split(ar, mc.dtype, (size_t)ff * mc.d_model);
-  p.wu = reserve_split(ar, mc.dtype, (size_t)ff * mc.d_model);
-  p.wd = reserve_split(ar, mc.dtype, (size_t)mc.d_model * ff);
   p.gu = ar.take<float>(M * 2 * ff);
   p.h_hi = ar.take<bf16>(M * ff);
   p.h_lo = ar.take<bf16>(M * ff);
@@ -906,36 +871,19 @@ hspec_status run_mlp(const hspec_mamba_cfg& c, const hspec_layer_w& L, int ff, P
                      const void* x, int x_bf16, float* x_out, hspec::Parts* sum, hipStream_t st) {
   const int M = c.B * c.k;
   hspec::Parts gu(p.gu);
-  Planes wg, wu, wd;
-  HIP_TRY(as_planes(L.W_gate, c.dtype, p.wg, wg, st));
-  HIP_TRY(as_planes(L.W_up, c.dtype, p.wu, wu, st));
-  HIP_TRY(as_planes(L.W_down, c.dtype, p.wd, wd, st));
-  if (!wg.lo) {
-    // one product over the two row segments [W_gate; W_up]
-    hspec::GemmArgs g;
-    g.A_hi = u.hi; g.A_lo = u.lo; g.lda = c.d_model;
-    g.W_hi = wg.hi; g.W2 = wu.hi; g.N1 = ff; g.N2 = ff; g.ldw = c.d_model;
-    g.M = M; g.N = 2 * ff; g.K = c.d_model;
-    g.C = p.gu; g.ldc = 2 * ff;
-    g.defer = &gu;
-    use_scratch(g, p.gs);
-    HIP_TRY(hspec::launch_gemm(g, st));
-  } else {
-    const Planes* w2[2] = {&wg, &wu};
-    for (int i = 0; i < 2; ++i) {
-      hspec::GemmArgs g;
-      g.A_hi = u.hi; g.A_lo = u.lo; g.lda = c.d_model;
-      g.W_hi = w2[i]->hi; g.W_lo = w2[i]->lo; g.ldw = c.d_model;
-      g.M = M; g.N = ff; g.K = c.d_model;
-      g.C = p.gu + (size_t)i * ff; g.ldc = 2 * ff;
-      use_scratch(g, p.gs);
-      HIP_TRY(hspec::launch_gemm(g, st));
-    }
-  }
+  hspec::GemmArgs gg;   // one product over the two row segments [W_gate; W_up]
+  set_a(gg, u, c.d_model);
+  set_w(gg, L.W_gate, c.dtype, c.d_model);
+  gg.W2 = rows_of(L.W_up); gg.N1 = ff; gg.N2 = ff;
+  gg.M = M; gg.N = 2 * ff; gg.K = c.d_model;
+  gg.C = p.gu; gg.ldc = 2 * ff;
+  gg.defer = &gu;
+  use_scratch(gg, p.gs);
+  HIP_TRY(hspec::launch_gemm(gg, st));
   HIP_TRY(hspec::launch_silu_mul(gu, M, ff, p.h_hi, p.h_lo, st));
   hspec::GemmArgs g;
   g.A_hi = p.h_hi; g.A_lo = p.h_lo; g.lda = ff;
-  g.W_hi = wd.hi; g.W_lo = wd.lo; g.ldw = ff;
+  set_w(g, L.W_down, c.dtype, ff);
   g.M = M; g.N = c.d_model; g.K = ff;
   g.C = x_out; g.ldc = c.d_model;
   g.R = x; g.ldr = c.d_model; g.r_bf16 = x_bf16;
@@ -1083,7 +1031,6 @@ constexpr int kInjectGroup = hspec::AppendArgs::kMaxLayers;
 
 struct InjectPlan {
   int* status = nullptr;
-  SplitSlot h, wfc, wk, wv;
   bf16 *f_hi = nullptr, *f_lo = nullptr;     // fused [M, d_model]
   float* kv = nullptr;                       // [M, layers of a group, 2 Hkv D]: k | v of each layer
   GemmScratch gs;
@@ -1092,10 +1039,6 @@ struct InjectPlan {
 void plan_inject(Arena& ar, const hspec_attn_cfg& c, int d_h, InjectPlan& p) {
   p.status = status_word(ar);
   const size_t M = (size_t)c.B * c.k, kvw = (size_t)c.Hkv * c.D;
-  p.h = reserve_split(ar, c.dtype, M * d_h);
-  p.wfc = reserve_split(ar, c.dtype, (size_t)c.d_model * d_h);
-  p.wk = reserve_split(ar, c.dtype, kvw * c.d_model);
-  p.wv = reserve_split(ar, c.dtype, kvw * c.d_model);
   p.f_hi = ar.take<bf16>(M * c.d_model);
   p.f_lo = ar.take<bf16>(M * c.d_model);
   p.kv = ar.take<float>(M * 2 * kvw * kInjectGroup);
@@ -1139,12 +1082,9 @@ HSPEC_API hspec_status hspec_kv_inject(const hspec_attn_cfg* cfg, int d_h, int n
   plan_inject(ar, c, d_h, p);
   HIP_TRY(hspec::launch_zero_words(p.status, hspec::kStatusClear, st));
   const int M = c.B * c.k, kvw = c.Hkv * c.D;
-  Planes h, wfc;
-  HIP_TRY(as_planes(h_new, c.dtype, p.h, h, st));
-  HIP_TRY(as_planes(W_fc, c.dtype, p.wfc, wfc, st));
   hspec::GemmArgs g;
-  g.A_hi = h.hi; g.A_lo = h.lo; g.lda = d_h;
-  g.W_hi = wfc.hi; g.W_lo = wfc.lo; g.ldw = d_h;
+  set_a(g, in_place(h_new, c.dtype), d_h);
+  set_w(g, W_fc, c.dtype, d_h);
   g.M = M; g.N = c.d_model; g.K = d_h;
   g.C_hi = p.f_hi; g.C_lo = p.f_lo; g.ldch = c.d_model;
   use_scratch(g, p.gs);
@@ -1153,32 +1093,17 @@ HSPEC_API hspec_status hspec_kv_inject(const hspec_attn_cfg* cfg, int d_h, int n
     const int nl = std::min(kInjectGroup, n_layers - l0), ld = nl * 2 * kvw;
     hspec::AppendArgs a;
     a.kv = hspec::Parts(p.kv);
-    if (!is_f32(c.dtype)) {   // one product over the row segments [W_k; W_v] of the group's layers
-      hspec::GemmArgs gk;
-      gk.A_hi = p.f_hi; gk.A_lo = p.f_lo; gk.lda = c.d_model;
-      gk.nseg = 2 * nl; gk.seg_rows = kvw; gk.ldw = c.d_model;
-      for (int i = 0; i < nl; ++i) {
-        gk.seg[2 * i] = static_cast<const bf16*>(W_k[l0 + i]);
-        gk.seg[2 * i + 1] = static_cast<const bf16*>(W_v[l0 + i]);
-      }
-      gk.M = M; gk.N = ld; gk.K = c.d_model;
-      gk.C = p.kv; gk.ldc = ld;
-      gk.defer = &a.kv;
-      use_scratch(gk, p.gs);
-      HIP_TRY(hspec::launch_gemm(gk, st));
-    } else {
-      for (int i = 0; i < 2 * nl; ++i) {
-        Planes w;
-        HIP_TRY(as_planes(i % 2 ? W_v[l0 + i / 2] : W_k[l0 + i / 2], c.dtype, i % 2 ? p.wv : p.wk, w, st));
-        hspec::GemmArgs gk;
-        gk.A_hi = p.f_hi; gk.A_lo = p.f_lo; gk.lda = c.d_model;
-        gk.W_hi = w.hi; gk.W_lo = w.lo; gk.ldw = c.d_model;
-        gk.M = M; gk.N = kvw; gk.K = c.d_model;
-        gk.C = p.kv + (size_t)i * kvw; gk.ldc = ld;
-        use_scratch(gk, p.gs);
-        HIP_TRY(hspec::launch_gemm(gk, st));
-      }
-    }
+    // one product over the row segments [W_k; W_v] of the group's layers
+    hspec::GemmArgs gk;
+    gk.A_hi = p.f_hi; gk.A_lo = p.f_lo; gk.lda = c.d_model;
+    set_w(gk, nullptr, c.dtype, c.d_model);
+    gk.nseg = 2 * nl; gk.seg_rows = kvw;
+    for (int i = 0; i < 2 * nl; ++i) gk.seg[i] = rows_of(i % 2 ? W_v[l0 + i / 2] : W_k[l0 + i / 2]);
+    gk.M = M; gk.N = ld; gk.K = c.d_model;
+    gk.C = p.kv; gk.ldc = ld;
+    gk.defer = &a.kv;
+    use_scratch(gk, p.gs);
+    HIP_TRY(hspec::launch_gemm(gk, st));
     a.n_layers = nl;
     for (int i = 0; i < nl; ++i) {
       a.kw[i] = k_norm_w[l0 + i];
@@ -1256,7 +1181,7 @@ HSPEC_API hspec_status hspec_draft_head(const hspec_head_cfg* cfg, const hspec_h
   float* base = logits ? logits : p.base;
   hspec::GemmArgs g;
   g.A_hi = p.hn; g.lda = c.d_model;
-  g.W_hi = static_cast<const bf16*>(w->W_lm); g.ldw = c.d_model;
+  g.W = static_cast<const bf16*>(w->W_lm); g.ldw = c.d_model;
   g.M = M; g.N = c.vocab; g.K = c.d_model;
   g.C = base; g.ldc = c.vocab;
   use_scratch(g, p.gs);

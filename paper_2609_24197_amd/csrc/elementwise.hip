@@ -598,9 +598,33 @@ __global__ void __launch_bounds__(256) qk_norm_rope4_kernel(Parts qkv, const flo
   }
 }
 
-__global__ void split_kernel(const float* x, size_t n, bf16* hi, bf16* lo) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    put_planes(hi, lo, i, x[i]);
+// blockIdx.y: tensor.  Four elements per thread and step; the tail one by one.
+__global__ void __launch_bounds__(256) split_kernel(SplitArgs a) {
+  const float* x = a.x[0];
+  bf16 *hi = a.hi[0], *lo = a.lo[0];
+  size_t n = a.len[0];
+#pragma unroll
+  for (int k = 1; k < SplitArgs::kMax; ++k)   // (no indexed copy of the arguments)
+    if (blockIdx.y == k) {
+      x = a.x[k];
+      hi = a.hi[k];
+      lo = a.lo[k];
+      n = a.len[k];
+    }
+  const size_t i0 = blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+  const size_t quads = reinterpret_cast<uintptr_t>(x) % 16 ? 0 : n / 4;
+  for (size_t q = i0; q < quads; q += step) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(x + 4 * q);
+    bf16x4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h[e] = f2bf(v[e]);
+      l[e] = f2bf(v[e] - bf2f(h[e]));
+    }
+    *reinterpret_cast<bf16x4*>(hi + 4 * q) = h;
+    *reinterpret_cast<bf16x4*>(lo + 4 * q) = l;
+  }
+  for (size_t i = 4 * quads + i0; i < n; i += step) put_planes(hi, lo, i, x[i]);
 }
 
 // h = SiLU(gate) * up for rows [gate | up] of width 2 ff, as bf16 hi/lo planes [rows, ff]; four
@@ -834,11 +858,13 @@ hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, cons
   return hipGetLastError();
 }
 
-hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(split_kernel, dim3((unsigned)blocks), dim3(256), 0, s, x, n, hi, lo);
+hipError_t launch_split_planes(const SplitArgs& a, hipStream_t s) {
+  size_t most = 0;
+  for (int i = 0; i < a.n; ++i) most = a.len[i] > most ? a.len[i] : most;
+  if (most == 0) return hipSuccess;
+  size_t blocks = (most / 4 + 255) / 256;
+  blocks = blocks < 1 ? 1 : blocks > 16384 ? 16384 : blocks;
+  hipLaunchKernelGGL(split_kernel, dim3((unsigned)blocks, a.n), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -43,7 +43,7 @@ namespace {
 constexpr int BK = 64;          // k-tile (elements); 128 bytes per row
 constexpr int CPR = BK / 8;     // 16-byte chunks per row
 
-template <int WM, int WN, int TM, int TN, bool ALO, bool WLO>
+template <int WM, int WN, int TM, int TN, bool ALO, bool WF>
 struct GemmCfg {
   static constexpr int NT = 64 * WM * WN;
   static constexpr int BM = WM * TM * 32;
@@ -53,7 +53,7 @@ struct GemmCfg {
   static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/threads mismatch");
   static constexpr int LDS_A = BM * BK;        // elements per plane
   static constexpr int LDS_W = BN * BK;
-  static constexpr int LDS_BYTES = 2 * (LDS_A * (ALO ? 2 : 1) + LDS_W * (WLO ? 2 : 1));
+  static constexpr int LDS_BYTES = 2 * (LDS_A * (ALO ? 2 : 1) + LDS_W * (WF ? 2 : 1));
 };
 
 // LDS position (16-byte units) of chunk `chunk` of tile row `row`: the chunk is XOR-ed with
@@ -77,10 +77,34 @@ __device__ __forceinline__ void tile_of(int id, int total, int mt_count, int& mt
   nt = v / mt_count;
 }
 
-template <int WM, int WN, int TM, int TN, bool ALO, bool WLO>
+// 8 consecutive fp32 elements, and their bf16 hi/lo planes.
+struct F8 {
+  f32x4 a, b;
+};
+__device__ __forceinline__ F8 ld_chunk_f(const float* base, int ld, int row, int col, int rows, int K) {
+  F8 v = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  if (row < rows && col < K) {
+    const float* p = base + (size_t)row * ld + col;
+    v.a = *reinterpret_cast<const f32x4*>(p);
+    v.b = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  return v;
+}
+__device__ __forceinline__ void split_f(const F8& v, bf16x8& hi, bf16x8& lo) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float x = e < 4 ? v.a[e] : v.b[e - 4];
+    hi[e] = f2bf(x);
+    lo[e] = f2bf(x - bf2f(hi[e]));
+  }
+}
+
+// WF, AF: that operand is fp32 in memory and split into its planes on the way into LDS.
+template <int WM, int WN, int TM, int TN, bool ALO, bool WF, bool AF>
 __global__ void __launch_bounds__(64 * WM * WN)
 gemm_kernel(GemmArgs g) {
-  using C = GemmCfg<WM, WN, TM, TN, ALO, WLO>;
+  static_assert(!AF || ALO, "fp32 A is two planes");
+  using C = GemmCfg<WM, WN, TM, TN, ALO, WF>;
   extern __shared__ __align__(16) unsigned char smem[];
   bf16* sA = reinterpret_cast<bf16*>(smem);
   bf16* sAl = sA + C::LDS_A;
@@ -96,34 +120,44 @@ gemm_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
 
-  bf16x8 ra[C::A_CH], ral[ALO ? C::A_CH : 1], rw[C::W_CH], rwl[WLO ? C::W_CH : 1];
+  bf16x8 ra[C::A_CH], ral[ALO ? C::A_CH : 1], rw[C::W_CH], rwl[WF ? C::W_CH : 1];
+  F8 raf[AF ? C::A_CH : 1], rwf[WF ? C::W_CH : 1];
 
   auto load = [&](int k0) {
 #pragma unroll
     for (int i = 0; i < C::A_CH; ++i) {
       int q = i * C::NT + tid, r = q / CPR, c = q % CPR;
+      if constexpr (AF) {
+        raf[i] = ld_chunk_f(reinterpret_cast<const float*>(g.A_hi) + (size_t)m0 * g.lda, g.lda, r, k0 + 8 * c, g.M - m0, g.K);
+        continue;
+      }
       ra[i] = ld_chunk(g.A_hi + (size_t)m0 * g.lda, g.lda, r, k0 + 8 * c, g.M - m0, g.K);
       if constexpr (ALO) ral[i] = ld_chunk(g.A_lo + (size_t)m0 * g.lda, g.lda, r, k0 + 8 * c, g.M - m0, g.K);
     }
 #pragma unroll
     for (int i = 0; i < C::W_CH; ++i) {
       int q = i * C::NT + tid, r = q / CPR, c = q % CPR;
-      rw[i] = ld_chunk(g.W_hi + (size_t)n0 * g.ldw, g.ldw, r, k0 + 8 * c, g.N - n0, g.K);
-      if constexpr (WLO) rwl[i] = ld_chunk(g.W_lo + (size_t)n0 * g.ldw, g.ldw, r, k0 + 8 * c, g.N - n0, g.K);
+      if constexpr (WF) {
+        rwf[i] = ld_chunk_f(reinterpret_cast<const float*>(g.W) + (size_t)n0 * g.ldw, g.ldw, r, k0 + 8 * c, g.N - n0, g.K);
+        continue;
+      }
+      rw[i] = ld_chunk(g.W + (size_t)n0 * g.ldw, g.ldw, r, k0 + 8 * c, g.N - n0, g.K);
     }
   };
   auto store = [&]() {
 #pragma unroll
     for (int i = 0; i < C::A_CH; ++i) {
       int q = i * C::NT + tid, r = q / CPR, c = q % CPR;
+      if constexpr (AF) split_f(raf[i], ra[i], ral[i]);
       *reinterpret_cast<bf16x8*>(sA + 8 * swz(r, c)) = ra[i];
       if constexpr (ALO) *reinterpret_cast<bf16x8*>(sAl + 8 * swz(r, c)) = ral[i];
     }
 #pragma unroll
     for (int i = 0; i < C::W_CH; ++i) {
       int q = i * C::NT + tid, r = q / CPR, c = q % CPR;
+      if constexpr (WF) split_f(rwf[i], rw[i], rwl[i]);
       *reinterpret_cast<bf16x8*>(sW + 8 * swz(r, c)) = rw[i];
-      if constexpr (WLO) *reinterpret_cast<bf16x8*>(sWl + 8 * swz(r, c)) = rwl[i];
+      if constexpr (WF) *reinterpret_cast<bf16x8*>(sWl + 8 * swz(r, c)) = rwl[i];
     }
   };
 
@@ -145,7 +179,7 @@ gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       const int ch = 2 * ks + (lane >> 5);
-      bf16x8 fa[TM], fal[ALO ? TM : 1], fw[TN], fwl[WLO ? TN : 1];
+      bf16x8 fa[TM], fal[ALO ? TM : 1], fw[TN], fwl[WF ? TN : 1];
 #pragma unroll
       for (int a = 0; a < TM; ++a) {
         int r = (wm * TM + a) * 32 + (lane & 31);
@@ -156,7 +190,7 @@ gemm_kernel(GemmArgs g) {
       for (int b = 0; b < TN; ++b) {
         int r = (wn * TN + b) * 32 + (lane & 31);
         fw[b] = *reinterpret_cast<const bf16x8*>(sW + 8 * swz(r, ch));
-        if constexpr (WLO) fwl[b] = *reinterpret_cast<const bf16x8*>(sWl + 8 * swz(r, ch));
+        if constexpr (WF) fwl[b] = *reinterpret_cast<const bf16x8*>(sWl + 8 * swz(r, ch));
       }
 #pragma unroll
       for (int a = 0; a < TM; ++a)
@@ -164,7 +198,7 @@ gemm_kernel(GemmArgs g) {
         for (int b = 0; b < TN; ++b) {
           acc[a][b] = mma32(fa[a], fw[b], acc[a][b]);
           if constexpr (ALO) acc[a][b] = mma32(fal[a], fw[b], acc[a][b]);
-          if constexpr (WLO) acc[a][b] = mma32(fa[a], fwl[b], acc[a][b]);
+          if constexpr (WF) acc[a][b] = mma32(fa[a], fwl[b], acc[a][b]);
         }
     }
   }
@@ -193,6 +227,107 @@ gemm_kernel(GemmArgs g) {
         }
       }
     }
+}
+
+// The W row segment that holds column n0: its first row, and the columns [seg0, seg1) it serves (tiles
+// never straddle one).
+__device__ __forceinline__ const bf16* w_segment(const GemmArgs& g, int n0, int& seg0, int& seg1) {
+  const bf16* w = g.W;
+  seg0 = 0;
+  seg1 = g.N;
+  if (g.nseg) {
+    const int i = n0 / g.seg_rows;
+    w = g.seg[0];
+#pragma unroll
+    for (int k = 1; k < GemmArgs::kMaxSeg; ++k) w = i == k ? g.seg[k] : w;   // (no indexed copy of the arguments)
+    seg0 = i * g.seg_rows;
+    seg1 = seg0 + g.seg_rows;
+  } else if (g.W2) {
+    if (n0 >= g.N1 + g.N2) { w = g.W3; seg0 = g.N1 + g.N2; }
+    else if (n0 >= g.N1) { w = g.W2; seg0 = g.N1; seg1 = g.N1 + g.N2; }
+    else seg1 = g.N1;
+  }
+  return w;
+}
+
+// fp32 storage at up to 64 rows (small models, single requests): a chain of latencies, so as many
+// workgroups as there are 16-column tiles, and one round of loads each where K allows it.  The eight waves of
+// a workgroup take every eighth 32-wide k-step, straight from memory into v_mfma_f32_16x16x32_bf16
+// operands (W as fp32, split into hi/lo planes in registers; A as planes or fp32), and their sums meet
+// in LDS in wave order.  Against a split pass over W (and A) and 64 x 256 tiles, linear() with its status
+// launch: 4 x 256 x 256 17 -> 11 us, 4 x 4096 x 4096 150 -> 19, 64 x 4096 x 4096 156 -> 44,
+// 64 x 24576 x 4096 345 -> 225 (there bound by A, read from L2 once per 16 columns).
+template <int MT, bool AF>
+__global__ void __launch_bounds__(512) gemm_f32_small(GemmArgs g) {
+  __shared__ f32x4 red[8][MT][64];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = blockIdx.x * 16;
+  int seg0, seg1;
+  const float* W = reinterpret_cast<const float*>(w_segment(g, n0, seg0, seg1));   // (segments are whole tiles)
+  const float* wrow = W + (size_t)(min(n0 + l16, g.N - 1) - seg0) * g.ldw;         // (columns past N are not stored)
+  const float* Af = reinterpret_cast<const float*>(g.A_hi);
+  f32x4 acc[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nks = (g.K + 31) / 32;
+#pragma unroll 2
+  for (int ks = wave; ks < nks; ks += 8) {
+    const int k = 32 * ks + 8 * g4;
+    const bool ok = k < g.K;          // (K % 8 == 0: a piece of 8 is whole or absent)
+    const int kc = ok ? k : 0;
+    F8 wf = {*reinterpret_cast<const f32x4*>(wrow + kc), *reinterpret_cast<const f32x4*>(wrow + kc + 4)};
+    bf16x8 ah[MT], al[MT];
+    F8 af[AF ? MT : 1];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const size_t o = (size_t)min(16 * t + l16, g.M - 1) * g.lda + kc;   // (rows past M are not stored)
+      if constexpr (AF) {
+        af[t].a = *reinterpret_cast<const f32x4*>(Af + o);
+        af[t].b = *reinterpret_cast<const f32x4*>(Af + o + 4);
+      } else {
+        ah[t] = ld8(g.A_hi + o);
+        al[t] = ld8(g.A_lo + o);
+      }
+    }
+    bf16x8 wh, wl;
+    split_f(wf, wh, wl);
+    if (!ok) wh = wl = zero8();
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      if constexpr (AF) split_f(af[t], ah[t], al[t]);
+      if (!ok) ah[t] = al[t] = zero8();   // (inf and NaN of the piece read instead)
+      acc[t] = mma16(ah[t], wh, acc[t]);
+      acc[t] = mma16(al[t], wh, acc[t]);
+      acc[t] = mma16(ah[t], wl, acc[t]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[t];
+  __syncthreads();
+  if (tid >= 64 * MT) return;
+  const int t = tid >> 6;
+  f32x4 v = red[0][t][lane];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) v += red[w][t][lane];
+  const int n = n0 + l16;
+  if (n >= g.N) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = 16 * t + 4 * g4 + i;
+    if (m >= g.M) break;
+    float x = v[i];
+    if (g.R) {
+      x += g.r_bf16 ? bf2f(reinterpret_cast<const bf16*>(g.R)[(size_t)m * g.ldr + n])
+                    : reinterpret_cast<const float*>(g.R)[(size_t)m * g.ldr + n];
+    }
+    if (g.C) g.C[(size_t)m * g.ldc + n] = x;
+    if (g.C_hi) {
+      const bf16 h = f2bf(x);
+      g.C_hi[(size_t)m * g.ldch + n] = h;
+      if (g.C_lo) g.C_lo[(size_t)m * g.ldch + n] = f2bf(x - bf2f(h));
+    }
+  }
 }
 
 // ---------------------------------------------------------------- weight-streaming path
@@ -294,14 +429,14 @@ skinny_kernel(GemmArgs g, int kper, int nitems) {
       const int gr = t0 / 32, gs = min(32, ntile16 - 32 * gr);
       const size_t s_k = (size_t)(p_item.kb / SK_STEP + (live ? p_st : 0));
       const __amdgpu_buffer_rsrc_t rs =
-          buf(g.W_hi + ((size_t)gr * 32 * (g.K / SK_STEP) + s_k * gs + (t0 - 32 * gr)) * 512,
+          buf(g.W + ((size_t)gr * 32 * (g.K / SK_STEP) + s_k * gs + (t0 - 32 * gr)) * 512,
               live ? (long long)min(NTW, ntile16 - t0) * 1024 : 0);
 #pragma unroll
       for (int j = 0; j < NTW; ++j)   // aux 2: non-temporal, W is read once
         slot[j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, vrow[j], 0, 2));
     } else {
       const int rows = live ? max(0, min(S::BNW, g.N - p_item.n_w)) : 0;
-      const __amdgpu_buffer_rsrc_t rs = buf(g.W_hi + (size_t)min(p_item.n_w, g.N) * g.ldw, (long long)rows * g.ldw * 2);
+      const __amdgpu_buffer_rsrc_t rs = buf(g.W + (size_t)min(p_item.n_w, g.N) * g.ldw, (long long)rows * g.ldw * 2);
       const int koff = (p_item.kb + p_st * SK_STEP) * 2;
 #pragma unroll
       for (int j = 0; j < NTW; ++j)
@@ -721,27 +856,6 @@ __device__ __forceinline__ int swz_t(int row, int chunk) {
   return row * (KT / 8) + (chunk ^ swz_key_t<KT>(row));
 }
 
-// The W row segment that holds column n0: its first row, and the columns [seg0, seg1) it serves (tiles
-// never straddle one).
-__device__ __forceinline__ const bf16* w_segment(const GemmArgs& g, int n0, int& seg0, int& seg1) {
-  const bf16* w = g.W_hi;
-  seg0 = 0;
-  seg1 = g.N;
-  if (g.nseg) {
-    const int i = n0 / g.seg_rows;
-    w = g.seg[0];
-#pragma unroll
-    for (int k = 1; k < GemmArgs::kMaxSeg; ++k) w = i == k ? g.seg[k] : w;   // (no indexed copy of the arguments)
-    seg0 = i * g.seg_rows;
-    seg1 = seg0 + g.seg_rows;
-  } else if (g.W2) {
-    if (n0 >= g.N1 + g.N2) { w = g.W3; seg0 = g.N1 + g.N2; }
-    else if (n0 >= g.N1) { w = g.W2; seg0 = g.N1; seg1 = g.N1 + g.N2; }
-    else seg1 = g.N1;
-  }
-  return w;
-}
-
 __device__ __forceinline__ void dma16(const bf16* src, bf16* lds) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
@@ -1045,11 +1159,11 @@ constexpr long long kStreamPlaneMax = 1LL << 22;
 // The plan launch_gemm runs a product with on the streamed path, bm = 0 if another path takes it.
 StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   StreamPlan p;
-  if (g.W_lo || g.w_packed || g.f16) return p;
+  if (g.w_f32 || g.w_packed || g.f16) return p;
   if (g.W2 && (g.N1 % SG_BN || g.N2 % SG_BN)) return p;
   if (g.nseg && g.seg_rows % SG_BN) return p;
   // 16-byte LDS DMA
-  for (const void* q : {(const void*)g.A_hi, (const void*)g.A_lo, (const void*)g.W_hi, (const void*)g.W2, (const void*)g.W3})
+  for (const void* q : {(const void*)g.A_hi, (const void*)g.A_lo, (const void*)g.W, (const void*)g.W2, (const void*)g.W3})
     if ((uintptr_t)q % 16) return p;
   for (int i = 0; i < g.nseg; ++i)
     if ((uintptr_t)g.seg[i] % 16) return p;
@@ -1402,7 +1516,7 @@ __global__ void __launch_bounds__(256) gemm_big_fixup(GemmArgs g, BigPlan p) {
 // tiles for every full round, the tiles of a short last round split over K so that the round
 // fills the chip (at least 4 k-tiles per part).
 bool big_ok(const GemmArgs& g) {
-  if (g.M < HSPEC_BIG_MIN_M || g.W_lo || g.w_packed || g.K % GB_KT) return false;
+  if (g.M < HSPEC_BIG_MIN_M || g.w_f32 || g.w_packed || g.K % GB_KT) return false;
   const int bm = g.A_lo ? BigCfg<true>::BM : BigCfg<false>::BM, bn = g.A_lo ? BigCfg<true>::BN : BigCfg<false>::BN;
   // 32-bit element offsets inside a tile's rows of A and W
   if ((long long)bm * g.lda >= (1ll << 31) || (long long)bn * g.ldw >= (1ll << 31)) return false;
@@ -1465,10 +1579,10 @@ hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int WM, int WN, int TM, int TN, bool ALO, bool WLO>
+template <int WM, int WN, int TM, int TN, bool ALO, bool WF, bool AF>
 hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
-  using C = GemmCfg<WM, WN, TM, TN, ALO, WLO>;
-  auto kern = gemm_kernel<WM, WN, TM, TN, ALO, WLO>;
+  using C = GemmCfg<WM, WN, TM, TN, ALO, WF>;
+  auto kern = gemm_kernel<WM, WN, TM, TN, ALO, WF, AF>;
   const int tiles = ((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
   if (C::LDS_BYTES > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
@@ -1480,11 +1594,31 @@ hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
 
 template <int WM, int WN, int TM, int TN>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
-  const bool alo = g.A_lo != nullptr, wlo = g.W_lo != nullptr;
-  if (!alo && !wlo) return launch_one<WM, WN, TM, TN, false, false>(g, s);
-  if (alo && !wlo) return launch_one<WM, WN, TM, TN, true, false>(g, s);
-  if (!alo && wlo) return launch_one<WM, WN, TM, TN, false, true>(g, s);
-  return launch_one<WM, WN, TM, TN, true, true>(g, s);
+  if (g.w_f32) {
+    return g.a_f32 ? launch_one<WM, WN, TM, TN, true, true, true>(g, s)
+                   : launch_one<WM, WN, TM, TN, true, true, false>(g, s);
+  }
+  return g.A_lo ? launch_one<WM, WN, TM, TN, true, false, false>(g, s)
+                : launch_one<WM, WN, TM, TN, false, false, false>(g, s);
+}
+
+// Whether gemm_f32_small takes the product: its 16-column tiles must not straddle a row segment.
+bool f32_small_ok(const GemmArgs& g) {
+  if (!g.w_f32 || g.M > 64 || g.K % 8) return false;
+  if (g.W2 && (g.N1 % 16 || g.N2 % 16)) return false;
+  return !g.nseg || g.seg_rows % 16 == 0;
+}
+hipError_t launch_f32_small(const GemmArgs& g, hipStream_t s) {
+  const dim3 grid((g.N + 15) / 16), nt(512);
+  auto go = [&](auto MT) {
+    constexpr int T = decltype(MT)::value;
+    if (g.a_f32) hipLaunchKernelGGL((gemm_f32_small<T, true>), grid, nt, 0, s, g);
+    else hipLaunchKernelGGL((gemm_f32_small<T, false>), grid, nt, 0, s, g);
+  };
+  if (g.M <= 16) go(Int<1>{});
+  else if (g.M <= 32) go(Int<2>{});
+  else go(Int<4>{});
+  return hipGetLastError();
 }
 
 __global__ void __launch_bounds__(256) pack_w_kernel(const bf16* __restrict__ W, int N, int K, _Float16* __restrict__ Wp) {
@@ -1553,6 +1687,8 @@ size_t gemm_scratch_elems(int M, int N, int K, bool a_lo, bool w_lo) {
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.defer) *g.defer = Parts(g.C);
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (g.w_f32 ? (!g.a_f32 && !g.A_lo) || g.w_packed || g.C_h16 : g.a_f32) return hipErrorInvalidValue;
+  if (f32_small_ok(g)) return launch_f32_small(g, s);
   if (g.f16 && !g.w_packed) return hipErrorInvalidValue;   // fp16 operands: the packed W only
   // products with the packed (fp16) W and fp16 outputs run on the weight-streaming path, in
   // launches of at most 128 rows
@@ -1579,7 +1715,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.W2 || g.nseg) {
     if (big_ok(g)) return launch_big(g, s);
     // one launch per segment, each writing its own column range of C
-    const bf16* ws[3] = {g.W_hi, g.W2, g.W3};
+    const bf16* ws[3] = {g.W, g.W2, g.W3};
     const int n0s[3] = {0, g.N1, g.N1 + g.N2}, ns[3] = {g.N1, g.N2, g.N - g.N1 - g.N2};
     for (int i = 0; i < (g.nseg ? g.nseg : 3); ++i) {
       const int n0 = g.nseg ? i * g.seg_rows : n0s[i];
@@ -1587,7 +1723,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
       h.defer = nullptr;
       h.W2 = h.W3 = nullptr;
       h.nseg = 0;
-      h.W_hi = g.nseg ? g.seg[i] : ws[i];
+      h.W = g.nseg ? g.seg[i] : ws[i];
       h.N = g.nseg ? g.seg_rows : ns[i];
       if (h.C) h.C += n0;
       if (h.C_hi) h.C_hi += n0;
@@ -1597,11 +1733,11 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     }
     return hipSuccess;
   }
-  SkPlan p = skinny_plan(g.M, g.N, g.K, g.A_lo != nullptr, g.W_lo != nullptr, device_cus());
+  SkPlan p = skinny_plan(g.M, g.N, g.K, g.A_lo != nullptr, g.w_f32, device_cus());
   if ((g.C && g.ldc % 4) || ((g.C_hi || g.C_h16) && g.ldch % 4) || (g.R && g.ldr % 4)) p.use = false;   // 16-byte stores
   if (g.C_h16 && (!p.use || g.W2)) return hipErrorInvalidValue;   // only the weight-streaming path writes fp16
   if (g.C_l16 && !g.C_h16) return hipErrorInvalidValue;
-  if (g.w_packed && (!p.use || g.N % 16 || g.K % BK || g.W_lo || g.R)) return hipErrorInvalidValue;   // packed W: no residual
+  if (g.w_packed && (!p.use || g.N % 16 || g.K % BK || g.R)) return hipErrorInvalidValue;   // packed W: no residual
   // packed W: one output, fp32 C or one fp16 plane (16-byte rows), not both, no bf16 planes
   if (g.w_packed && ((g.C != nullptr) == (g.C_h16 != nullptr) || g.C_hi || g.C_lo || g.C_l16 || (g.C_h16 && g.ldch % 8)))
     return hipErrorInvalidValue;

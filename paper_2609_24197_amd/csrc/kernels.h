@@ -20,10 +20,12 @@ struct Parts {
   Parts(const float* q) : p(q) {}
 };
 
-// C[M,N] = A[M,K] * W[N,K]^T (+ R), fp32 accumulate.  *_lo planes are optional.
+// C[M,N] = A[M,K] * W[N,K]^T (+ R), fp32 accumulate.  A as one bf16 plane or hi/lo planes, W bf16; or W
+// fp32 (w_f32, pointers cast), which is split into hi/lo planes on chip, with A as hi/lo planes or fp32 too (a_f32).
 struct GemmArgs {
   const bf16* A_hi = nullptr; const bf16* A_lo = nullptr; int lda = 0;
-  const bf16* W_hi = nullptr; const bf16* W_lo = nullptr; int ldw = 0;
+  const bf16* W = nullptr; int ldw = 0;
+  int a_f32 = 0, w_f32 = 0;    // A_hi; W, W2, W3 and seg[] point at fp32 elements
   int M = 0, N = 0, K = 0;
   float* C = nullptr; int ldc = 0;             // fp32 result (optional)
   const void* R = nullptr; int ldr = 0; int r_bf16 = 0;   // residual added (optional)
@@ -34,8 +36,8 @@ struct GemmArgs {
   float out_scale = 1.f;       // the product is multiplied by this (a power of two) before any output
   int f16 = 0;                 // A planes and the packed W hold fp16 values (packed W only)
   float* part = nullptr; size_t part_cap = 0;  // split-K scratch (fp32 elements), optional
-  int w_packed = 0;   // W_hi is in the fragment-major packed layout (launch_pack_w, fp16 W x 2^kPackScaleLog2)
-  // Optional row segments of W (bf16, not packed): rows [0, N1) come from W_hi, [N1, N1 + N2)
+  int w_packed = 0;   // W is in the fragment-major packed layout (launch_pack_w, fp16 W x 2^kPackScaleLog2)
+  // Optional row segments of W (not packed): rows [0, N1) come from W, [N1, N1 + N2)
   // from W2 and [N1 + N2, N) from W3, each with leading dimension ldw.
   const bf16* W2 = nullptr; const bf16* W3 = nullptr; int N1 = 0, N2 = 0;
   // Or nseg row segments of seg_rows rows each, segment i from seg[i] (N = nseg * seg_rows).
@@ -193,8 +195,15 @@ hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, cons
                                int B, int T, int Hq, int Hkv, int D, float eps, double theta,
                                bf16* q_hi, bf16* q_lo, bf16* k_hi, bf16* k_lo, bf16* v_hi, bf16* v_lo,
                                hipStream_t s, const AttnArgs* plan = nullptr, int plan_clear = 0);
-// fp32 -> bf16 hi/lo planes (lo optional).
-hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hipStream_t s);
+// fp32 -> bf16 hi/lo planes, several tensors in one launch.
+struct SplitArgs {
+  static constexpr int kMax = 5;
+  int n = 0;
+  const float* x[kMax] = {};
+  bf16 *hi[kMax] = {}, *lo[kMax] = {};
+  size_t len[kMax] = {};
+};
+hipError_t launch_split_planes(const SplitArgs& a, hipStream_t s);
 // SwiGLU: h = SiLU(gate) * up from rows [gate | up] (fp32, width 2 ff) -> bf16 planes [rows, ff].
 hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipStream_t s);
 // New K/V rows of n_layers drafter-side caches: rows of kv [B*n, n_layers * 2 * Hkv * D] hold k | v of each

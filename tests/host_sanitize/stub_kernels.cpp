@@ -144,22 +144,25 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t) {
   Scope s("launch_gemm");
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.lda < g.K || g.ldw < g.K) die("lda/ldw below K", nullptr, 0);
-  rd("A_hi", g.A_hi, strided(g.M, g.K, g.lda) * BF);
+  if (g.a_f32 && (!g.w_f32 || g.A_lo)) die("fp32 A with a bf16 W or a lo plane", g.A_hi, 0);
+  if (g.w_f32 && !g.a_f32 && !g.A_lo) die("fp32 W without hi/lo planes of A", g.A_hi, 0);
+  rd("A_hi", g.A_hi, strided(g.M, g.K, g.lda) * (g.a_f32 ? F : BF));
   rd_opt("A_lo", g.A_lo, strided(g.M, g.K, g.lda) * BF);
+  const size_t WB = g.w_f32 ? F : BF;
   if (g.w_packed) {
-    rd("W_hi (packed)", g.W_hi, (size_t)g.N * g.K * BF);
+    if (g.w_f32) die("a packed W is fp16", g.W, 0);
+    rd("W (packed)", g.W, (size_t)g.N * g.K * BF);
   } else if (g.nseg) {
     if (g.nseg < 0 || g.nseg > GemmArgs::kMaxSeg || (long long)g.nseg * g.seg_rows != g.N) die("W segments", nullptr, 0);
-    for (int i = 0; i < g.nseg; ++i) rd("W segment", g.seg[i], strided(g.seg_rows, g.K, g.ldw) * BF);
+    for (int i = 0; i < g.nseg; ++i) rd("W segment", g.seg[i], strided(g.seg_rows, g.K, g.ldw) * WB);
   } else if (g.W2) {
     const int n3 = g.N - g.N1 - g.N2;
     if (g.N1 <= 0 || g.N2 <= 0 || n3 < 0 || (n3 > 0) != (g.W3 != nullptr)) die("W segments", nullptr, 0);
-    rd("W_hi", g.W_hi, strided(g.N1, g.K, g.ldw) * BF);
-    rd("W2", g.W2, strided(g.N2, g.K, g.ldw) * BF);
-    if (n3) rd("W3", g.W3, strided(n3, g.K, g.ldw) * BF);
+    rd("W", g.W, strided(g.N1, g.K, g.ldw) * WB);
+    rd("W2", g.W2, strided(g.N2, g.K, g.ldw) * WB);
+    if (n3) rd("W3", g.W3, strided(n3, g.K, g.ldw) * WB);
   } else {
-    rd("W_hi", g.W_hi, strided(g.N, g.K, g.ldw) * BF);
-    rd_opt("W_lo", g.W_lo, strided(g.N, g.K, g.ldw) * BF);
+    rd("W", g.W, strided(g.N, g.K, g.ldw) * WB);
   }
   if (g.R) {
     if (g.ldr < g.N) die("ldr below N", g.R, 0);
@@ -180,7 +183,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t) {
     if (g.C_l16 && !g.C_h16) die("C_l16 without C_h16", g.C_l16, 0);
     wr_opt("C_l16", g.C_l16, strided(g.M, g.N, g.ldch) * sizeof(_Float16));
   }
-  const size_t need = gemm_scratch_elems(g.M, g.N, g.K, g.A_lo != nullptr, g.W_lo != nullptr);
+  const size_t need = gemm_scratch_elems(g.M, g.N, g.K, g.A_lo != nullptr, g.w_f32);
   if (need && g.part_cap >= need) wr("part", g.part, need * F);
   if (g.defer) {   // partial sums left for the next kernel wherever the scratch allows it
     *g.defer = Parts(g.C);
@@ -377,11 +380,14 @@ hipError_t launch_qk_norm_rope(Parts qkv, const float* qw, const float* kw, cons
   return hipSuccess;
 }
 
-hipError_t launch_split_planes(const float* x, size_t n, bf16* hi, bf16* lo, hipStream_t) {
+hipError_t launch_split_planes(const SplitArgs& a, hipStream_t) {
   Scope s("launch_split_planes");
-  rd("x", x, n * F);
-  wr("hi", hi, n * BF);
-  wr_opt("lo", lo, n * BF);
+  if (a.n < 0 || a.n > SplitArgs::kMax) die("tensors", nullptr, 0);
+  for (int i = 0; i < a.n; ++i) {
+    rd("x", a.x[i], a.len[i] * F);
+    wr("hi", a.hi[i], a.len[i] * BF);
+    wr_opt("lo", a.lo[i], a.len[i] * BF);
+  }
   return hipSuccess;
 }
 

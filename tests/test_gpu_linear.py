@@ -32,3 +32,26 @@ def test_streamed_product(M, N, K, residual):
     out.fill_(float("nan"))
     hspec.linear(hspec.BF16, A, W, out, ws, R=R)
     assert torch.equal(out, first)   # one order of sums
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 8), (3, 15, 40), (16, 16, 256), (17, 40, 264), (32, 272, 1000), (33, 33, 2048), (64, 1030, 520),
+    (65, 260, 72), (129, 130, 1000), (260, 300, 64),
+])
+def test_fp32_product(M, N, K):
+    """fp32 operands read in place, split into hi/lo planes on chip: each element keeps all but 2^-18 of itself,
+    the lo x lo term (2^-18) is left out, and 3 K terms are added in fp32."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    g = torch.Generator(device="cuda").manual_seed(M * 11 + N)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda")
+    R = torch.randn(M, N, generator=g, device="cuda")
+    guard = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = guard[:M * N].view(M, N)
+    ws = hspec.workspace(hspec.linear_workspace(hspec.F32, M, N, K))
+    ref = A.double() @ W.double().t().contiguous() + R.double()
+    mag = A.double().abs() @ W.double().abs().t().contiguous() + R.double().abs()
+    hspec.linear(hspec.F32, A, W, out, ws, R=R)
+    assert ((out.double() - ref).abs() <= (3 * 2.0 ** -18 + (3 * K + 1) * 2.0 ** -24) * mag).all()
+    assert guard[M * N:].isnan().all()
