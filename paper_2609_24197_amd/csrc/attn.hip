@@ -446,12 +446,12 @@ attn_sweep(AttnArgs a) {
 
 // Work list of the sweep (build_worklist) as a kernel of its own: the first kernel of an
 // attention call that has no earlier kernel to carry it.
-constexpr int PLAN_THREADS = 256;
 constexpr int PLAN_RANK_MAX = 4096;
 
-__global__ void __launch_bounds__(PLAN_THREADS) attn_plan(AttnArgs a, int clear_words) {
+__global__ void __launch_bounds__(WL_THREADS) attn_plan(AttnArgs a, int clear_words) {
   __shared__ WorklistLds<PLAN_RANK_MAX> lds;
-  build_worklist<PLAN_RANK_MAX>(a, clear_words, lds);
+  if (a.B <= PLAN_RANK_MAX) build_worklist<PLAN_RANK_MAX>(a, clear_words, lds);
+  else build_worklist_unranked(a, clear_words);
 }
 
 // Split reduction and block keys.  One workgroup per (request, KV head, 16 query columns);
@@ -828,7 +828,7 @@ int attention_sweep_grid(int D, int R, bool lo) {
 }
 
 hipError_t launch_attention_plan(const AttnArgs& a, int clear_words, hipStream_t s) {
-  hipLaunchKernelGGL(attn_plan, dim3(1), dim3(PLAN_THREADS), 0, s, a, clear_words);
+  hipLaunchKernelGGL(attn_plan, dim3(1), dim3(WL_THREADS), 0, s, a, clear_words);
   return hipGetLastError();
 }
 
