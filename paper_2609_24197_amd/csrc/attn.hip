@@ -93,6 +93,7 @@ constexpr float RESCALE_SLACK = 8.f;
 template <int D, int QB, int NW, int KT, int ST, bool LO>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HSPEC_SWEEP_WPE)))
 attn_sweep(AttnArgs a) {
+  touch_args<sizeof(AttnArgs)>();
   using C = Sweep<D, QB, NW, KT, ST, LO>;
   constexpr int NS = D / 32;             // d-steps of the QK^T contraction
   constexpr int NDB = D / 16;            // 16-wide d blocks of the output

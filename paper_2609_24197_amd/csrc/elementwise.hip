@@ -488,6 +488,7 @@ __global__ void __launch_bounds__(256) qk_norm_rope4_kernel(Parts qkv, const flo
                                                             int D, float eps, double log2_theta, bf16* q_hi,
                                                             bf16* q_lo, bf16* k_hi, bf16* k_lo, bf16* v_hi,
                                                             bf16* v_lo, AttnArgs plan, int plan_clear) {
+  touch_args<128 + (PLAN ? sizeof(AttnArgs) : 0)>();
   if constexpr (PLAN) {   // the first workgroup (dispatched first) builds the KV sweep's work list
     __shared__ WorklistLds<kWorklistFusedMax> wl;
     if (blockIdx.x == 0) {

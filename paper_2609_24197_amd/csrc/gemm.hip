@@ -259,6 +259,7 @@ __device__ __forceinline__ const bf16* w_segment(const GemmArgs& g, int n0, int&
 // 64 x 24576 x 4096 345 -> 225 (there bound by A, read from L2 once per 16 columns).
 template <int MT, bool AF>
 __global__ void __launch_bounds__(512) gemm_f32_small(GemmArgs g) {
+  touch_args<sizeof(GemmArgs)>();
   __shared__ f32x4 red[8][MT][64];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -936,6 +937,7 @@ struct StreamCfg {
 
 template <int BMV, int NP, int ST>
 __global__ void __launch_bounds__(SG_NT) gemm_stream_kernel(GemmArgs g, StreamPlan p) {
+  touch_args<sizeof(GemmArgs) + sizeof(StreamPlan)>();
   using C = StreamCfg<BMV, NP, ST>;
   constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN;
   __shared__ __align__(16) bf16 s0[C::STAGE], s1[C::STAGE];
@@ -1250,6 +1252,7 @@ struct BigPlan {
 
 template <bool ALO, int TMV>
 __global__ void __launch_bounds__(GB_NT) gemm_big_kernel(GemmArgs g, BigPlan p) {
+  touch_args<sizeof(GemmArgs) + sizeof(BigPlan)>();
   using C = BigCfg<ALO, TMV>;
   constexpr int TM = C::TM, TN = C::TN, BM = C::BM, BN = C::BN;
   constexpr int PA = C::SA * (ALO ? 2 : 1);
