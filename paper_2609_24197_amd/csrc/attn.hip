@@ -470,15 +470,22 @@ constexpr int RED_THREADS = 256;
 // few workgroups per CU anyway and takes 8.
 constexpr int RED_NS = 4, RED_NM = 8, RED_NS_MANY = 8;
 
-__device__ __forceinline__ f32x4 ld4_planes(const bf16* hi, const bf16* lo, size_t off) {
-  const bf16x4 hv = *reinterpret_cast<const bf16x4*>(hi + off);
-  f32x4 v = {bf2f(hv[0]), bf2f(hv[1]), bf2f(hv[2]), bf2f(hv[3])};
-  if (lo) {
-    const bf16x4 lv = *reinterpret_cast<const bf16x4*>(lo + off);
-    v += f32x4{bf2f(lv[0]), bf2f(lv[1]), bf2f(lv[2]), bf2f(lv[3])};
+// Four elements as planes on their way, and their fp32 values (lo may be null).
+struct Planes4 {
+  bf16x4 hi, lo;
+  __device__ __forceinline__ void load(const bf16* h, const bf16* l, size_t off) {
+    hi = *reinterpret_cast<const bf16x4*>(h + off);
+    if (l) lo = *reinterpret_cast<const bf16x4*>(l + off);
   }
-  return v;
-}
+  __device__ __forceinline__ f32x4 sum(const bf16* l) const {
+    f32x4 v = {bf2f(hi[0]), bf2f(hi[1]), bf2f(hi[2]), bf2f(hi[3])};
+    if (l) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += bf2f(lo[i]);
+    }
+    return v;
+  }
+};
 
 
 // Split reduction when the sweep took the block keys: one thread per (column, 4 dims), PER of
@@ -609,8 +616,27 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   const int nb = a.causal ? j + 1 : T;   // block keys this column sees
   const int d0 = ln * DPL;
 
-  // the splits' running maxima, sums and partial outputs for this lane's dims (all loads in
-  // flight together when there are at most NS splits), issued before the block keys
+  // q of the workgroup's columns (the last column repeated past R) and the first chunk of block keys, then
+  // the splits' running maxima, sums and partial outputs for this lane's dims (in flight together with
+  // them when there are at most NS splits): two round trips to memory, the second behind nsplit.
+  // 8 requests x 8 KV heads, 8 splits: 13.0 -> 10.7 us.
+  constexpr int QN = RED_COLS * P4 / RED_THREADS, KN = KC * P4 / RED_THREADS;   // 4-element pieces per thread
+  Planes4 qx[QN], kx[KN], vx[KN];
+#pragma unroll
+  for (int i = 0; i < QN; ++i) {
+    const int p = tid + i * RED_THREADS, cr = min(c0 + p / P4, R - 1);
+    qx[i].load(a.q_hi, a.q_lo, ((size_t)(b * T + cr / g) * a.Hq + h * g + cr % g) * D + (p % P4) * 4);
+  }
+  auto load_kv = [&](int s0) {
+#pragma unroll
+    for (int i = 0; i < KN; ++i) {
+      const int p = tid + i * RED_THREADS;
+      const size_t off = ((size_t)(b * T + min(s0 + p / P4, T - 1)) * a.Hkv + h) * D + (p % P4) * 4;
+      kx[i].load(a.kb_hi, a.kb_lo, off);
+      vx[i].load(a.vb_hi, a.vb_lo, off);
+    }
+  };
+  load_kv(0);
   float m[NS], l[NS];
   f32x4 o[NS][DPL / 4];
   auto fetch = [&](int s0) {
@@ -627,12 +653,10 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   };
   if (nsplit <= NS) fetch(0);
 
-  // q of the workgroup's columns (the last column repeated past R)
-  for (int p = tid; p < RED_COLS * P4; p += RED_THREADS) {
-    const int r = p / P4, d4 = (p % P4) * 4;
-    const int cr = min(c0 + r, R - 1);
-    const size_t qoff = ((size_t)(b * T + cr / g) * a.Hq + h * g + cr % g) * D + d4;
-    *reinterpret_cast<f32x4*>(sQ + r * DP + d4) = ld4_planes(a.q_hi, a.q_lo, qoff);
+#pragma unroll
+  for (int i = 0; i < QN; ++i) {
+    const int p = tid + i * RED_THREADS;
+    *reinterpret_cast<f32x4*>(sQ + p / P4 * DP + (p % P4) * 4) = qx[i].sum(a.q_lo);
   }
   float mb = -INFINITY, lb = 0.f;
   f32x4 ob[DPL / 4];
@@ -640,11 +664,12 @@ __global__ void __launch_bounds__(RED_THREADS) attn_reduce(AttnArgs a) {
   for (int e = 0; e < DPL / 4; ++e) ob[e] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < T; s0 += KC) {
     __syncthreads();   // q staged; the previous chunk's tiles are no longer read
-    for (int p = tid; p < KC * P4; p += RED_THREADS) {
-      const int r = p / P4, d4 = (p % P4) * 4;
-      const size_t koff = ((size_t)(b * T + min(s0 + r, T - 1)) * a.Hkv + h) * D + d4;
-      *reinterpret_cast<f32x4*>(sK + r * DP + d4) = ld4_planes(a.kb_hi, a.kb_lo, koff);
-      *reinterpret_cast<f32x4*>(sV + r * DP + d4) = ld4_planes(a.vb_hi, a.vb_lo, koff);
+    if (s0) load_kv(s0);
+#pragma unroll
+    for (int i = 0; i < KN; ++i) {
+      const int p = tid + i * RED_THREADS, o4 = p / P4 * DP + (p % P4) * 4;
+      *reinterpret_cast<f32x4*>(sK + o4) = kx[i].sum(a.kb_lo);
+      *reinterpret_cast<f32x4*>(sV + o4) = vx[i].sum(a.vb_lo);
     }
     __syncthreads();
     float sc = 0.f;
