@@ -1,10 +1,16 @@
 // bf16 MFMA GEMM for the drafting step's projections:  C[M,N] = A[M,K] * W[N,K]^T (+ R).
 //
-// Both operands are K-contiguous (PyTorch Linear layout W[out, in]).  An operand may carry
-// a second bf16 plane holding the rounding residual of an fp32 value (x = hi + lo); the
-// products hi*hi + lo*hi + hi*lo then reproduce fp32 operands to ~2^-16 relative.
+// Both operands are K-contiguous (PyTorch Linear layout W[out, in]).  A may carry
+// a second bf16 plane holding the rounding residual of an fp32 value (x = hi + lo), and fp32 operands are
+// split into such planes on chip; the products hi*hi + lo*hi + hi*lo then reproduce fp32 operands to
+// ~2^-16 relative.
 //
-// Tiling: 4 waves per workgroup in a WM x WN grid, each wave owns TM x TN blocks of 32x32
+// Paths (launch_gemm): bf16 W, K in whole 64-wide tiles, up to 128 rows or one round of 128 x 128
+// tiles: gemm_stream_kernel; more than that, K % 32 == 0: gemm_big_kernel; the packed W, and bf16 W of up to 128
+// rows that the streamed path does not take: skinny_kernel; fp32 W of up to 64 rows: gemm_f32_small; the
+// rest: gemm_kernel, described next.
+//
+// gemm_kernel: 4 waves per workgroup in a WM x WN grid, each wave owns TM x TN blocks of 32x32
 // computed with v_mfma_f32_32x32x16_bf16.  K is consumed in 64-wide tiles staged through
 // LDS (16-byte chunks, XOR-swizzled by row so the per-lane fragment reads of 32 rows spread
 // over all banks); the next tile's global loads are issued before the current tile is
@@ -12,7 +18,7 @@
 // weight tile land on the same XCD (its own L2), and every weight byte is fetched from
 // HBM once.
 //
-// Few rows (M <= 64, e.g. the state projection of one step's B requests) make the product a
+// skinny_kernel.  Few rows (M <= 64, e.g. the state projection of one step's B requests) make the product a
 // stream over W: each weight byte feeds at most 64 rows, far below the MFMA/HBM balance
 // point, so that path skips LDS for W.  Every lane loads its 16-byte B fragment of
 // v_mfma_f32_16x16x32_bf16 straight from HBM (buffer loads whose range check zero-fills rows

@@ -14,8 +14,8 @@
 // fragments (as bf16 hi/lo planes, or as one fp16 plane multiplied with C rounded to fp16 on
 // v_mfma_f32_16x16x32_f16); with the fp16 plane and heads in groups of 4 that share B and C
 // (the drafting step), ssd_scan_grp runs those 4 heads in one workgroup, one wave each, and
-// shares the C and C B^T work through LDS; otherwise (ssd_scan_kernel) the fp32 state lives
-// in LDS between chunks.
+// shares the C and C B^T work through LDS; otherwise (ssd_scan_state) the fp32 state stays in the
+// accumulators of its own update from S0 to S_final.
 #include "common.h"
 #include "kernels.h"
 
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LO ? 1
 }
 
 // The block in one chunk and no final state (every drafting step): the same arithmetic as
-// ssd_scan_kernel<N, false>, with every global load of the wave (dt, the x tile, the B and C
+// ssd_scan_state, with every global load of the wave (dt, the x tile, the B and C
 // fragments, all initial-state fragments) issued before the first is used, so that a wave
 // waits for memory once instead of once per state fragment.
 template <int N, bool H16>
