@@ -810,12 +810,38 @@ HSPEC_API hspec_status hspec_gather_slots(int B, int max_pages, int page_size, i
   return HSPEC_OK;
 }
 
+// fp32 storage: room for both operands, for calls whose C lies over one of them (see operand_for).
+struct LinearPlan {
+  int* status = nullptr;
+  float *A = nullptr, *W = nullptr;
+  GemmScratch gs;
+};
+void plan_linear(Arena& ar, hspec_dtype dtype, int M, int N, int K, LinearPlan& p) {
+  p.status = status_word(ar);
+  if (M <= 0 || N <= 0 || K <= 0) return;
+  if (is_f32(dtype)) {
+    p.A = ar.take<float>((size_t)M * K);
+    p.W = ar.take<float>((size_t)N * K);
+  }
+  p.gs = reserve_gemm(ar, dtype, {{M, N, K}});
+}
+
+// The product reads fp32 operands in place while it writes C: an operand that shares memory with C
+// is read from a copy in the workspace (K == N and C in place of A, say).
+hipError_t operand_for(const void* x, size_t n, hspec_dtype dtype, const float* C, size_t c_n, float* copy,
+                       const void*& out, hipStream_t st) {
+  out = x;
+  if (!is_f32(dtype)) return hipSuccess;
+  const uintptr_t x0 = (uintptr_t)x, c0 = (uintptr_t)C;
+  if (x0 >= c0 + 4 * c_n || c0 >= x0 + 4 * n) return hipSuccess;
+  out = copy;
+  return hspec::launch_copy_f32(static_cast<const float*>(x), n, copy, st);
+}
+
 HSPEC_API size_t hspec_linear_workspace(hspec_dtype dtype, int M, int N, int K) {
   Arena ar;
-  status_word(ar);
-  if (M > 0 && N > 0 && K > 0) {
-    reserve_gemm(ar, dtype, {{M, N, K}});
-  }
+  LinearPlan p;
+  plan_linear(ar, dtype, M, N, K, p);
   return ar.size();
 }
 
@@ -829,15 +855,17 @@ HSPEC_API hspec_status hspec_linear(hspec_dtype dtype, int M, int N, int K, cons
   if (hspec_status s = check_ws(workspace, ws_bytes, hspec_linear_workspace(dtype, M, N, K))) return s;
   hipStream_t st = (hipStream_t)stream;
   Arena ar{(char*)workspace};
-  int* status = status_word(ar);
-  const GemmScratch gs = reserve_gemm(ar, dtype, {{M, N, K}});
-  HIP_TRY(hspec::launch_zero_words(status, hspec::kStatusClear, st));
+  LinearPlan p;
+  plan_linear(ar, dtype, M, N, K, p);
+  HIP_TRY(hspec::launch_zero_words(p.status, hspec::kStatusClear, st));
+  HIP_TRY(operand_for(A, (size_t)M * K, dtype, C, (size_t)M * N, p.A, A, st));
+  HIP_TRY(operand_for(W, (size_t)N * K, dtype, C, (size_t)M * N, p.W, W, st));
   hspec::GemmArgs g;
   set_a(g, in_place(A, dtype), K);
   set_w(g, W, dtype, K);
   g.M = M; g.N = N; g.K = K;
   g.C = C; g.ldc = N; g.R = R; g.ldr = N; g.r_bf16 = 0;
-  use_scratch(g, gs);
+  use_scratch(g, p.gs);
   HIP_TRY(hspec::launch_gemm(g, st));
   return HSPEC_OK;
 }

@@ -741,6 +741,10 @@ __global__ void zero_kernel(int* p, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
+__global__ void __launch_bounds__(256) copy_kernel(const float* x, size_t n, float* y) {
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) y[i] = x[i];
+}
+
 }  // namespace
 
 namespace {
@@ -886,6 +890,13 @@ hipError_t launch_kv_append(const AppendArgs& a, hipStream_t s) {
 
 hipError_t launch_zero_words(int* p, int n, hipStream_t s) {
   hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s, p, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_f32(const float* x, size_t n, float* y, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  const size_t blocks = (n + 255) / 256;
+  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, x, n, y);
   return hipGetLastError();
 }
 

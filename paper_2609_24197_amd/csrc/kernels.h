@@ -229,6 +229,8 @@ struct AppendArgs {
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t s);
 // Zero n int32 words (device status, counters) with a kernel, graph-capture safe.
 hipError_t launch_zero_words(int* p, int n, hipStream_t s);
+// y[0, n) = x[0, n), any 4-byte alignment.
+hipError_t launch_copy_f32(const float* x, size_t n, float* y, hipStream_t s);
 
 // Markov correction and token choice of the draft head (one launch per block position; one for
 // all of them when the tokens are forced).

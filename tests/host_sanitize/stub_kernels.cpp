@@ -421,6 +421,13 @@ hipError_t launch_zero_words(int* p, int n, hipStream_t) {
   return hipSuccess;
 }
 
+hipError_t launch_copy_f32(const float* x, size_t n, float* y, hipStream_t) {
+  Scope s("launch_copy_f32");
+  rd("x", x, n * F);
+  wr("y", y, n * F);
+  return hipSuccess;
+}
+
 hipError_t launch_head_norm(const HeadArgs& a, int status_words, const float* x, const float* w, int n, float,
                             bf16* out, hipStream_t) {
   Scope s("launch_head_norm");

@@ -55,3 +55,21 @@ def test_fp32_product(M, N, K):
     hspec.linear(hspec.F32, A, W, out, ws, R=R)
     assert ((out.double() - ref).abs() <= (3 * 2.0 ** -18 + (3 * K + 1) * 2.0 ** -24) * mag).all()
     assert guard[M * N:].isnan().all()
+
+
+@pytest.mark.parametrize("M,K", [(5, 40), (64, 64), (100, 128), (300, 264)])
+@pytest.mark.parametrize("over", ["A", "W"])
+def test_fp32_product_over_an_operand(M, K, over):
+    """C in the memory of A (N == K) or of W (M == N == K): the result of the call with a C of its own."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    N = K
+    M = M if over == "A" else K
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda")
+    ws = hspec.workspace(hspec.linear_workspace(hspec.F32, M, N, K))
+    ref = torch.empty(M, N, device="cuda")
+    hspec.linear(hspec.F32, A, W, ref, ws)
+    hspec.linear(hspec.F32, A, W, A if over == "A" else W, ws)
+    assert torch.equal(A if over == "A" else W, ref)
