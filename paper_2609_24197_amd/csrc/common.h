@@ -104,25 +104,28 @@ __device__ __forceinline__ void wg_barrier() {
 }
 
 // NV pieces of 4 elements (16-byte aligned, from element i[e]) of a matrix given as np planes,
-// added in plane order.  Every load of UP planes is issued before the first is added.
+// added in plane order.  Every load of UP planes is issued before the first is added.  UP = 0: one plane
+// (np = 1), without the registers of the others.
 template <int NV, int UP = 2>
 __device__ __forceinline__ void ld4_parts(const float* p, int np, size_t plane, const size_t (&i)[NV], f32x4 (&v)[NV]) {
 #pragma unroll
   for (int e = 0; e < NV; ++e) v[e] = *reinterpret_cast<const f32x4*>(p + i[e]);
-  for (int k = 1; k < np; k += UP) {
-    f32x4 t[UP][NV];
+  if constexpr (UP > 0) {
+    for (int k = 1; k < np; k += UP) {
+      f32x4 t[UP][NV];
 #pragma unroll
-    for (int u = 0; u < UP; ++u) {
-      const float* q = p + (size_t)min(k + u, np - 1) * plane;
+      for (int u = 0; u < UP; ++u) {
+        const float* q = p + (size_t)min(k + u, np - 1) * plane;
 #pragma unroll
-      for (int e = 0; e < NV; ++e) t[u][e] = *reinterpret_cast<const f32x4*>(q + i[e]);
-    }
-#pragma unroll
-    for (int u = 0; u < UP; ++u)
-      if (k + u < np) {
-#pragma unroll
-        for (int e = 0; e < NV; ++e) v[e] += t[u][e];
+        for (int e = 0; e < NV; ++e) t[u][e] = *reinterpret_cast<const f32x4*>(q + i[e]);
       }
+#pragma unroll
+      for (int u = 0; u < UP; ++u)
+        if (k + u < np) {
+#pragma unroll
+          for (int e = 0; e < NV; ++e) v[e] += t[u][e];
+        }
+    }
   }
 }
 __device__ __forceinline__ float ld1_parts(const float* p, int np, size_t plane, size_t i) {
