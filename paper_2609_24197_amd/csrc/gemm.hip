@@ -1754,7 +1754,8 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.w_packed && ((g.C != nullptr) == (g.C_h16 != nullptr) || g.C_hi || g.C_lo || g.C_l16 || (g.C_h16 && g.ldch % 8)))
     return hipErrorInvalidValue;
   if (p.use) {
-    if (p.ksplit > 1 && (!g.part || g.part_cap < (size_t)p.ksplit * g.M * g.N)) {
+    // unsplit: no room for the planes, or the packed W, whose kernel writes its one output and no planes
+    if (p.ksplit > 1 && (g.w_packed || !g.part || g.part_cap < (size_t)p.ksplit * g.M * g.N)) {
       p.ksplit = 1;
       p.kper = ((g.K + SK_KC - 1) / SK_KC) * SK_KC;
     }

@@ -126,6 +126,34 @@ def test_draft_step_packed(name):
     assert_close(out, O.draft_step(W, x, cfg), "out")
 
 
+@pytest.mark.parametrize("B,H,N,dm,precise", [
+    (3, 8, 16, 512, False), (2, 4, 32, 1024, False), (20, 4, 16, 512, True), (70, 4, 64, 512, True), (130, 8, 16, 512, False),
+])
+def test_packed_state_of_few_columns(B, H, N, dm, precise):
+    """Packed W_dS of fewer 128-column tiles than the chip has CUs (d_S = H P N < 32768) over several k-chunks: the
+    fp16 S0 that the scan reads, and the fp32 S0 of state_init, in a workspace full of NaN."""
+    import torch
+    cfg = I.StepConfig(name="s", B=B, k=4, d_model=dm, H=H, P=64, N=N, G=1, chunk=16, Hq=4, Hkv=1, D=64,
+                       lengths="fixed:20", precise_io=precise)
+    W, Wd = _weights(cfg, 8)
+    x = I.make_inputs(cfg, seed=8)
+    Wd["W_dS_packed"] = hspec.pack_w_ds(Wd.pop("W_dS"), cfg.d_S, cfg.rank)
+    d = dev(dict(h_last=x["h_last"], u=x["block_emb"]))
+    ws = hspec.workspace(hspec.mamba_block_scan_workspace(cfg))
+    ws.view(torch.uint8).fill_(255)
+    out, Sf = empty((cfg.B, cfg.k, cfg.d_model)), empty((cfg.B, cfg.H, cfg.P, cfg.N))
+    hspec.mamba_block_scan(cfg, Wd, d["h_last"], d["u"], out, ws, S_final=Sf)
+    S0, _ = O.state_init(x["h_last"], W["W_r"], W["W_dS"], cfg.H, cfg.P, cfg.N)
+    ref, parts = O.mamba_mixer(O.f64(x["block_emb"]), S0, W, cfg, return_parts=True)
+    assert_close(host(out), ref, "out")
+    assert_close(host(Sf), parts["S_final"], "S_final")
+    ws = hspec.workspace(hspec.state_init_workspace(cfg))
+    ws.view(torch.uint8).fill_(255)
+    got = empty((cfg.B, cfg.H, cfg.P, cfg.N))
+    hspec.state_init(cfg, Wd, d["h_last"], got, ws)
+    assert_close(host(got), S0, "S0")
+
+
 def test_draft_step_zero_inputs():
     """e = 0 and h_last = 0: out = W_o mean(V over cache and block) per query head."""
     cfg = SMALL["small_bf16"]
