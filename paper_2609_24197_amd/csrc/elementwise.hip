@@ -656,8 +656,9 @@ template <typename T>
 __global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log2_theta) {
   __shared__ float s_cs[256], s_sn[256];
   const int tok = blockIdx.x, b = tok / a.n, i = tok % a.n;
-  const int L = a.ctx_lens[b], pos = L + i, pg = pos / a.ps;
-  if (L < 0 || pg >= a.max_pages) {
+  const int L = a.ctx_lens[b];
+  const unsigned pos = (unsigned)L + i, pg = pos / (unsigned)a.ps;   // (no sum that wraps below zero at lengths near 2^31)
+  if (L < 0 || pg >= (unsigned)a.max_pages) {
     if (threadIdx.x == 0 && a.status) atomicOr(a.status, 2);
     return;
   }
@@ -667,7 +668,7 @@ __global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log
     return;
   }
   const int D = a.D, half = D / 2, lph = D / 8, hpp = 256 / lph;   // heads per pass
-  const size_t dst0 = ((size_t)pid * a.ps + pos % a.ps) * a.Hkv * D;
+  const size_t dst0 = ((size_t)pid * a.ps + pos % (unsigned)a.ps) * a.Hkv * D;
   for (int p = threadIdx.x; p < half; p += 256) {
     double phi = (double)pos * exp2(-2.0 * (double)p / (double)D * log2_theta);
     const double two_pi = 6.283185307179586476925286766559;

@@ -63,3 +63,21 @@ def test_inject_flags_and_skips():
     for l in range(2):
         changed = (host(dc[l]["k_cache"]).reshape(80, -1) != caches[l]["k_cache"].reshape(80, -1)).any(1)
         assert set(np.nonzero(changed)[0]) == written
+
+
+@pytest.mark.parametrize("length", [2**31 - 1, 2**31 - 3, 32, 29, -1, -2**31])
+def test_inject_length_past_the_table(length):
+    """A length whose new positions lie past a table of 32 positions, up to the largest int32 (where length + i has no
+    int32): flagged, and only the mapped positions written."""
+    cfg = I.StepConfig(name="i", B=1, k=4, d_model=64, H=2, P=64, N=16, G=1, chunk=16, Hq=1, Hkv=1, D=64, lengths="list:3")
+    pt, pages = np.array([[2, 1]], np.int32), 3
+    W = I.make_inject_weights(cfg, 2, 1)
+    cache = dict(k_cache=I.normal("k", (pages, 16, 1, 64), 1.0, 2, "bf16"), v_cache=I.normal("v", (pages, 16, 1, 64), 1.0, 2, "bf16"))
+    d = dict(W_fc=hspec.to_device(W["W_fc"]), layers=[dev(w) for w in W["layers"]])
+    dc = dev(cache)
+    ws = hspec.workspace(hspec.kv_inject_workspace(cfg, 2, pages))
+    h = I.normal("h", (1, 4, cfg.d_h), 1.0, 2, "bf16")
+    hspec.kv_inject(cfg, d, hspec.to_device(h), [dc], hspec.to_device(pt), hspec.to_device(np.array([length], np.int32)), ws)
+    assert hspec.read_status(ws) == hspec.DEV_BAD_CTX_LEN
+    changed = (host(dc["k_cache"]).reshape(48, -1) != cache["k_cache"].reshape(48, -1)).any(1)
+    assert set(np.nonzero(changed)[0]) == ({16 + 13, 16 + 14, 16 + 15} if length == 29 else set())
