@@ -1077,6 +1077,17 @@ void plan_inject(Arena& ar, const hspec_attn_cfg& c, int d_h, InjectPlan& p) {
   if (p.gs.cap) p.gs.p = ar.take<float>(p.gs.cap);
 }
 
+// Whether no two of the layers' caches share memory.
+bool caches_apart(const hspec_attn_cfg& c, int n, void* const* k, void* const* v) {
+  const uintptr_t bytes = (uintptr_t)c.num_pages * c.page_size * c.Hkv * c.D * (is_f32(c.dtype) ? 4 : 2);
+  for (int i = 0; i < 2 * n; ++i)
+    for (int j = 0; j < i; ++j) {
+      const uintptr_t x = (uintptr_t)(i % 2 ? v : k)[i / 2], y = (uintptr_t)(j % 2 ? v : k)[j / 2];
+      if (x < y + bytes && y < x + bytes) return false;
+    }
+  return true;
+}
+
 HSPEC_API size_t hspec_kv_inject_workspace(const hspec_attn_cfg* cfg, int d_h) {
   if (!cfg || d_h <= 0 || cfg->B <= 0 || cfg->k <= 0) return 0;
   Arena ar;
@@ -1142,7 +1153,13 @@ HSPEC_API hspec_status hspec_kv_inject(const hspec_attn_cfg* cfg, int d_h, int n
     a.B = c.B; a.n = c.k; a.Hkv = c.Hkv; a.D = c.D; a.eps = c.eps; a.rope_theta = c.rope_theta;
     a.page_table = page_table; a.max_pages = c.max_pages; a.num_pages = c.num_pages; a.ps = c.page_size;
     a.ctx_lens = ctx_lens; a.status = p.status;
-    HIP_TRY(hspec::launch_kv_append(a, st));
+    // the group's caches at once, or one after the other (k, then v of each layer) where two share memory
+    const bool apart = caches_apart(c, nl, k_cache + l0, v_cache + l0);
+    const int heads = nl * 2 * c.Hkv, step = apart ? heads : c.Hkv;
+    for (a.head0 = 0; a.head0 < heads; a.head0 += step) {
+      a.head1 = a.head0 + step;
+      HIP_TRY(hspec::launch_kv_append(a, st));
+    }
   }
   return HSPEC_OK;
 }

@@ -687,13 +687,13 @@ __global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log
     sn[e] = s_sn[i0 + e];
   }
   constexpr int U = 4;
-  for (int h0 = 0; h0 < nh; h0 += U * hpp) {
+  for (int h0 = a.head0; h0 < a.head1; h0 += U * hpp) {
     size_t at[2 * U];
     f32x4 x[2 * U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int head = h0 + u * hpp + threadIdx.x / lph;
-      at[2 * u] = ((size_t)tok * nh + (head < nh ? head : 0)) * D + i0;
+      at[2 * u] = ((size_t)tok * nh + (head < a.head1 ? head : a.head0)) * D + i0;
       at[2 * u + 1] = at[2 * u] + half;
     }
     ld4_parts<2 * U, 2>(a.kv.p, a.kv.np, a.kv.plane, at, x);
@@ -706,7 +706,7 @@ __global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log
 #pragma unroll
       for (int e = 0; e < 4; ++e) ss += x1[e] * x1[e] + x2[e] * x2[e];
       for (int off = lph / 2; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-      if (head >= nh) continue;
+      if (head >= a.head1) continue;
       const int l = head / (2 * a.Hkv), hh = head % (2 * a.Hkv);
       const float* kw = a.kw[0];
       void* dst = hh < a.Hkv ? a.k_cache[0] : a.v_cache[0];
@@ -897,6 +897,7 @@ hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipSt
 
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t s) {
   if (a.B * a.n <= 0 || a.n_layers <= 0) return hipSuccess;
+  if (a.head0 < 0 || a.head1 <= a.head0 || a.head1 > a.n_layers * 2 * a.Hkv) return hipErrorInvalidValue;
   if (a.D < 8 || a.D % 8 || a.D > 512 || 64 % (a.D / 8) || a.n_layers > AppendArgs::kMaxLayers) return hipErrorInvalidValue;
   if (a.cache_bf16) hipLaunchKernelGGL(kv_append_kernel<bf16>, dim3(a.B * a.n), dim3(256), 0, s, a, log2(a.rope_theta));
   else hipLaunchKernelGGL(kv_append_kernel<float>, dim3(a.B * a.n), dim3(256), 0, s, a, log2(a.rope_theta));

@@ -209,11 +209,13 @@ hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipSt
 // New K/V rows of n_layers drafter-side caches: rows of kv [B*n, n_layers * 2 * Hkv * D] hold k | v of each
 // layer; k gets its per-head RMSNorm (kw[l], [D]) and RoPE at position ctx_len + i, and both are written at
 // slot(ctx_len + i) of that layer's paged cache (bf16 or fp32 storage); unmapped positions set status bit
-// 2, bad page ids bit 1.
+// 2, bad page ids bit 1.  Heads are counted over the row (k, then v of each layer); only [head0, head1) are
+// written, in no order, so caches that share memory take a launch each.
 struct AppendArgs {
   static constexpr int kMaxLayers = GemmArgs::kMaxSeg / 2;
   Parts kv;
   int n_layers = 0;
+  int head0 = 0, head1 = 0;
   const float* kw[kMaxLayers] = {};
   void* k_cache[kMaxLayers] = {};
   void* v_cache[kMaxLayers] = {};

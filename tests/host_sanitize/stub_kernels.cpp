@@ -402,6 +402,7 @@ hipError_t launch_silu_mul(Parts gu, int rows, int ff, bf16* hi, bf16* lo, hipSt
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t) {
   Scope s("launch_kv_append");
   if (a.n_layers < 1 || a.n_layers > AppendArgs::kMaxLayers) die("layers", nullptr, 0);
+  if (a.head0 < 0 || a.head1 <= a.head0 || a.head1 > a.n_layers * 2 * a.Hkv) die("heads", nullptr, 0);
   const size_t row = (size_t)a.Hkv * a.D, cache = (size_t)a.num_pages * a.ps * row * (a.cache_bf16 ? BF : F);
   rd_parts("kv", a.kv, (size_t)a.B * a.n * a.n_layers * 2 * row);
   rd("page_table", a.page_table, (size_t)a.B * a.max_pages * I);

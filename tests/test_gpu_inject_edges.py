@@ -81,3 +81,45 @@ def test_inject_length_past_the_table(length):
     assert hspec.read_status(ws) == hspec.DEV_BAD_CTX_LEN
     changed = (host(dc["k_cache"]).reshape(48, -1) != cache["k_cache"].reshape(48, -1)).any(1)
     assert set(np.nonzero(changed)[0]) == ({16 + 13, 16 + 14, 16 + 15} if length == 29 else set())
+
+
+@pytest.mark.parametrize("share", ["layers", "k_and_v", "interleaved"])
+@pytest.mark.parametrize("layers,Hkv,D", [(2, 1, 64), (3, 3, 64), (8, 2, 128), (9, 5, 128)])
+def test_inject_caches_that_share_memory(share, layers, Hkv, D):
+    """Caches that share memory are written in the order of the layers, k before v: one cache for all layers keeps the
+    last layer's rows, one tensor for k and v keeps v, and pools that overlap without a common slot keep all."""
+    import torch
+    B, k = 3, 5
+    cfg = I.StepConfig(name="i", B=B, k=k, d_model=64, H=2, P=64, N=16, G=1, chunk=16, Hq=Hkv, Hkv=Hkv, D=D,
+                       lengths="list:3,14,30")
+    L = I.make_lengths(cfg, 1)
+    pt, pages = I.make_page_table(cfg, L + k, 1)
+    W = I.make_inject_weights(cfg, 3, layers)
+    d = dict(W_fc=hspec.to_device(W["W_fc"]), layers=[dev(w) for w in W["layers"]])
+    h = hspec.to_device(I.normal("h", (B, k, cfg.d_h), 1.0, 3, "bf16"))
+    lens = hspec.to_device(L)
+
+    def inject(caches, table, npages):
+        ws = hspec.workspace(hspec.kv_inject_workspace(cfg, table.shape[1], npages))
+        hspec.kv_inject(cfg, d, h, caches, hspec.to_device(table), lens, ws)
+        assert hspec.read_status(ws) == 0
+
+    zeros = lambda n: torch.zeros(n, 16, Hkv, D, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    own = [dict(k_cache=zeros(pages), v_cache=zeros(pages)) for _ in range(layers)]
+    inject(own, pt, pages)
+    if share == "layers":
+        one = dict(k_cache=zeros(pages), v_cache=zeros(pages))
+        inject([one] * layers, pt, pages)
+        assert torch.equal(one["k_cache"], own[-1]["k_cache"]) and torch.equal(one["v_cache"], own[-1]["v_cache"])
+    elif share == "k_and_v":
+        ts = [zeros(pages) for _ in range(layers)]
+        inject([dict(k_cache=t, v_cache=t) for t in ts], pt, pages)
+        assert all(torch.equal(t, c["v_cache"]) for t, c in zip(ts, own))
+    else:                       # page p of cache i is page p * n + i of one pool (the tail keeps the ranges inside it)
+        n = 2 * layers
+        pool = zeros(2 * pages * n)
+        view = [pool[i:i + pages * n] for i in range(n)]
+        inject([dict(k_cache=view[2 * l], v_cache=view[2 * l + 1]) for l in range(layers)], pt * n, pages * n)
+        for l in range(layers):
+            assert torch.equal(pool[2 * l:pages * n:n], own[l]["k_cache"])
+            assert torch.equal(pool[2 * l + 1:pages * n:n], own[l]["v_cache"])
