@@ -34,6 +34,11 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return t;
 }
 
+// Rotation per position of RoPE pair p: theta^(-2p/D).  Pair 0 turns by 1 whatever the base (0 x log2(inf) is NaN).
+__device__ __forceinline__ double inv_freq(int p, int D, double log2_theta) {
+  return p ? exp2(-2.0 * (double)p / (double)D * log2_theta) : 1.0;
+}
+
 // 8 consecutive elements as fp32 (one 16-byte bf16 load or two 16-byte fp32 loads).
 __device__ __forceinline__ void load8(const bf16* p, float (&v)[8]) {
   const bf16x8 x = ld8(p);
@@ -524,7 +529,7 @@ __global__ void __launch_bounds__(256) qk_norm_rope4_kernel(Parts qkv, const flo
   };
   load_heads(0);
   for (int p = threadIdx.x; p < half; p += blockDim.x) {
-    double phi = ((double)ctx_lens[b] + j) * exp2(-2.0 * (double)p / (double)D * log2_theta);
+    double phi = ((double)ctx_lens[b] + j) * inv_freq(p, D, log2_theta);
     const double two_pi = 6.283185307179586476925286766559;
     phi -= two_pi * rint(phi / two_pi);
     float sn, cs;
@@ -670,7 +675,7 @@ __global__ void __launch_bounds__(256) kv_append_kernel(AppendArgs a, double log
   const int D = a.D, half = D / 2, lph = D / 8, hpp = 256 / lph;   // heads per pass
   const size_t dst0 = ((size_t)pid * a.ps + pos % (unsigned)a.ps) * a.Hkv * D;
   for (int p = threadIdx.x; p < half; p += 256) {
-    double phi = (double)pos * exp2(-2.0 * (double)p / (double)D * log2_theta);
+    double phi = (double)pos * inv_freq(p, D, log2_theta);
     const double two_pi = 6.283185307179586476925286766559;
     phi -= two_pi * rint(phi / two_pi);
     float sn, cs;

@@ -94,6 +94,21 @@ def test_target_kv_block_attn(name):
     assert hspec.read_status(ws) == 0
 
 
+@pytest.mark.parametrize("theta", [1.0, 1e12, float("inf")])
+def test_rope_base(theta):
+    """Bases at the ends of their range: at 1 every pair turns by the position, at infinity pair 0 alone."""
+    cfg = SMALL["d64_k7"].replace(rope_theta=theta)
+    W, Wd = _weights(cfg, 9)
+    x = I.make_inputs(cfg, seed=9)
+    xin = I.normal("attn_x", (cfg.B, cfg.k, cfg.d_model), 1.0, 9, cfg.dtype)
+    d = dev(dict(x, xin=xin))
+    maxL = int(max(x["ctx_lens"]))
+    ws = hspec.workspace(hspec.target_kv_block_attn_workspace(cfg, x["page_table"].shape[1], x["num_pages"], maxL))
+    out = empty((cfg.B, cfg.k, cfg.d_model))
+    hspec.target_kv_block_attn(cfg, Wd, d["xin"], d, out, ws, maxL)
+    assert_close(host(out), O.attention_layer(O.f64(xin), W, x, cfg), "out")
+
+
 def _draft(cfg, W, Wd, x, maxL=None):
     d = dev(x)
     maxL = int(max(x["ctx_lens"])) if maxL is None else maxL
