@@ -34,6 +34,31 @@ def test_streamed_product(M, N, K, residual):
     assert torch.equal(out, first)   # one order of sums
 
 
+@pytest.mark.parametrize("M,N,K", [(3, 33, 64), (20, 300, 128), (60, 127, 192), (130, 698, 640), (352, 698, 640), (520, 1030, 256),
+                                   (16, 256, 4096), (300, 130, 2048)])
+def test_streamed_product_over_its_residual(M, N, K):
+    """C in the memory of R, products of one part and of several: every result reads its own residual before it is
+    stored; nothing past C is written."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    W = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    R = torch.randn(M, N, generator=g, device="cuda")
+    ws = hspec.workspace(hspec.linear_workspace(hspec.BF16, M, N, K))
+    ref = torch.empty(M, N, device="cuda")
+    hspec.linear(hspec.BF16, A, W, ref, ws, R=R)
+    guard = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = guard[:M * N].view(M, N)
+    out.copy_(R)
+    hspec.linear(hspec.BF16, A, W, out, ws, R=out)
+    assert torch.equal(out, ref)
+    assert guard[M * N:].isnan().all()
+    exact = A.double() @ W.double().t().contiguous() + R.double()
+    mag = A.double().abs() @ W.double().abs().t().contiguous() + R.double().abs()
+    assert ((ref.double() - exact).abs() <= (K + 1) * 2.0 ** -24 * mag + 1e-30).all()
+
+
 @pytest.mark.parametrize("M,N,K", [
     (1, 8, 8), (3, 15, 40), (16, 16, 256), (17, 40, 264), (32, 272, 1000), (33, 33, 2048), (64, 1030, 520),
     (65, 260, 72), (129, 130, 1000), (260, 300, 64),
