@@ -1190,6 +1190,28 @@ StreamPlan stream_plan(int M, int N, int K, bool a_lo, int cus) {
 // most this many elements (larger ones keep the kernels that write them directly).
 constexpr long long kStreamPlaneMax = 1LL << 22;
 
+// Whether every row of the outputs and of the residual starts 16 bytes apart (the weight-streaming kernel's stores).
+bool vec_rows(const GemmArgs& g) {
+  return !((g.C && g.ldc % 4) || ((g.C_hi || g.C_h16) && g.ldch % 4) || (g.R && g.ldr % 4));
+}
+
+// Products of few rows and many columns over a short K, which stay on the weight-streaming kernel: its workgroups walk
+// from column tile to column tile with the next one's W in flight, where these start and end a workgroup per
+// tile.  The line is where the two meet (us, weight-streaming and streamed).  Up to 64 rows: 16 x 65536 x 128 9.2 and
+// 11.0, x 320 16.7 and 15.7; 16 x 131072 x 256 20.1 and 27.3; 16 x 262144 x 64 16.2 and 32.0, x 512 60.9 and 69.4;
+// 16 x 32000 x 64 6.6 and 6.5.  More rows take a round of workgroups twice as long, so there a last round that is mostly
+// empty counts too: 128 x 65536 x 256 19.8 and 22.3, 128 x 66000 x 256 31.2 and 28.7, x 128 23.6 and 20.5;
+// 128 x 131072 x 256 36.7 and 41.8, x 320 43.2 and 43.6; 128 x 262144 x 512 99.3 and 104.
+bool skinny_better(const GemmArgs& g, int cus) {
+  if (g.M > 128 || g.W2 || g.nseg || g.N % 4 || !vec_rows(g)) return false;
+  const int nt = (g.N + SG_BN - 1) / SG_BN, nk = g.K / SG_KT;
+  if (nt < 2 * cus) return false;
+  if (g.M <= 64) return nk <= std::min(8, 2 * (nt / cus));
+  const int items = (nt + 1) / 2;   // (256 columns each)
+  const int over = items % cus;
+  return (over == 0 || over >= cus - cus / 8) && nk <= std::min(8, std::max(4, nt / cus));
+}
+
 // The plan launch_gemm runs a product with on the streamed path, bm = 0 if another path takes it.
 StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   StreamPlan p;
@@ -1205,6 +1227,7 @@ StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   // 32-bit element offsets inside a tile's rows of A, W, the output and the residual
   const int ldo = std::max({g.ldc, g.N, g.R ? g.ldr : 0});
   if (128LL * g.lda >= (1LL << 31) || 128LL * g.ldw >= (1LL << 31) || 128LL * ldo * 4 >= 0x7ffffeffLL) return p;
+  if (skinny_better(g, cus)) return p;
   p = stream_plan(g.M, g.N, g.K, g.A_lo != nullptr, cus);
   if (!p.bm) return p;
   const bool plain = g.C && !g.C_hi && !g.C_h16 && g.out_scale == 1.f;
@@ -1769,7 +1792,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     return hipSuccess;
   }
   SkPlan p = skinny_plan(g.M, g.N, g.K, g.A_lo != nullptr, g.w_f32, device_cus());
-  if ((g.C && g.ldc % 4) || ((g.C_hi || g.C_h16) && g.ldch % 4) || (g.R && g.ldr % 4)) p.use = false;   // 16-byte stores
+  if (!vec_rows(g)) p.use = false;   // 16-byte stores
   if (g.C_h16 && (!p.use || g.W2)) return hipErrorInvalidValue;   // only the weight-streaming path writes fp16
   if (g.C_l16 && !g.C_h16) return hipErrorInvalidValue;
   if (g.w_packed && (!p.use || g.N % 16 || g.K % BK || g.R)) return hipErrorInvalidValue;   // packed W: no residual

@@ -34,6 +34,31 @@ def test_streamed_product(M, N, K, residual):
     assert torch.equal(out, first)   # one order of sums
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 65536, 64), (16, 65412, 256), (17, 65540, 320), (64, 131073, 64), (64, 131076, 512), (65, 65536, 256), (96, 66000, 64),
+    (128, 131072, 256), (128, 131072, 320),
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_many_columns_short_k(M, N, K, residual):
+    """Both sides of the line between the streamed tiles and the weight-streaming kernel."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    g = torch.Generator(device="cuda").manual_seed(M * 5 + N)
+    A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    W = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    R = torch.randn(M, N, generator=g, device="cuda") if residual else None
+    guard = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = guard[:M * N].view(M, N)
+    ws = hspec.workspace(hspec.linear_workspace(hspec.BF16, M, N, K))
+    hspec.linear(hspec.BF16, A, W, out, ws, R=R)
+    ref = A.double() @ W.double().t().contiguous()
+    mag = A.double().abs() @ W.double().abs().t().contiguous()
+    if residual:
+        ref, mag = ref + R.double(), mag + R.double().abs()
+    assert ((out.double() - ref).abs() <= (K + 1) * 2.0 ** -24 * mag + 1e-30).all()
+    assert guard[M * N:].isnan().all()
+
+
 @pytest.mark.parametrize("M,N,K", [(3, 33, 64), (20, 300, 128), (60, 127, 192), (130, 698, 640), (352, 698, 640), (520, 1030, 256),
                                    (16, 256, 4096), (300, 130, 2048)])
 def test_streamed_product_over_its_residual(M, N, K):
