@@ -1142,6 +1142,8 @@ __global__ void __launch_bounds__(SG_NT) gemm_stream_kernel(GemmArgs g, StreamPl
   }
 }
 
+bool big_ok(const GemmArgs& g);
+
 // Rows of a streamed tile: as few as cover M, up to 128.
 constexpr int stream_bm(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
 
@@ -1212,6 +1214,17 @@ bool skinny_better(const GemmArgs& g, int cus) {
   return (over == 0 || over >= cus - cus / 8) && nk <= std::min(8, std::max(4, nt / cus));
 }
 
+// Products of a handful of tiles from 256 rows, which the large tiles finish sooner where K has to be split: their parts
+// are as many as there are CUs, and the fix-up reads whole tiles (256 x 96 x 640 8.8 us, streamed 10.0; 512 x 96 x 1024 9.3 and
+// 10.1; 256 x 300 x 640 9.2 and 10.2).  Not where the next kernel adds up the parts, which saves the streamed ones a launch.
+// With more tiles, or up to K = 320, which stays in one part, the streamed ones win (700 x 300 x 640 10.8 and
+// 10.2, 256 x 96 x 320 9.2 and 8.3, 512 x 96 x 2048 10.7 and 10.4).
+bool big_better(const GemmArgs& g) {
+  const int nk = g.K / SG_KT;
+  if (g.M < 256 || g.A_lo || g.defer || nk < 8 || nk > 24) return false;
+  return ((g.M + 127) / 128) * ((g.N + SG_BN - 1) / SG_BN) <= 8 && big_ok(g);
+}
+
 // The plan launch_gemm runs a product with on the streamed path, bm = 0 if another path takes it.
 StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   StreamPlan p;
@@ -1227,7 +1240,7 @@ StreamPlan stream_plan_for(const GemmArgs& g, int cus) {
   // 32-bit element offsets inside a tile's rows of A, W, the output and the residual
   const int ldo = std::max({g.ldc, g.N, g.R ? g.ldr : 0});
   if (128LL * g.lda >= (1LL << 31) || 128LL * g.ldw >= (1LL << 31) || 128LL * ldo * 4 >= 0x7ffffeffLL) return p;
-  if (skinny_better(g, cus)) return p;
+  if (skinny_better(g, cus) || big_better(g)) return p;
   p = stream_plan(g.M, g.N, g.K, g.A_lo != nullptr, cus);
   if (!p.bm) return p;
   const bool plain = g.C && !g.C_hi && !g.C_h16 && g.out_scale == 1.f;

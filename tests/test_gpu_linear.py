@@ -59,6 +59,35 @@ def test_many_columns_short_k(M, N, K, residual):
     assert guard[M * N:].isnan().all()
 
 
+@pytest.mark.parametrize("M,N,K", [
+    # a handful of tiles of 256 rows and more, every one split over K: whole and scalar fix-up, ragged M and N
+    (256, 96, 640), (300, 98, 1024), (1000, 40, 512), (512, 256, 1536),
+    # K that is no multiple of 64 (from 129 rows)
+    (129, 130, 96), (300, 258, 1056), (200, 2049, 160), (513, 1028, 32),
+    # more than one round of tiles: 256-row tiles with the last 8 split (ragged M and N; scalar fix-up), 128-row tiles
+    (800, 16768, 1024), (800, 16766, 1024), (800, 16768, 992), (256, 33000, 256),
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_large_tiles(M, N, K, residual):
+    """The large tiles: whole tiles, tiles split over K with their fix-up, ragged edges."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    g = torch.Generator(device="cuda").manual_seed(M * 3 + N + K)
+    A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    W = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    R = torch.randn(M, N, generator=g, device="cuda") if residual else None
+    guard = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = guard[:M * N].view(M, N)
+    ws = hspec.workspace(hspec.linear_workspace(hspec.BF16, M, N, K))
+    hspec.linear(hspec.BF16, A, W, out, ws, R=R)
+    ref = A.double() @ W.double().t().contiguous()
+    mag = A.double().abs() @ W.double().abs().t().contiguous()
+    if residual:
+        ref, mag = ref + R.double(), mag + R.double().abs()
+    assert ((out.double() - ref).abs() <= (K + 1) * 2.0 ** -24 * mag + 1e-30).all()
+    assert guard[M * N:].isnan().all()
+
+
 @pytest.mark.parametrize("M,N,K", [(3, 33, 64), (20, 300, 128), (60, 127, 192), (130, 698, 640), (352, 698, 640), (520, 1030, 256),
                                    (16, 256, 4096), (300, 130, 2048)])
 def test_streamed_product_over_its_residual(M, N, K):
