@@ -7,8 +7,9 @@
 //
 // Paths (launch_gemm): bf16 W, K in whole 64-wide tiles, up to 128 rows or one round of 128 x 128
 // tiles: gemm_stream_kernel; more than that, K % 32 == 0: gemm_big_kernel; the packed W, and bf16 W of up to 128
-// rows that the streamed path does not take: skinny_kernel; fp32 W of up to 64 rows: gemm_f32_small; the
-// rest: gemm_kernel, described next.
+// rows that the streamed path does not take: skinny_kernel; fp32 W of up to 64 rows, or of few 64 x 16 tiles:
+// gemm_f32_small; the rest: gemm_kernel, described next.  Where the lines lie: stream_plan, skinny_better, big_better
+// and f32_small_ok.
 //
 // gemm_kernel: 4 waves per workgroup in a WM x WN grid, each wave owns TM x TN blocks of 32x32
 // computed with v_mfma_f32_32x32x16_bf16.  K is consumed in 64-wide tiles staged through
@@ -256,8 +257,8 @@ __device__ __forceinline__ const bf16* w_segment(const GemmArgs& g, int n0, int&
   return w;
 }
 
-// fp32 storage at up to 64 rows (small models, single requests): a chain of latencies, so as many
-// workgroups as there are 16-column tiles, and one round of loads each where K allows it.  The eight waves of
+// fp32 storage at few rows or columns (small models, single requests): a chain of latencies, so as many
+// workgroups as there are tiles of 64 rows and 16 columns, and one round of loads each where K allows it.  The eight waves of
 // a workgroup take every eighth 32-wide k-step, straight from memory into v_mfma_f32_16x16x32_bf16
 // operands (W as fp32, split into hi/lo planes in registers; A as planes or fp32), and their sums meet
 // in LDS in wave order.  Against a split pass over W (and A) and 64 x 256 tiles, linear() with its status
@@ -269,7 +270,7 @@ __global__ void __launch_bounds__(512) gemm_f32_small(GemmArgs g) {
   __shared__ f32x4 red[8][MT][64];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = blockIdx.x * 16;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 64;
   int seg0, seg1;
   const float* W = reinterpret_cast<const float*>(w_segment(g, n0, seg0, seg1));   // (segments are whole tiles)
   const float* wrow = W + (size_t)(min(n0 + l16, g.N - 1) - seg0) * g.ldw;         // (columns past N are not stored)
@@ -288,7 +289,7 @@ __global__ void __launch_bounds__(512) gemm_f32_small(GemmArgs g) {
     F8 af[AF ? MT : 1];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      const size_t o = (size_t)min(16 * t + l16, g.M - 1) * g.lda + kc;   // (rows past M are not stored)
+      const size_t o = (size_t)min(m0 + 16 * t + l16, g.M - 1) * g.lda + kc;   // (rows past M are not stored)
       if constexpr (AF) {
         af[t].a = *reinterpret_cast<const f32x4*>(Af + o);
         af[t].b = *reinterpret_cast<const f32x4*>(Af + o + 4);
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(512) gemm_f32_small(GemmArgs g) {
   if (n >= g.N) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int m = 16 * t + 4 * g4 + i;
+    const int m = m0 + 16 * t + 4 * g4 + i;
     if (m >= g.M) break;
     float x = v[i];
     if (g.R) {
@@ -1673,14 +1674,21 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
                 : launch_one<WM, WN, TM, TN, false, false, false>(g, s);
 }
 
-// Whether gemm_f32_small takes the product: its 16-column tiles must not straddle a row segment.
+// Whether gemm_f32_small takes the product: its 16-column tiles must not straddle a row segment, and past 64 rows its
+// workgroups of 64 x 16 must come in a few rounds, since each reads its rows of A again.  Against the 128 x 128 tiles
+// of gemm_kernel: 220 x 64 x 2048 70 -> 22 us, 128 x 4096 x 4096 222 -> 75, 400 x 2048 x 4096 (896 workgroups) 141 -> 128,
+// 512 x 2048 x 4096 (1024) 141 -> 143, 512 x 4096 x 4096 146 -> 282.  Up to 64 rows it takes all but 33 rows and more over
+// a K that feeds two of its eight waves, with N in the hundreds of thousands (33 x 262144 x 16 37 us, here 55; 64 x
+// 262144 x 72 71 and 57; 64 x 65536 x 16 19 and 18).
 bool f32_small_ok(const GemmArgs& g) {
-  if (!g.w_f32 || g.M > 64 || g.K % 8) return false;
+  if (!g.w_f32 || g.K % 8) return false;
+  const long long wgs = (g.N + 15LL) / 16 * ((g.M + 63) / 64);
+  if (g.M > 64 ? 2 * wgs > 7LL * device_cus() : g.M > 32 && g.K <= 64 && wgs > 32LL * device_cus()) return false;
   if (g.W2 && (g.N1 % 16 || g.N2 % 16)) return false;
   return !g.nseg || g.seg_rows % 16 == 0;
 }
 hipError_t launch_f32_small(const GemmArgs& g, hipStream_t s) {
-  const dim3 grid((g.N + 15) / 16), nt(512);
+  const dim3 grid((g.N + 15) / 16, (g.M + 63) / 64), nt(512);
   auto go = [&](auto MT) {
     constexpr int T = decltype(MT)::value;
     if (g.a_f32) hipLaunchKernelGGL((gemm_f32_small<T, true>), grid, nt, 0, s, g);

@@ -136,6 +136,33 @@ def test_fp32_product(M, N, K):
     assert guard[M * N:].isnan().all()
 
 
+@pytest.mark.parametrize("M,N,K", [
+    # several groups of 64 rows of 16-column tiles, up to the last that still takes them
+    (65, 16, 2048), (127, 40, 264), (220, 64, 520), (400, 2040, 72), (1000, 33, 1032), (3000, 17, 40),
+    # one column tile more: 128 x 128 tiles; up to 128 rows: 128 x 256; up to 64 rows with two k-steps: 64 x 256
+    (400, 2049, 72), (300, 2890, 264), (100, 7300, 136), (40, 131100, 64),
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_fp32_product_of_many_rows(M, N, K, residual):
+    """The bound of test_fp32_product on both sides of the line between the 16-column tiles and the large ones."""
+    import torch
+    from paper_2609_24197_amd import hspec
+    g = torch.Generator(device="cuda").manual_seed(M * 13 + N)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda")
+    R = torch.randn(M, N, generator=g, device="cuda") if residual else None
+    guard = torch.full((M * N + 64,), float("nan"), device="cuda")
+    out = guard[:M * N].view(M, N)
+    ws = hspec.workspace(hspec.linear_workspace(hspec.F32, M, N, K))
+    hspec.linear(hspec.F32, A, W, out, ws, R=R)
+    ref = A.double() @ W.double().t().contiguous()
+    mag = A.double().abs() @ W.double().abs().t().contiguous()
+    if residual:
+        ref, mag = ref + R.double(), mag + R.double().abs()
+    assert ((out.double() - ref).abs() <= (3 * 2.0 ** -18 + (3 * K + 1) * 2.0 ** -24) * mag).all()
+    assert guard[M * N:].isnan().all()
+
+
 @pytest.mark.parametrize("M,K", [(5, 40), (64, 64), (100, 128), (300, 264)])
 @pytest.mark.parametrize("over", ["A", "W"])
 def test_fp32_product_over_an_operand(M, K, over):
