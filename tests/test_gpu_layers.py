@@ -20,13 +20,18 @@ SMALL = {
                                  D=128, lengths="list:45,200"),
     "window_causal": I.StepConfig(name="s", B=2, k=16, d_model=256, H=4, P=64, N=128, G=1, chunk=8, Hq=32, Hkv=8,
                                   D=128, lengths="list:900,100", window=256, block_causal=True),
-    # B*k = 160 rows: the pipelined dense GEMMs, the fused Q/K/V product with a ragged last tile
+    # B*k = 160 rows: streamed products, the fused Q/K/V product over its weight segments, a ragged last row tile
     "m160_fused_qkv": I.StepConfig(name="s", B=10, k=16, d_model=320, H=5, P=64, N=32, G=1, chunk=16, Hq=8,
                                    Hkv=2, D=128, lengths="uniform:1:700"),
-    # B*k = 640 rows: the 256 x 256 products, with k-split last tiles (in_proj, out_proj with
-    # hi/lo inputs; Q/K/V over weight segments of 4096 and 1024 rows; O projection)
+    # B*k = 640 rows, streamed: at most 240 tiles of 128 x 128 (Q/K/V over weight segments of 4096 and 1024 rows)
     "m640_large_tiles": I.StepConfig(name="s", B=40, k=16, d_model=512, H=8, P=64, N=16, G=1, chunk=16, Hq=32,
                                      Hkv=8, D=128, lengths="uniform:0:300"),
+    # B*k = 640 rows past one round of 128 x 128 tiles: Q/K/V (280 of them, weight segments of 5120 and 1024 rows) on
+    # the large tiles; with hi/lo A every product past 512 rows is, most of them split over K
+    "m640_past_one_round": I.StepConfig(name="s", B=40, k=16, d_model=512, H=8, P=64, N=16, G=1, chunk=16, Hq=40,
+                                        Hkv=8, D=128, lengths="uniform:0:300"),
+    "m640_precise": I.StepConfig(name="s", B=40, k=16, d_model=512, H=8, P=64, N=16, G=1, chunk=16, Hq=40,
+                                 Hkv=8, D=128, lengths="uniform:0:300", precise_io=True),
     # fp32 storage with the 4-tap conv (token-parallel conv kernel, fp32 weights), ragged k
     "f32_conv4": I.StepConfig(name="s", B=2, k=5, d_model=256, H=4, P=64, N=16, G=1, chunk=4, Hq=8, Hkv=2,
                               D=128, lengths="list:33,150", dtype="f32"),

@@ -1,6 +1,7 @@
-"""Streamed products (row-major bf16 W): tile edges, remainders, K splits and segments against
-float64.  The products are exact in fp32 (8 x 8 significant bits), so only the fp32 sums differ:
-K additions in any order are within K 2^-24 of the sum of magnitudes."""
+"""Streamed products (row-major bf16 W, one plane of A), the paths beside them and fp32 operands: tile edges, remainders
+and K splits against float64 (row segments and hi/lo A are in test_gpu_plane_sums.py).  The products of bf16 operands are
+exact in fp32 (8 x 8 significant bits), so only the fp32 sums differ: K additions in any order are within K 2^-24 of the sum
+of magnitudes."""
 import pytest
 
 pytestmark = pytest.mark.gpu

@@ -27,12 +27,13 @@ def _small_attn_cfg(**kw):
 @pytest.mark.parametrize("M,N,K", [(4, 256, 256), (64, 1000, 512), (100, 384, 264), (128, 512, 1024),
                                    (300, 700, 4096), (1, 4096, 4096), (48, 5000, 4096), (20, 3000, 1024),
                                    (8, 300, 264), (64, 200000, 160),
-                                   # 65..128 rows: 128-row weight streaming
+                                   # 65..128 rows: 128-row tiles, streamed over K
                                    (65, 4096, 1024), (128, 16768, 512), (96, 300, 512), (127, 1000, 2048),
-                                   # 256 x 256 tiles: whole tiles, k-split last tiles, ragged M and N
+                                   # many rows: bf16 streamed over K while 128 x 128 tiles fill one round of CUs
+                                   # (1536 x 4096: the large tiles; those split over K are in test_gpu_linear.py)
                                    (512, 768, 256), (1024, 2304, 1024), (777, 1000, 512), (1536, 4096, 512),
                                    (600, 300, 4096),
-                                   # 256..511 rows: one or two row tiles, most columns k-split
+                                   # 256..511 rows: the same two paths (256 x 16768: the large tiles)
                                    (256, 16768, 512), (384, 4096, 1024), (257, 1000, 2048)])
 def test_linear(dtype, M, N, K):
     print(f"[linear] dtype={dtype} M={M} N={N} K={K}", flush=True)
