@@ -537,11 +537,7 @@ __global__ void __launch_bounds__(256) qk_norm_rope4_kernel(Parts qkv, const flo
     s_cs[p] = cs;
     s_sn[p] = sn;
   }
-  f32x4 gq1 = {0.f, 0.f, 0.f, 0.f}, gq2 = gq1;
-  if (Hq > 0) {
-    gq1 = *reinterpret_cast<const f32x4*>(qw + i0);
-    gq2 = *reinterpret_cast<const f32x4*>(qw + half + i0);
-  }
+  const f32x4 gq1 = *reinterpret_cast<const f32x4*>(qw + i0), gq2 = *reinterpret_cast<const f32x4*>(qw + half + i0);
   const f32x4 gk1 = *reinterpret_cast<const f32x4*>(kw + i0), gk2 = *reinterpret_cast<const f32x4*>(kw + half + i0);
   __syncthreads();
   float cs[4], sn[4];
