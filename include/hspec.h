@@ -404,7 +404,9 @@ hspec_status hspec_gather_slots(int B, int max_pages, int page_size, int num_pag
  * Plain projection C [M, N] fp32 = A [M, K] W [N, K]^T (+ R [M, N] fp32 if R != NULL), A and W
  * in the storage dtype (the GEMM used by every projection above: Proj_r and Proj_dS of the
  * Sec. 3.3.1 fusion equation, and the bias-free linear maps of the Mamba and attention modules
- * of Sec. 3.3.1-3.3.2).  Row-major, caller-owned device memory; K must be a multiple of 8
+ * of Sec. 3.3.1-3.3.2).  Row-major, caller-owned device memory.  C may be R; with HSPEC_F32 it may
+ * also lie over A or W (which it then overwrites: the product reads a copy in the workspace), with
+ * HSPEC_BF16 it must not.  K must be a multiple of 8
  * (else HSPEC_ERR_UNSUPPORTED); the workspace comes from hspec_linear_workspace and must be
  * 256-byte aligned (else HSPEC_ERR_WORKSPACE).
  */

@@ -1156,7 +1156,8 @@ constexpr int stream_bm(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
 // tiles are faster (1024 x 6144 x 4096: 74 us against 78; 192 x 24576 x 4096 hi/lo 105 against 122, since a
 // 128-wide column tile re-reads A from L2 twice as often: at 128 x 24576 x 4096 hi/lo the DMA of A alone
 // takes 37 us, of W 41, both 59, the whole product 65), within it these (1024 x 4096 x 4096: 41 us
-// against 53; 512 x 6320 x 4096: 40 against 50).  With hi/lo A the line is at 512 rows: inside the
+// against 53; 512 x 6320 x 4096: 40 against 50; inside the 64-request step, whose 1024-row products it moves, the step
+// takes 1980 us with these and 2008 with large tiles).  With hi/lo A the line is at 512 rows: inside the
 // drafter's forward, where the whole chip multiplies, 1024 x 4096 x 8192 took 181 us against 149 with its fix-up
 // and 1024 x 4096 x 4096 101 against 88 (four-layer forward with these, large tiles: 768 rows 3766, 3696 us; 512 rows
 // 2551, 2595; 256 rows 1569, 1700).

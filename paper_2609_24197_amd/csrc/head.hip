@@ -21,7 +21,7 @@
 namespace hspec {
 namespace {
 
-constexpr int MK_COLS = 128;   // vocabulary columns per workgroup (4 waves x 2 MFMA column blocks)
+constexpr int MK_COLS = 128;   // vocabulary columns per workgroup (rank 256: 8 waves x 16; others: 4 waves x 2 x 16)
 constexpr int MK_ROWS = 64;    // requests per tile (4 MFMA row blocks)
 constexpr int ST_BAD_TOKEN = 4;
 constexpr int ST_NONFINITE = 8;

@@ -5,17 +5,18 @@
 // Per head (scalar decay a_t = exp(dt_t A)), within a chunk with l_t = sum_{u<=t} dt_u A:
 //   y_t = exp(l_t) C_t S_in^T + sum_{s<=t} exp(l_t - l_s) dt_s (C_t . B_s) x_s + D x_t
 //   S_out = exp(l_end) S_in + sum_s exp(l_end - l_s) dt_s x_s (outer) B_s
-// One wave owns one (request, head).  C S_in^T (16 x N x 64) and C B^T (16 x N x 16) run on
+// One wave owns one (request, head).  C S_in^T (16 x N x 64), C B^T (16 x N x 16) and the
+// intra-chunk product of the 16 x 16 decay-weighted mixing matrix M with x (M as hi/lo planes) run on
 // v_mfma_f32_16x16x32_bf16; operands given as bf16 hi/lo planes use three products so fp32
-// values survive.  The 16x16 decay-weighted mixing matrix and the x tile go through LDS and
-// the intra-chunk product is done in fp32 on the VALU.  The chunk-local cumulative sum of
-// dt*A is a 16-lane shuffle scan.  When the block fits one chunk and no final state is
-// requested (ssd_scan_one), the initial state is read straight from global memory into MFMA
-// fragments (as bf16 hi/lo planes, or as one fp16 plane multiplied with C rounded to fp16 on
-// v_mfma_f32_16x16x32_f16); with the fp16 plane and heads in groups of 4 that share B and C
-// (the drafting step), ssd_scan_grp runs those 4 heads in one workgroup, one wave each, and
-// shares the C and C B^T work through LDS; otherwise (ssd_scan_state) the fp32 state stays in the
-// accumulators of its own update from S0 to S_final.
+// values survive.  The chunk-local cumulative sum of dt*A is a 16-lane shuffle scan.
+//   * One chunk and no final state (ssd_scan_one): the initial state is read straight from global
+//     memory into MFMA fragments (as bf16 hi/lo planes, or as one fp16 plane multiplied with C
+//     rounded to fp16 on v_mfma_f32_16x16x32_f16); M and the x tile go through LDS in fp32.
+//   * With the fp16 plane and heads in groups of 4 that share B and C (the drafting step),
+//     ssd_scan_grp runs those 4 heads in one workgroup, one wave each, and shares the C and C B^T
+//     work through LDS.
+//   * Otherwise (ssd_scan_state) the fp32 state stays in the accumulators of its own update from S0
+//     to S_final; x and B lie in LDS as they are, M never leaves its registers.
 #include "common.h"
 #include "kernels.h"
 
